@@ -192,11 +192,7 @@ size_t prenom_workspace_size(const prenom_arch* arch, int64_t n_rays, int32_t n_
  * Outputs: rgb [n][3], depth [n], opacity [n]; loss [1] (device scalar, or
  *   NULL); sample_out [n][S][4] = (sigma, r, g, b) per sample, or NULL.
  * workspace: >= prenom_workspace_size(arch, n, S, cfg->recompute) bytes,
- *   256-byte aligned.  In the stored form it also
- *   receives the per-tile histograms of the hash-table gradient's records
- *   (per level and block of 512 samples: one per corner of every sample,
- *   a corner that repeats the previous sample's row joining its record)
- *   that the backward's table-gradient scatter starts from.  Unless cfg->recompute is set, it
+ *   256-byte aligned.  Unless cfg->recompute is set, it
  *   carries the per-sample features and per-ray results that
  *   prenom_render_bwd reads: pass the same workspace and unchanged inputs to
  *   the matching bwd call.
@@ -220,15 +216,10 @@ prenom_status prenom_render_fwd(const prenom_model* model, const prenom_render_c
  * same workspace and inputs; with it, only the inputs must match.  The
  * backward leaves what the forward wrote unchanged, so several backward calls
  * (for instance with different upstream gradients) may follow one forward.  A call
- * that breaks this gives a wrong gradient but stays within its arrays: the
- * scatter checks that the forward's histograms hold no more records than
- * there are corners of samples, else it adds nothing to the table gradient,
- * and every record it writes or reads is bounded by the workspace's record
- * arrays.
- * The table gradient is accumulated per 2^13-row tile in 64-bit fixed point
- * (order independent); tiles that receive more than 2^21 contributions are
- * split and their partial sums added with FP32 atomics, so only those may
- * differ in the last bits between runs.
+ * that breaks this gives a wrong gradient but stays within its arrays.
+ * The table gradient is accumulated per 2^13-row tile in 64-bit fixed point,
+ * which does not depend on the order of the additions: its bits are the same
+ * from run to run.
  * ---------------------------------------------------------------------- */
 prenom_status prenom_render_bwd(const prenom_model* model, const prenom_render_cfg* cfg,
                                 const float* ray_obj, const float* t, const float* dt,
@@ -391,7 +382,7 @@ typedef struct prenom_mlp_tiles {
  *   worst-case records (64 bytes per sample and level) fit the budget; an
  *   object above it is a group of its own.  The workspace holds the largest
  *   group's records, so a smaller budget trades a smaller workspace for more
- *   launches (six per group); the gradients do not depend on the grouping. */
+ *   launches (four per group); the gradients do not depend on the grouping. */
 #define PRENOM_RECORD_BUDGET ((int64_t)4 << 30)
 typedef struct prenom_batch {
     int32_t n_objects;

@@ -69,16 +69,6 @@ void prof_record(const char* name, hipEvent_t a, hipEvent_t b)
     g_prof_records.push_back({name, a, b});
 }
 
-// Compute units of the current device (persistent grids size to it).
-int device_cus()
-{
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus <= 0)
-        return 256;
-    return cus;
-}
-
 // Shape rules an architecture must satisfy (independent of what is compiled).
 prenom_status check_arch(const prenom_arch* a)
 {
@@ -222,7 +212,7 @@ using namespace prenom::host;
 
 struct WsLayout {
     size_t y, sc, dout, dy, ray_state, loss_partial, mlp_partial, act;
-    size_t counts, offsets, block_max, level_max, tile_exp, tile_total, tile_start, chunk_start, work_counter, recs, total;
+    size_t seg, block_max, level_exp, parts, recs, total;
     int n_loss_blocks, n_mlp_slots;
     ScatterObj plan;
 };
@@ -246,6 +236,14 @@ int64_t buffered_rays(int64_t n_rays, int32_t S, bool recompute)
     if (!recompute) return n_rays;
     const int64_t c = recompute_chunk_rays(S);
     return n_rays < c ? n_rays : c;
+}
+
+// Scatter geometry of one object in a pass of its own.
+ScatterObj scatter_plan(const GridInfo& g, int64_t n_s)
+{
+    ScatterObj o = scatter_obj(g, n_s);
+    scatter_split(o, scatter_target(scatter_records(o)));
+    return o;
 }
 
 WsLayout ws_layout(const prenom_arch* a, int64_t n_rays_all, int32_t S, bool recompute)
@@ -272,26 +270,15 @@ WsLayout ws_layout(const prenom_arch* a, int64_t n_rays_all, int32_t S, bool rec
     off = align_up(off + (size_t)w.n_mlp_slots * (size_t)mlp_params(a) * sizeof(float));
     w.act = off;
     off = align_up(off + (size_t)mlp_act_floats(mlp_shape(a), (int64_t)n_s) * sizeof(float));
-    w.plan = scatter_obj(grid_info(a), (int64_t)n_s);
-    const size_t nt = (size_t)w.plan.n_tiles;
-    w.counts = off;
-    off = align_up(off + nt * (size_t)w.plan.n_blocks * sizeof(uint32_t));
-    w.offsets = off;
-    off = align_up(off + nt * (size_t)w.plan.n_blocks * sizeof(uint32_t));
+    w.plan = scatter_plan(grid_info(a), (int64_t)n_s);
+    w.seg = off;
+    off = align_up(off + (size_t)scatter_segs(w.plan) * sizeof(uint16_t));
     w.block_max = off;
-    off = align_up(off + (size_t)a->n_levels * (size_t)w.plan.n_blocks * sizeof(float));
-    w.level_max = off;
-    off = align_up(off + (size_t)a->n_levels * sizeof(float));
-    w.tile_exp = off;
-    off = align_up(off + nt * sizeof(int32_t));
-    w.tile_total = off;
-    off = align_up(off + nt * sizeof(uint64_t));
-    w.tile_start = off;
-    off = align_up(off + (nt + 1) * sizeof(uint64_t));
-    w.chunk_start = off;
-    off = align_up(off + (nt + 2) * sizeof(uint64_t));
-    w.work_counter = off;
-    off = align_up(off + sizeof(uint64_t));
+    off = align_up(off + (size_t)scatter_items(w.plan) * sizeof(float));
+    w.level_exp = off;
+    off = align_up(off + (size_t)a->n_levels * sizeof(int32_t));
+    w.parts = off;
+    off = align_up(off + (size_t)w.plan.n_parts * scatter_part_bytes());
     w.recs = off;
     off = align_up(off + (size_t)scatter_records(w.plan) * sizeof(uint64_t));
     w.total = off;
@@ -329,20 +316,6 @@ size_t prior_refresh_ws(const prenom_arch* a, int32_t R, size_t* sc_off)
     const size_t y = align_up((size_t)c * a->n_levels * a->n_features * sizeof(float));
     if (sc_off) *sc_off = y;
     return y + align_up((size_t)c * 4 * sizeof(float));
-}
-
-// Tile histograms of the training forward, in the workspace's scatter counts,
-// laid out for the scatter plan of the samples encoded.
-TileHist tile_hist(const WsLayout& w, const ScatterObj& plan, void* workspace)
-{
-    TileHist h{};
-    h.counts = at<uint32_t>(workspace, w.counts);
-    h.n_blocks = plan.n_blocks;
-    for (int l = 0; l < plan.grid.n_levels; ++l) {
-        h.tiles[l] = plan.tiles[l];
-        h.tile_base[l] = plan.tile_base[l];
-    }
-    return h;
 }
 
 }  // namespace
@@ -445,17 +418,14 @@ prenom_status prenom_render_fwd(const prenom_model* model, const prenom_render_c
     const void* tlp = a->table_dtype == PRENOM_F16 ? model->table_lp : nullptr;
     double* loss_partial = loss ? at<double>(workspace, w.loss_partial) : nullptr;
     // The stored form runs once over all rays and keeps features, head outputs
-    // and per-ray results (and the scatter's histograms) for render_bwd; the
+    // and per-ray results for render_bwd; the
     // recompute form runs pass by pass over chunks of rays and keeps nothing.
     const int64_t chunk = recompute ? recompute_chunk_rays(S) : (n_rays > 0 ? n_rays : 1);
     for (int64_t r0 = 0; r0 < n_rays; r0 += chunk) {
         const int64_t nr = n_rays - r0 < chunk ? n_rays - r0 : chunk;
         const int64_t n_s = nr * S;
-        const ScatterObj plan = scatter_obj(g, n_s);
-        const TileHist h = tile_hist(w, plan, workspace);
         PRENOM_LAUNCH("k_encode_fwd", s,
-                      launch_encode_samples(g, model->params, tlp, ray_obj + 6 * r0, t + S * r0, nr, S, y, s,
-                                            recompute ? nullptr : &h));
+                      launch_encode_samples(g, model->params, tlp, ray_obj + 6 * r0, t + S * r0, nr, S, y, s));
         PRENOM_LAUNCH("k_mlp_fwd", s,
                       mlp_fwd_any(m, model->params + table_params(a), y, n_s, sc, at<float>(workspace, w.act), s));
         CompositeArgs c{};
@@ -510,7 +480,7 @@ prenom_status prenom_render_bwd(const prenom_model* model, const prenom_render_c
     for (int64_t r0 = 0; r0 < n_rays; r0 += chunk) {
         const int64_t nr = n_rays - r0 < chunk ? n_rays - r0 : chunk;
         const int64_t n_s = nr * S;
-        const ScatterObj plan = scatter_obj(g, n_s);
+        const ScatterObj plan = scatter_plan(g, n_s);
         const float* ro = ray_obj + 6 * r0;
         const float* tc = t + S * r0;
         CompositeArgs c{};
@@ -531,10 +501,9 @@ prenom_status prenom_render_bwd(const prenom_model* model, const prenom_render_c
         c.ray_state = at<float>(workspace, w.ray_state);
         if (recompute) {
             // rebuild this pass's features, head outputs and per-ray results
-            // (and the scatter's tile histograms) as render_fwd would have left them
-            const TileHist h = tile_hist(w, plan, workspace);
+            // as render_fwd would have left them
             PRENOM_LAUNCH("k_encode_fwd", s,
-                          launch_encode_samples(g, model->params, tlp, ro, tc, nr, S, at<float>(workspace, w.y), s, &h));
+                          launch_encode_samples(g, model->params, tlp, ro, tc, nr, S, at<float>(workspace, w.y), s));
             PRENOM_LAUNCH("k_mlp_fwd", s, mlp_fwd_any(m, model->params + table_params(a), at<float>(workspace, w.y),
                                                       n_s, at<float>(workspace, w.sc), at<float>(workspace, w.act), s));
             CompositeArgs f = c;
@@ -562,32 +531,24 @@ prenom_status prenom_render_bwd(const prenom_model* model, const prenom_render_c
         sa.one = plan;
         sa.objs = nullptr;
         sa.tiles_max = scatter_tiles_max(plan);
-        sa.reduce_blocks = device_cus();
-        sa.n_tiles = plan.n_tiles;
         sa.n_items = scatter_items(plan);
+        sa.n_ritems = plan.n_ritems;
+        sa.n_ctiles = plan.n_ctiles;
         sa.n_levels_total = a->n_levels;
         sa.ray_obj = ro;
         sa.t = tc;
         sa.dy = reinterpret_cast<const float2*>(dy);
         sa.g_table = model->grads;
-        sa.counts = at<uint32_t>(workspace, w.counts);
-        sa.offsets = at<uint32_t>(workspace, w.offsets);
         sa.block_max = at<float>(workspace, w.block_max);
-        sa.level_max = at<float>(workspace, w.level_max);
-        sa.tile_exp = at<int32_t>(workspace, w.tile_exp);
-        sa.tile_total = at<uint64_t>(workspace, w.tile_total);
-        sa.tile_start = at<uint64_t>(workspace, w.tile_start);
-        sa.chunk_start = at<uint64_t>(workspace, w.chunk_start);
-        sa.work_counter = at<unsigned long long>(workspace, w.work_counter);
+        sa.level_exp = at<int32_t>(workspace, w.level_exp);
+        sa.seg = at<uint16_t>(workspace, w.seg);
+        sa.parts = at<unsigned long long>(workspace, w.parts);
         sa.recs = at<uint64_t>(workspace, w.recs);
         sa.n_records = scatter_records(plan);
         sa.nonfinite = model->loss_scale ? model->scaler_state : nullptr;
-        sa.fwd_counts = 1;  // render_fwd (or the recompute above) wrote the tile histograms
-        sa.merge_runs = 1;
-        sa.chunk_min_bits = 21;  // one pass over one object: items of 2^21 records keep the CUs busy
         sa.compact = a->table_dtype == PRENOM_F16;
         for (int ph = 0; ph < kScatterPhases; ++ph)
-            PRENOM_LAUNCH(ph == 0 ? "k_scatter_dymax" : kScatterPhaseNames[ph], s, launch_scatter_phase(sa, ph, s));
+            PRENOM_LAUNCH(kScatterPhaseNames[ph], s, launch_scatter_phase(sa, ph, s));
     }
     return PRENOM_OK;
 }

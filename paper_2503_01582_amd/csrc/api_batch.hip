@@ -3,7 +3,7 @@
 // sequence of each call.  Host code only.
 //
 // Every phase is one launch over all objects (sampler, encoding, compositing,
-// loss, MLP-gradient reduction, the five scatter kernels, Adam); the MLP is
+// loss, MLP-gradient reduction, the scatter kernels, Adam); the MLP is
 // one launch per distinct MLP shape, since the shape fixes the kernel's
 // registers and LDS.  The plan is a pure function of the objects, the tile
 // shapes and S, so the calls need no host-device traffic and a step can be
@@ -40,11 +40,11 @@ struct Group {
 
 // One pass of the table-gradient scatter: consecutive whole objects
 // [first, first + count), with their scatter geometry re-based so the pass's
-// items, tiles and levels count from 0 (counts, block maxima, dy and the
-// gradient keep the batch's offsets).
+// items, levels, segments, reduce items and partial sums count from 0 (dy and
+// the gradient keep the batch's offsets).
 struct ScatterGroup {
     int first = 0, count = 0;
-    int64_t n_items = 0, n_tiles = 0, records = 0;
+    int64_t n_items = 0, records = 0, n_segs = 0, n_ritems = 0, n_ctiles = 0, n_parts = 0;
     int32_t n_levels = 0;
 };
 
@@ -57,14 +57,14 @@ struct Plan {
     std::vector<MlpRed> red;
     std::vector<MlpWork> fwd, bwd;
     std::vector<Group> groups;
-    int64_t n_rays = 0, n_params = 0, n_mlp_total = 0, n_tiles = 0, n_items = 0, records = 0;
-    int64_t y_floats = 0, partial_floats = 0, counts = 0, bmax = 0, act_floats = 0;
-    int32_t n_levels_total = 0, tiles_max = 1;
+    int64_t n_rays = 0, n_params = 0, n_mlp_total = 0, n_items = 0;
+    int64_t y_floats = 0, partial_floats = 0, act_floats = 0;
+    int64_t records = 0, pass_items = 0, pass_segs = 0, pass_parts = 0;  // largest of any scatter pass
+    int32_t pass_levels = 0, tiles_max = 1;
     bool any_f16_table = false, all_f16_table = true;
     // workspace offsets (bytes)
     size_t o_dev, o_sc, o_sc_pass, o_red, o_fwd, o_bwd;
-    size_t y, sc_out, dout, dy, ray_state, ray_loss, partial, act, cnt, offs, block_max, level_max, tile_exp, tile_total,
-        tile_start, chunk_start, work_counter, recs, total;
+    size_t y, sc_out, dout, dy, ray_state, ray_loss, partial, act, seg, block_max, level_exp, parts, recs, total;
     uint64_t fingerprint = 0;
 };
 
@@ -131,8 +131,7 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
     h = fnv(h, &n, sizeof n);
     h = fnv(h, &S, sizeof S);
 
-    int64_t ray = 0, param = 0, yoff = 0, tile = 0, item = 0, cnt = 0, bmax = 0, mlp = 0;
-    int32_t lev = 0;
+    int64_t ray = 0, param = 0, yoff = 0, tile = 0, item = 0, mlp = 0;
     for (int i = 0; i < n; ++i) {
         const prenom_object& o = b->objects[i];
         const prenom_arch* a = &o.arch;
@@ -158,13 +157,9 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
 
         ScatterObj& so = p.sc[i];
         so = scatter_obj(d.grid, n_s);
-        so.lev_off = lev;
         so.s_begin = ray * S;
         so.dy_off = yoff / 2;
         so.g_off = param;
-        so.tile_off = tile;
-        so.count_off = cnt;
-        so.bmax_off = bmax;
         so.item_off = item;
         p.tiles_max = scatter_tiles_max(so) > p.tiles_max ? scatter_tiles_max(so) : p.tiles_max;
 
@@ -178,20 +173,13 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
         yoff += (int64_t)a->n_levels * n_s * 2;
         tile += so.n_tiles;
         item += scatter_items(so);
-        cnt += (int64_t)so.n_tiles * so.n_blocks;
-        bmax += (int64_t)a->n_levels * so.n_blocks;
-        lev += a->n_levels;
         mlp += r.n_mlp;
     }
     if ((double)ray * S > 536870912.0) return fail(PRENOM_ERR_SHAPE, "batch rays * n_samples > 2^29");
     p.n_rays = ray;
     p.n_params = param;
     p.y_floats = yoff;
-    p.n_tiles = tile;
     p.n_items = item;
-    p.counts = cnt;
-    p.bmax = bmax;
-    p.n_levels_total = lev;
     p.n_mlp_total = mlp;
     if (item >= ((int64_t)1 << 31) || tile >= ((int64_t)1 << 31))
         return fail(PRENOM_ERR_SHAPE, "batch grid too large");
@@ -200,23 +188,36 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
     const int64_t budget = (b->record_budget > 0 ? b->record_budget : PRENOM_RECORD_BUDGET) / (int64_t)sizeof(uint64_t);
     h = fnv(h, &budget, sizeof budget);
     p.sc_pass = p.sc;
-    p.records = 0;
     for (int i = 0; i < n;) {
         ScatterGroup g{};
         g.first = i;
         do {
-            ScatterObj& lo = p.sc_pass[i];
-            lo.item_off = g.n_items;
-            lo.tile_off = g.n_tiles;
-            lo.lev_off = g.n_levels;
-            g.n_items += scatter_items(p.sc[i]);
-            g.n_tiles += p.sc[i].n_tiles;
-            g.n_levels += p.sc[i].grid.n_levels;
             g.records += scatter_records(p.sc[i]);
             ++i;
         } while (i < n && g.records + scatter_records(p.sc[i]) <= budget);
         g.count = i - g.first;
+        const int64_t target = scatter_target(g.records);
+        for (int k = g.first; k < i; ++k) {
+            ScatterObj& lo = p.sc_pass[k];
+            scatter_split(lo, target);
+            lo.item_off = g.n_items;
+            lo.lev_off = g.n_levels;
+            lo.seg_off = g.n_segs;
+            lo.ritem_off = g.n_ritems;
+            lo.part_off = g.n_parts;
+            lo.ctile_off = g.n_ctiles;
+            g.n_items += scatter_items(lo);
+            g.n_levels += lo.grid.n_levels;
+            g.n_segs += scatter_segs(lo);
+            g.n_ritems += lo.n_ritems;
+            g.n_parts += lo.n_parts;
+            g.n_ctiles += lo.n_ctiles;
+        }
         p.records = g.records > p.records ? g.records : p.records;
+        p.pass_items = g.n_items > p.pass_items ? g.n_items : p.pass_items;
+        p.pass_segs = g.n_segs > p.pass_segs ? g.n_segs : p.pass_segs;
+        p.pass_parts = g.n_parts > p.pass_parts ? g.n_parts : p.pass_parts;
+        p.pass_levels = g.n_levels > p.pass_levels ? g.n_levels : p.pass_levels;
         p.sgroups.push_back(g);
     }
 
@@ -251,8 +252,6 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
             w.s_off = p.dev[i].ray_begin * S;
             w.n_s = n_s;
             w.a_off = act;
-            w.bmax_off = p.sc[i].bmax_off;
-            w.n_sblocks = p.sc[i].n_blocks;
             act += mlp_act_floats(m, n_s);
             for (int64_t t0 = 0; t0 < n_t; t0 += g.fwd_tiles) {
                 w.tile_begin = t0;
@@ -303,15 +302,10 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
     p.ray_loss = take(sizeof(double) * (size_t)p.n_rays);
     p.partial = take(sizeof(float) * (size_t)p.partial_floats);
     p.act = take(sizeof(float) * (size_t)p.act_floats);
-    p.cnt = take(sizeof(uint32_t) * (size_t)p.counts);
-    p.offs = take(sizeof(uint32_t) * (size_t)p.counts);
-    p.block_max = take(sizeof(float) * (size_t)p.bmax);
-    p.level_max = take(sizeof(float) * (size_t)p.n_levels_total);
-    p.tile_exp = take(sizeof(int32_t) * (size_t)p.n_tiles);
-    p.tile_total = take(sizeof(uint64_t) * (size_t)p.n_tiles);
-    p.tile_start = take(sizeof(uint64_t) * (size_t)(p.n_tiles + 1));
-    p.chunk_start = take(sizeof(uint64_t) * (size_t)(p.n_tiles + 2));
-    p.work_counter = take(sizeof(uint64_t));
+    p.seg = take(sizeof(uint16_t) * (size_t)p.pass_segs);
+    p.block_max = take(sizeof(float) * (size_t)p.pass_items);
+    p.level_exp = take(sizeof(int32_t) * (size_t)p.pass_levels);
+    p.parts = take(scatter_part_bytes() * (size_t)p.pass_parts);
     p.recs = take(sizeof(uint64_t) * (size_t)p.records);
     p.total = off;
     return PRENOM_OK;
@@ -343,8 +337,8 @@ prenom_status check_params(const prenom_batch* b, const Plan& p, bool need_grads
     return PRENOM_OK;
 }
 
-// Scatter of group g's objects; the per-tile and per-level arrays are reused
-// from their start by every pass.
+// Scatter of group g's objects; every pass uses the scatter's arrays from their
+// start.
 ScatterArgs scatter_args(const Plan& p, const ScatterGroup& g, void* ws, const float* ray_obj, const float* t,
                          float* grads, int32_t* nonfinite)
 {
@@ -353,29 +347,21 @@ ScatterArgs scatter_args(const Plan& p, const ScatterGroup& g, void* ws, const f
     sa.n_obj = g.count;
     sa.objs = at<ScatterObj>(ws, p.o_sc_pass) + g.first;
     sa.tiles_max = p.tiles_max;
-    sa.reduce_blocks = device_cus();
-    sa.n_tiles = g.n_tiles;
     sa.n_items = g.n_items;
+    sa.n_ritems = g.n_ritems;
+    sa.n_ctiles = g.n_ctiles;
     sa.n_levels_total = g.n_levels;
     sa.ray_obj = ray_obj;
     sa.t = t;
     sa.dy = at<const float2>(ws, p.dy);
     sa.g_table = grads;
-    sa.counts = at<uint32_t>(ws, p.cnt);
-    sa.offsets = at<uint32_t>(ws, p.offs);
     sa.block_max = at<float>(ws, p.block_max);
-    sa.level_max = at<float>(ws, p.level_max);
-    sa.tile_exp = at<int32_t>(ws, p.tile_exp);
-    sa.tile_total = at<uint64_t>(ws, p.tile_total);
-    sa.tile_start = at<uint64_t>(ws, p.tile_start);
-    sa.chunk_start = at<uint64_t>(ws, p.chunk_start);
-    sa.work_counter = at<unsigned long long>(ws, p.work_counter);
+    sa.level_exp = at<int32_t>(ws, p.level_exp);
+    sa.seg = at<uint16_t>(ws, p.seg);
+    sa.parts = at<unsigned long long>(ws, p.parts);
     sa.recs = at<uint64_t>(ws, p.recs);
     sa.n_records = p.records;
     sa.nonfinite = nonfinite;
-    sa.fwd_counts = 1;  // fwd_features (render_fwd, or the recompute in render_bwd) wrote the histograms
-    sa.merge_runs = 1;
-    sa.chunk_min_bits = 18;  // a pass of a few objects needs smaller items to fill the CUs
     sa.compact = p.all_f16_table;
     return sa;
 }
@@ -386,11 +372,9 @@ prenom_status fwd_features(const prenom_batch* b, const Plan& p, const float* ra
 {
     const ObjDev* dev = at<const ObjDev>(ws, p.o_dev);
     float* y = at<float>(ws, p.y);
-    // the encoding also writes the tile histograms the backward's scatter starts from
     PRENOM_LAUNCH("k_encode_fwd", s,
-                  launch_encode_batch_hist(dev, at<const ScatterObj>(ws, p.o_sc), p.n_obj, p.n_items, b->params,
-                                           p.any_f16_table ? b->params_lp : nullptr, ray_obj, t, p.S, y,
-                                           at<uint32_t>(ws, p.cnt), s));
+                  launch_encode_batch(dev, at<const ScatterObj>(ws, p.o_sc), p.n_obj, p.n_items, b->params,
+                                      p.any_f16_table ? b->params_lp : nullptr, ray_obj, t, p.S, y, s));
     for (const Group& g : p.groups) {
         const MlpWork* work = at<const MlpWork>(ws, p.o_fwd) + g.fwd_first;
         float* sc = at<float>(ws, p.sc_out);
@@ -591,10 +575,6 @@ prenom_status prenom_batch_render_bwd(const prenom_batch* batch, const prenom_re
     c.dout = at<float>(workspace, p.dout);
     PRENOM_LAUNCH("k_composite_bwd", s, launch_composite_bwd(c, s));
     float* partial = at<float>(workspace, p.partial);
-    // the MLP backward also writes the maxima of |dy| per (object, level,
-    // scatter block) and flags a non-finite dy, so the scatter starts at its
-    // level maxima (phase 1)
-    float* block_max = at<float>(workspace, p.block_max);
     int32_t* nonfinite = batch->loss_scale ? batch->scaler_state : nullptr;
     for (const Group& g : p.groups) {
         const MlpWork* work = at<const MlpWork>(workspace, p.o_bwd) + g.bwd_first;
@@ -604,18 +584,16 @@ prenom_status prenom_batch_render_bwd(const prenom_batch* batch, const prenom_re
         PRENOM_LAUNCH("k_mlp_bwd", s,
                       g.shape.dtype == PRENOM_F32
                           ? launch_mlp_bwd_batch(g.shape, work, (int)g.n_bwd, batch->params, y, c.dout, c.sc, dy,
-                                                 partial + g.partial_off, n_mlp, at<float>(workspace, p.act),
-                                                 block_max, nonfinite, s)
+                                                 partial + g.partial_off, n_mlp, at<float>(workspace, p.act), s)
                           : launch_mlp_bwd_lp_batch(g.shape, work, (int)g.n_bwd, batch->params, y, c.dout, c.sc, dy,
-                                                    partial + g.partial_off, n_mlp, at<float>(workspace, p.act),
-                                                    block_max, nonfinite, s));
+                                                    partial + g.partial_off, n_mlp, at<float>(workspace, p.act), s));
     }
     PRENOM_LAUNCH("k_reduce_partials", s,
                   launch_reduce_partials_batch(at<const MlpRed>(workspace, p.o_red), p.n_obj, p.n_mlp_total, partial,
                                                batch->grads, s));
     for (const ScatterGroup& g : p.sgroups) {
         const ScatterArgs sa = scatter_args(p, g, workspace, ray_obj, t, batch->grads, nonfinite);
-        for (int ph = 1; ph < kScatterPhases; ++ph)
+        for (int ph = 0; ph < kScatterPhases; ++ph)
             PRENOM_LAUNCH(kScatterPhaseNames[ph], s, launch_scatter_phase(sa, ph, s));
     }
     return PRENOM_OK;

@@ -35,7 +35,6 @@ hipError_t timed(const char* name, hipStream_t s, F&& launch)
 
 inline bool aligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
-int device_cus();  // compute units of the current device
 prenom_status check_arch(const prenom_arch* a);
 prenom_status check_supported(const prenom_arch* a);
 MlpShape mlp_shape(const prenom_arch* a);

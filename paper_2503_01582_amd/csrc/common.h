@@ -95,8 +95,7 @@ __device__ __forceinline__ void level_corners(const GridInfo& g, int l, float x0
 
 // ------------------------------------------------------------------ table tiles
 // The hash-table gradient buckets contributions by table tile (2^13 rows),
-// per (level, block of kScatterBlockSamples samples).  The training forward
-// writes the same per-block tile histograms as it encodes (TileHist).
+// per (level, block of kScatterBlockSamples samples).
 constexpr int kTileBits = 13;
 constexpr int kTileRows = 1 << kTileBits;
 constexpr int kMaxTilesPerLevel = 1 << (24 - kTileBits);  // T <= 2^24
@@ -160,64 +159,18 @@ __device__ __forceinline__ float dpp_f32(float v)
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xf, 0xf, true));
 }
 
-// Tile histogram of the wave's records on a level of at most 16 tiles, for
-// counting only (no ranks): bit e of `heads` marks corner e as a record.  Each
-// lane counts its records per tile in the 4-bit fields of a 64-bit word (at
-// most 8 per tile), the fields are widened to bytes and summed over each row
-// of 16 lanes by four DPP additions (mirror, half mirror, two quad swaps:
-// every lane ends with the row's sums, at most 128 per tile), and lane i of
-// each row adds the row's count of tile i.  About 90 instructions per wave,
-// against about 35 per corner for wave_aggregated_add.  Every lane of the wave
-// must call it (lanes without records pass heads = 0).
-__device__ __forceinline__ void wave_count_tiles16(uint32_t* hist, const uint32_t row[8], uint32_t heads, int nt)
-{
-    uint64_t p = 0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const uint32_t t = row[e] >> kTileBits;  // < 16 for every row of the level
-        p += (uint64_t)((heads >> e) & 1u) << ((4u * t) & 63u);
-    }
-    const uint32_t lo = (uint32_t)p, hi = (uint32_t)(p >> 32);
-    // v[k]: tile b sits in byte (b >> 1) & 3 of v[(b & 1) * 2 + (b >> 3)]
-    uint32_t v[4] = {lo & 0x0f0f0f0fu, hi & 0x0f0f0f0fu, (lo >> 4) & 0x0f0f0f0fu, (hi >> 4) & 0x0f0f0f0fu};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        v[k] += dpp_u32<0x140>(v[k]);  // row_mirror: lane i + lane 15 - i
-        v[k] += dpp_u32<0x141>(v[k]);  // row_half_mirror
-        v[k] += dpp_u32<0x1b>(v[k]);   // quad_perm [3, 2, 1, 0]
-        v[k] += dpp_u32<0xb1>(v[k]);   // quad_perm [1, 0, 3, 2]
-    }
-    const uint32_t b = threadIdx.x & 15u;
-    const uint32_t k = (b & 1u) * 2u + (b >> 3);
-    const uint32_t w = k == 0 ? v[0] : k == 1 ? v[1] : k == 2 ? v[2] : v[3];
-    const uint32_t cnt = (w >> (8u * ((b >> 1) & 3u))) & 0xffu;
-    if ((int)b < nt && cnt != 0u) atomicAdd(&hist[b], cnt);
-}
-
-// Adds the lane's records (bit e of heads: corner e) to a block's LDS tile
-// histogram of a level of nt tiles.  Every lane of the wave must call it.
-__device__ __forceinline__ void count_records(uint32_t* hist, const Corners& c, uint32_t heads, int nt)
-{
-    if (nt <= 16) {
-        wave_count_tiles16(hist, c.row, heads, nt);
-        return;
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        if ((heads >> e) & 1u) atomicAdd(&hist[c.row[e] >> kTileBits], 1u);
-}
-
 // Merging repeated corners.  Consecutive samples of a ray often share a cell
 // on the coarser levels, so the same corner row repeats on neighbouring
 // lanes; such a run becomes one record (the sum of its contributions).  Runs
 // stay inside groups of 8 lanes.  Bit e of the result is set when the lane's
-// corner e starts a run: the lane holds a sample and is the first of its
-// group of 8, or lane - 1's corner e has another row.  Lanes with samples
-// must form a prefix of the wave (then lane - 1 holds one whenever the lane
-// does).  Every lane of the wave must call it.
+// corner e starts a run: the lane has a contribution and is the first of its
+// group of 8, or lane - 1 has none, or lane - 1's corner e has another row.
+// Every lane of the wave must call it.
 __device__ __forceinline__ uint32_t run_heads(const Corners& c, bool has)
 {
-    const bool first = (threadIdx.x & 7) == 0;
+    const uint64_t B = __ballot(has);
+    const int lane = threadIdx.x & 63;
+    const bool first = (lane & 7) == 0 || ((B << 1 >> lane) & 1ull) == 0;
     uint32_t m = 0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -230,7 +183,7 @@ __device__ __forceinline__ uint32_t run_heads(const Corners& c, bool has)
 // Per lane that starts a run (boundary set): the sum of v over its run (the
 // lane and the following lanes of its group of 8 up to the next boundary); a
 // segmented suffix scan in three steps, in a fixed order.  Lanes without a
-// sample pass v = 0 and boundary = true.  Every lane of the wave must call it.
+// contribution pass v = 0 and boundary = true.  Every lane of the wave must call it.
 __device__ __forceinline__ float2 run_sum(float2 v, bool boundary)
 {
     const int g = threadIdx.x & 7;
@@ -250,17 +203,6 @@ __device__ __forceinline__ float2 run_sum(float2 v, bool boundary)
     if (c4) { v.x += ox; v.y += oy; }
     return v;
 }
-
-// Tile histograms of one object: counts[(tile_base[l] + i) * n_blocks + b]
-// = records (runs of repeated corners, run_heads) of sample block b of level
-// l in tile i of that level.
-struct TileHist {
-    uint32_t* counts;
-    int32_t n_blocks;
-    int32_t pad_;
-    int32_t tiles[PRENOM_MAX_LEVELS];
-    int32_t tile_base[PRENOM_MAX_LEVELS];
-};
 
 // ------------------------------------------------------------------ batches
 // Device descriptor of one object of a batch (offsets index the batch's
@@ -325,21 +267,18 @@ hipError_t launch_encode_points(const GridInfo& g, const float* table, const flo
                                 float* features, int32_t* corner_idx, hipStream_t s);
 
 struct ScatterObj;
-// Encoding of the rendered samples of every object of a batch, which also
-// writes the tile histograms of its hash-table gradient: one block per
-// scatter item (object, level, sample block) of sobjs, counts laid out as the
-// scatter reads them; FP16 tables come from params_f16.
-hipError_t launch_encode_batch_hist(const ObjDev* objs, const ScatterObj* sobjs, int n_obj, int64_t n_items,
-                                    const float* params, const void* params_f16, const float* ray_obj, const float* t,
-                                    int32_t S, float* y, uint32_t* counts, hipStream_t s);
+// Encoding of the rendered samples of every object of a batch: one block per
+// scatter item (object, level, sample block) of sobjs; FP16 tables come from
+// params_f16.
+hipError_t launch_encode_batch(const ObjDev* objs, const ScatterObj* sobjs, int n_obj, int64_t n_items,
+                               const float* params, const void* params_f16, const float* ray_obj, const float* t,
+                               int32_t S, float* y, hipStream_t s);
 
 // Encoding of the rendered samples (positions from rays and t); reads the
 // FP16 table copy when table_f16 is not null, the FP32 tables otherwise.
-// hist (or null): also write the tile histograms of every (level, block of
-// kScatterBlockSamples samples), counting every sample, for the backward.
 hipError_t launch_encode_samples(const GridInfo& g, const float* table, const void* table_f16,
                                  const float* ray_obj, const float* t, int64_t n_rays, int32_t S, float* y,
-                                 hipStream_t s, const TileHist* hist = nullptr);
+                                 hipStream_t s);
 
 // Bucketed scatter-add of the feature gradients into the table gradient.
 // Geometry of one object's scatter: its table tiles and sample blocks, and
@@ -348,77 +287,67 @@ struct ScatterObj {
     GridInfo grid;
     int32_t n_blocks;  // sample blocks per level
     int32_t n_tiles;   // table tiles over the object's levels
-    int32_t lev_off;   // first (object, level) entry of level_max
-    int32_t pad_;
+    int32_t lev_off;   // first (object, level) entry of level_exp
+    int32_t n_ritems;  // reduce items
+    int32_t n_ctiles;  // tiles reduced in several ranges of blocks
+    int32_t n_parts;   // 64-bit partial sums of those (one per range)
     int32_t tiles[PRENOM_MAX_LEVELS];
     int32_t tile_base[PRENOM_MAX_LEVELS];
+    int32_t split[PRENOM_MAX_LEVELS];       // ranges of blocks each of the level's tiles is reduced in
+    int32_t ritem_base[PRENOM_MAX_LEVELS];  // the level's first reduce item (tile-major, then range)
+    int32_t part_base[PRENOM_MAX_LEVELS];   // its first partial sum, and
+    int32_t ctile_base[PRENOM_MAX_LEVELS];  // its first split tile (where split > 1)
     int64_t level_rows[PRENOM_MAX_LEVELS];
     int64_t n_s;        // samples
     int64_t s_begin;    // first sample in the per-sample arrays (t; ray = sample / S)
     int64_t dy_off;     // float2 index of the object's dy [L][n_s]
     int64_t g_off;      // float index of the object's table gradient
-    int64_t tile_off;   // first tile in the per-tile arrays
-    int64_t count_off;  // first entry of its counts [n_tiles][n_blocks]
-    int64_t bmax_off;   // first entry of its block_max [L][n_blocks]
-    int64_t item_off;   // first (level, sample block) item of the count and place grids
+    int64_t item_off;   // first (level, sample block) item
+    int64_t seg_off;    // first entry of its segment starts
+    int64_t ritem_off;  // first reduce item
+    int64_t part_off;   // first partial sum
+    int64_t ctile_off;  // first split tile
 };
 // Fills the geometry of one object (offsets within the batch are left 0).
 ScatterObj scatter_obj(const GridInfo& g, int64_t n_s);
 int64_t scatter_items(const ScatterObj& o);      // L * n_blocks
-int64_t scatter_records(const ScatterObj& o);    // n_s * L * 8
-int scatter_max_tiles_per_level();
+int64_t scatter_records(const ScatterObj& o);    // record capacity: 4096 per item
+int64_t scatter_segs(const ScatterObj& o);       // segment starts
 int scatter_tiles_max(const ScatterObj& o);      // max tiles of one level
+// Records a reduce item of a pass over `records` of capacity should take, and
+// the object's split of its tiles into such items.
+int64_t scatter_target(int64_t records);
+void scatter_split(ScatterObj& o, int64_t target);
+size_t scatter_part_bytes();                     // one partial sum
 
 struct ScatterArgs {
     int32_t S;
     int32_t n_obj;              // 1: `one` holds the object; else `objs` (device) holds n_obj of them
     int32_t tiles_max;          // max tiles of one level over all objects
-    int32_t reduce_blocks;
-    int64_t n_tiles;            // over all objects
-    int64_t n_items;            // (object, level, sample block) items of count and place
     int32_t n_levels_total;     // (object, level) pairs
-    int32_t pad_;
+    int64_t n_items;            // (object, level, sample block) items
+    int64_t n_ritems;           // reduce items
+    int64_t n_ctiles;           // tiles reduced in several ranges
     ScatterObj one;
     const ScatterObj* objs;
     const float* ray_obj;
     const float* t;
     const float2* dy;
     float* g_table;
-    uint32_t* counts;       // per object [n_tiles][n_blocks], read only after the first phase
-    uint32_t* offsets;      // same layout: per block, its first record within the tile
-    float* block_max;       // per object [L][n_blocks] max |dy| per sample block
-    float* level_max;       // [n_levels_total]
-    int32_t* tile_exp;      // [n_tiles] fixed-point exponent
-    uint64_t* tile_total;   // [n_tiles]
-    uint64_t* tile_start;   // [n_tiles + 1]
-    uint64_t* chunk_start;  // [n_tiles + 2]: chunk bases, their total, the chunk size's log2
-    unsigned long long* work_counter;
-    uint64_t* recs;         // [records] packed records (scatter.hip: row, shared exponent, two mantissas); 8 bytes each
-    int64_t n_records;      // length of recs
-    int32_t* nonfinite;     // set to 1 when a dy entry is not finite (loss scaling), or null
-    // 1: counts were written by the training forward (TileHist); the first
-    // phase then only takes the per-block max |dy|, and the scan checks the
-    // histograms hold at most n_records (else place and reduce do nothing).
-    // 0: the first phase counts.
-    int32_t fwd_counts;
-    // 1: every sample counted, a corner repeating the previous lane's row
-    // joining its record (run_heads; the rule the forward's histograms
-    // follow).  0: one record per corner of every sample whose dy is not zero.
-    int32_t merge_runs;
-    // log2 of the smallest reduce work item in records (18..21; the scan picks
-    // a size from the pass's records).  A tile longer than one item is summed
-    // by several workgroups whose FP32 partials meet in atomics, in an order
-    // that can change the last bits; 21 keeps most tiles to one item.
-    int32_t chunk_min_bits;
+    float* block_max;           // [n_items] max |dy| of the item
+    int32_t* level_exp;         // [n_levels_total] fixed-point exponent
+    uint16_t* seg;              // per item [tiles + 1]: start of each tile's segment, and the end
+    unsigned long long* parts;  // partial sums: 64-bit fixed point, [2][tile rows] each
+    uint64_t* recs;             // packed records (scatter.hip), 4096 per item
+    int64_t n_records;          // length of recs
+    int32_t* nonfinite;         // set to 1 when a dy entry is not finite (loss scaling), or null
     // 1: compact records (15-bit mantissas, 48 bits: 32-bit words at recs,
     // then n_records 16-bit words), for FP16 tables; 0: 64-bit records.
     int32_t compact;
 };
-// The scatter runs as kScatterPhases dependent kernels, launched in order
-// (phase 0 .. kScatterPhases - 1): count (or, with fwd_counts, the block
-// maxima of |dy| alone), per-level max, scan over blocks, scan over tiles,
-// place, reduce.
-constexpr int kScatterPhases = 6;
+// The scatter runs as kScatterPhases dependent kernels, launched in order:
+// place, level scales, reduce, combine (none where no tile is split).
+constexpr int kScatterPhases = 4;
 extern const char* const kScatterPhaseNames[kScatterPhases];
 hipError_t launch_scatter_phase(const ScatterArgs& a, int phase, hipStream_t s);
 
@@ -438,8 +367,6 @@ struct MlpWork {
     int64_t w_off, y_off, s_off, n_s;
     int64_t tile_begin, tile_end;
     int64_t a_off;
-    int64_t bmax_off;   // the object's [L][n_blocks] maxima of |dy| (scatter blocks), written by the backward
-    int64_t n_sblocks;  // its scatter blocks (kScatterBlockSamples samples each)
 };
 
 // The 128-wide MLP stores its hidden activations in the forward and runs its
@@ -470,20 +397,14 @@ hipError_t launch_mlp_bwd_lp(const MlpShape& m, const float* w, const float* y, 
                              int64_t n_s, float* dy, float* partial, float* act, hipStream_t s);
 hipError_t launch_mlp_fwd_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
                                 const float* y, float* sc, float* act, hipStream_t s);
-// Batched backward: besides dy and the partial weight gradients, every work
-// item writes its maxima of |dy| into block_max (MlpWork::bmax_off) and sets
-// *nonfinite (when not null) on a non-finite dy; work items start at a
-// multiple of kScatterBlockSamples / 16 tiles and span at most 1024 tiles.
 hipError_t launch_mlp_bwd_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
                                 const float* y, const float* dout, const float* sc, float* dy, float* partial,
-                                int64_t slot_stride, float* act, float* block_max, int32_t* nonfinite,
-                                hipStream_t s);
+                                int64_t slot_stride, float* act, hipStream_t s);
 hipError_t launch_mlp_fwd_lp_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
                                    const float* y, float* sc, float* act, hipStream_t s);
 hipError_t launch_mlp_bwd_lp_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
                                    const float* y, const float* dout, const float* sc, float* dy, float* partial,
-                                   int64_t slot_stride, float* act, float* block_max, int32_t* nonfinite,
-                                   hipStream_t s);
+                                   int64_t slot_stride, float* act, hipStream_t s);
 hipError_t launch_reduce_partials(const float* partial, int n_slots, int64_t n_mlp, float* g_mlp,
                                   hipStream_t s);
 

@@ -146,8 +146,7 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_samples(GridInfo g, const 
     const int64_t s = (int64_t)blockIdx.x * kEncBlock + threadIdx.x;
     const int l = blockIdx.y;
     if (s >= n_s) return;
-    const int64_t ray = s / S;
-    const float* ro = ray_obj + 6 * ray;
+    const float* ro = ray_obj + 6 * (int64_t)((uint32_t)s / (uint32_t)S);  // (n_s <= 2^29)
     const float ts = t[s];
     Corners c;
     level_corners(g, l, sample_coord(ts, ro[3], ro[0]), sample_coord(ts, ro[4], ro[1]),
@@ -156,57 +155,17 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_samples(GridInfo g, const 
     y[(int64_t)l * n_s + s] = gather_blend(lt, g, l, c);
 }
 
-// The same, one block per (level, block of kScatterBlockSamples samples), also
-// counting the records of the hash-table gradient in an LDS histogram over
-// the level's table tiles: one per corner of every sample, except that a
-// corner repeating the previous lane's row joins that lane's record
-// (run_heads); place applies the same rule to the same corners.
-template <typename Row>
-__global__ __launch_bounds__(kScatterBlockSamples) void k_encode_samples_hist(GridInfo g, const Row* __restrict__ table,
-                                                                          const float* __restrict__ ray_obj,
-                                                                          const float* __restrict__ t, int64_t n_s,
-                                                                          int32_t S, float2* __restrict__ y,
-                                                                          TileHist h)
+// Batched: one block per item (object, level, block of kScatterBlockSamples
+// samples) of the batch's hash-table gradient (sobjs[i] and objs[i] describe
+// object i).
+__global__ __launch_bounds__(kScatterBlockSamples) void k_encode_batch(const ObjDev* __restrict__ objs,
+                                                                   const ScatterObj* __restrict__ sobjs, int n_obj,
+                                                                   const float* __restrict__ params,
+                                                                   const half2_t* __restrict__ params_f16,
+                                                                   const float* __restrict__ ray_obj,
+                                                                   const float* __restrict__ t, int32_t S,
+                                                                   float2* __restrict__ y)
 {
-    __shared__ uint32_t hist[kMaxTilesPerLevel];
-    const int l = blockIdx.y;
-    const int bx = blockIdx.x;
-    const int nt = h.tiles[l];
-    for (int i = threadIdx.x; i < nt; i += kScatterBlockSamples) hist[i] = 0;
-    __syncthreads();
-    const int64_t s = (int64_t)bx * kScatterBlockSamples + threadIdx.x;
-    const bool has = s < n_s;  // a prefix of every wave
-    const int64_t sc = has ? s : n_s - 1;
-    const float* ro = ray_obj + 6 * (sc / S);
-    const float ts = t[sc];
-    Corners c;
-    level_corners(g, l, sample_coord(ts, ro[3], ro[0]), sample_coord(ts, ro[4], ro[1]),
-                  sample_coord(ts, ro[5], ro[2]), c);
-    const uint32_t heads = run_heads(c, has);  // one record per run of a repeated corner
-    if (has) {
-        const Row* lt = table + ((int64_t)l << g.log2_table);
-        y[(int64_t)l * n_s + s] = gather_blend(lt, g, l, c);
-    }
-    count_records(hist, c, heads, nt);
-    __syncthreads();
-    uint32_t* out = h.counts + (int64_t)h.tile_base[l] * h.n_blocks + bx;
-    for (int i = threadIdx.x; i < nt; i += kScatterBlockSamples) out[(int64_t)i * h.n_blocks] = hist[i];
-}
-
-// Batched, with the tile histograms: one block per item (object, level,
-// block of kScatterBlockSamples samples) of the batch's hash-table gradient,
-// numbered as its scatter numbers them (sobjs[i] and objs[i] describe object
-// i); the same run rule as k_encode_samples_hist.
-__global__ __launch_bounds__(kScatterBlockSamples) void k_encode_batch_hist(const ObjDev* __restrict__ objs,
-                                                                        const ScatterObj* __restrict__ sobjs,
-                                                                        int n_obj, const float* __restrict__ params,
-                                                                        const half2_t* __restrict__ params_f16,
-                                                                        const float* __restrict__ ray_obj,
-                                                                        const float* __restrict__ t, int32_t S,
-                                                                        float2* __restrict__ y,
-                                                                        uint32_t* __restrict__ counts)
-{
-    __shared__ uint32_t hist[kMaxTilesPerLevel];
     const int64_t item = blockIdx.x;
     int lo = 0, hi = n_obj - 1;
     while (lo < hi) {
@@ -221,32 +180,22 @@ __global__ __launch_bounds__(kScatterBlockSamples) void k_encode_batch_hist(cons
     const uint32_t rem = (uint32_t)(item - so.item_off);
     const int l = (int)(rem / (uint32_t)so.n_blocks);
     const int bx = (int)(rem - (uint32_t)l * (uint32_t)so.n_blocks);
-    const int nt = so.tiles[l];
-    for (int i = threadIdx.x; i < nt; i += kScatterBlockSamples) hist[i] = 0;
-    __syncthreads();
     const int64_t n_s = so.n_s;
     const int64_t s = (int64_t)bx * kScatterBlockSamples + threadIdx.x;
-    const bool has = s < n_s;  // a prefix of every wave
-    const int64_t gs = so.s_begin + (has ? s : n_s - 1);
-    const float* ro = ray_obj + 6 * (gs / S);
+    if (s >= n_s) return;
+    const int64_t gs = so.s_begin + s;
+    const float* ro = ray_obj + 6 * (int64_t)((uint32_t)gs / (uint32_t)S);
     const float ts = t[gs];
     Corners c;
     level_corners(o.grid, l, sample_coord(ts, ro[3], ro[0]), sample_coord(ts, ro[4], ro[1]),
                   sample_coord(ts, ro[5], ro[2]), c);
-    const uint32_t heads = run_heads(c, has);
-    if (has) {
-        const int64_t row0 = (int64_t)l << o.grid.log2_table;  // rows of float2 / half2
-        float2 v;
-        if (o.table_dtype == PRENOM_F16)
-            v = gather_blend_rows(params_f16 + o.param_off / 2 + row0, c);
-        else
-            v = gather_blend_rows(reinterpret_cast<const float2*>(params + o.param_off) + row0, c);
-        y[o.y_off / 2 + (int64_t)l * n_s + s] = v;
-    }
-    count_records(hist, c, heads, nt);
-    __syncthreads();
-    uint32_t* out = counts + so.count_off + (int64_t)so.tile_base[l] * so.n_blocks + bx;
-    for (int i = threadIdx.x; i < nt; i += kScatterBlockSamples) out[(int64_t)i * so.n_blocks] = hist[i];
+    const int64_t row0 = (int64_t)l << o.grid.log2_table;  // rows of float2 / half2
+    float2 v;
+    if (o.table_dtype == PRENOM_F16)
+        v = gather_blend_rows(params_f16 + o.param_off / 2 + row0, c);
+    else
+        v = gather_blend_rows(reinterpret_cast<const float2*>(params + o.param_off) + row0, c);
+    y[o.y_off / 2 + (int64_t)l * n_s + s] = v;
 }
 
 __global__ __launch_bounds__(kEncBlock) void k_encode_points(GridInfo g, const float2* __restrict__ table,
@@ -302,20 +251,10 @@ dim3 enc_grid(int64_t n, int L) { return dim3((uint32_t)((n + kEncBlock - 1) / k
 
 hipError_t launch_encode_samples(const GridInfo& g, const float* table, const void* table_f16,
                                  const float* ray_obj, const float* t, int64_t n_rays, int32_t S, float* y,
-                                 hipStream_t s, const TileHist* hist)
+                                 hipStream_t s)
 {
     const int64_t n_s = n_rays * S;
     if (n_s == 0) return hipSuccess;
-    if (hist) {
-        const dim3 grid((uint32_t)((n_s + kScatterBlockSamples - 1) / kScatterBlockSamples), (uint32_t)g.n_levels);
-        if (table_f16)
-            hipLaunchKernelGGL(k_encode_samples_hist<half2_t>, grid, dim3(kScatterBlockSamples), 0, s, g,
-                               (const half2_t*)table_f16, ray_obj, t, n_s, S, (float2*)y, *hist);
-        else
-            hipLaunchKernelGGL(k_encode_samples_hist<float2>, grid, dim3(kScatterBlockSamples), 0, s, g,
-                               (const float2*)table, ray_obj, t, n_s, S, (float2*)y, *hist);
-        return hipGetLastError();
-    }
     if (table_f16)
         hipLaunchKernelGGL(k_encode_samples<half2_t>, enc_grid(n_s, g.n_levels), dim3(kEncBlock), 0, s, g,
                            (const half2_t*)table_f16, ray_obj, t, n_s, S, (float2*)y);
@@ -345,16 +284,15 @@ hipError_t launch_density_grid(const float* sc, int64_t n, float* out, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_encode_batch_hist(const ObjDev* objs, const ScatterObj* sobjs, int n_obj, int64_t n_items,
-                                    const float* params, const void* params_f16, const float* ray_obj, const float* t,
-                                    int32_t S, float* y, uint32_t* counts, hipStream_t s)
+hipError_t launch_encode_batch(const ObjDev* objs, const ScatterObj* sobjs, int n_obj, int64_t n_items,
+                               const float* params, const void* params_f16, const float* ray_obj, const float* t,
+                               int32_t S, float* y, hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_encode_batch_hist, dim3((uint32_t)n_items), dim3(kScatterBlockSamples), 0, s, objs, sobjs,
-                       n_obj, params, (const half2_t*)params_f16, ray_obj, t, S, (float2*)y, counts);
+    hipLaunchKernelGGL(k_encode_batch, dim3((uint32_t)n_items), dim3(kScatterBlockSamples), 0, s, objs, sobjs, n_obj,
+                       params, (const half2_t*)params_f16, ray_obj, t, S, (float2*)y);
     return hipGetLastError();
 }
-
 
 hipError_t launch_encode_points(const GridInfo& g, const float* table, const float* pos, int64_t n,
                                 float* features, int32_t* corner_idx, hipStream_t s)

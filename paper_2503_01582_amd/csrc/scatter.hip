@@ -7,29 +7,28 @@
 // one by one.  Instead the contributions are bucketed by table tile (2^13 rows,
 // whose accumulators fill 128 KB of LDS):
 //
-//   count  : per (sample block, level) an LDS histogram of contributions per
-//            tile -> counts[tile][block], and the block's max |dy|.  In the
-//            single-object training step the forward encoding has written
-//            the histograms already (it computes the same corners), so this
-//            phase only takes the block maxima of |dy| (k_scatter_dymax)
-//   scan   : exclusive prefix over blocks (per tile), then over tiles; the
-//            tile record ranges are cut into chunks of bounded length, and each
-//            tile gets a fixed-point scale 2^e
-//   place  : the block recomputes its contributions, sorts them by tile in LDS
-//            and writes each tile's run contiguously (coalesced) as 8-byte
-//            records (row within the tile, and the contribution's two
-//            features as 22-bit mantissas under one shared exponent)
-//   reduce : a persistent grid takes chunks from a counter; each chunk is
-//            accumulated in LDS and added to the gradient rows -- plain
-//            read-modify-write when the tile has one chunk (the block owns it),
-//            global atomics only for tiles split over several chunks.
+//   place  : one workgroup per item (level, block of 512 samples) computes the
+//            block's contributions, sorts them by tile in LDS and writes them
+//            to the item's own range of the record array, all tiles one after
+//            another, with the start of every tile's segment and the block's
+//            largest |dy|.  Nothing has to be known about the other blocks, so
+//            no counting pass and no scan over blocks precede it, and the
+//            write is one linear copy out of LDS
+//   level  : per (object, level) the largest |dy| and the sum of the block
+//            maxima, which fix the level's fixed-point scale 2^e
+//   reduce : one workgroup per (tile, range of blocks) gathers the tile's
+//            segments of those blocks, 16 lanes per segment, and accumulates
+//            them in LDS; a tile with one range is added to the gradient rows
+//            (the workgroup owns them), the others write their 64-bit sums
+//   combine: the 64-bit sums of a tile's ranges added and applied
 //
 // The LDS accumulation is 64-bit fixed point (integer LDS atomics run several
-// times faster than FP32 ones).  With e chosen so that max|dy| * records * 2^e
-// < 2^62, no sum can overflow; with max|dy| * 2^e < 2^50 as well, each
-// contribution is rounded by at most 2^-(e+1) <= 2^-51 max|dy|, far below FP32
-// resolution of the result.  Integer sums do not depend on order, so a tile
-// with one chunk gets a bit-reproducible gradient.
+// times faster than FP32 ones).  The trilinear weights of a sample sum to 1,
+// so |sum| of a row <= sum over the blocks of 512 max|dy|; with e chosen so
+// that this bound times 2^e < 2^62 no sum can overflow, and with one record's
+// value times 2^e < 2^50 as well, each contribution is rounded by at most
+// 2^-(e+1), far below FP32 resolution of the result.  Integer sums do not
+// depend on order, so the gradient is bit-reproducible.
 //
 // A record keeps 21 significant bits of the larger of its two features (an
 // FP32 value has 24): each feature is within 2^-21 of the larger one's
@@ -37,7 +36,7 @@
 // rounding.
 //
 // Corner rows and weights are computed by the same function as the forward
-// encoding, so count and place agree exactly.
+// encoding.
 //
 // The same kernels serve one object (its geometry passed by value) and a
 // batch of objects with different grids (geometry in a device table): tiles,
@@ -51,23 +50,27 @@ namespace {
 constexpr int kPlaceThreads = kScatterBlockSamples;
 constexpr int kSamplesPerBlock = kPlaceThreads;  // one sample per thread
 constexpr int kRecordsPerBlock = kSamplesPerBlock * 8;
-constexpr int kScanThreads = 1024;
 constexpr int kReduceThreads = 1024;
-constexpr int kRun = 8;            // consecutive records per thread and load
-constexpr int kRunsPerThread = 3;  // runs in flight per thread
-// Records per reduce work item: a power of two between 2^chunk_min_bits and
-// 2^kChunkMaxBits, the smallest that gives at most kChunksPerBlock items per
-// reduce block (few large items leave blocks idle at the end of a pass; each
-// item also zeroes and writes out its whole tile).
-constexpr int kChunkMinBits = 18, kChunkMaxBits = 21;
-constexpr uint64_t kChunksPerBlock = 4;
+constexpr int kSegLanes = 16;                           // lanes that read one segment
+constexpr int kSegGroups = kReduceThreads / kSegLanes;  // segments in flight per workgroup
+// Records in flight per lane: a step covers 80 records of a segment, so the
+// segments of a 2^19-row level (4096 / 64 = 64 records on average) take one.
+constexpr int kSegStep = 5;
+constexpr int kLevelThreads = 1024;
+constexpr int kCombineThreads = 256;
+// Reduce items of a pass (scatter_split): about kReduceItems of even size, so
+// that the CUs stay busy to the end whatever the tables' sizes, but none
+// smaller than kReduceMinRecords records, below which clearing and writing out
+// the 128 KB of accumulators costs more than the records.
+constexpr int64_t kReduceItems = 768;
+constexpr int64_t kReduceMinRecords = 1 << 15;
 
 // ---------------------------------------------------------------- records
 // A record holds the row within the tile (bits 0-12), an exponent offset r
 // (EB bits) and the two's-complement mantissas qx, qy (MB bits each); its
-// value is (qx, qy) * 2^(E - r - (MB - 1)), E being the level's record
-// exponent, and a record whose larger feature lies below 2^(E - 2^EB - 1) (r
-// beyond EB bits) is dropped.  Two formats:
+// value is (qx, qy) * 2^(E - r - (MB - 1)), E being the record exponent of
+// its item (level, sample block), and a record whose larger feature lies below
+// 2^(E - 2^EB - 1) (r beyond EB bits) is dropped.  Two formats:
 //   full:    EB = 7, MB = 22, one 64-bit word (21 significant bits);
 //   compact: EB = 5, MB = 15, 48 bits kept as a 32-bit word (bits 0-31) in
 //            one array and a 16-bit word (bits 32-47) in another (14
@@ -76,58 +79,61 @@ constexpr int kRecExpBits = 7;
 constexpr int kRecMantBits = 22;
 constexpr int kRecExpBitsC = 5;
 constexpr int kRecMantBitsC = 15;
-
-// Record exponent E of a level whose largest |dy| is lm: a record sums at most
-// 8 contributions w dy with 0 <= w <= 1, so |record| <= 8 lm < 2^(E - 1).
-__device__ __forceinline__ int level_rec_exp(float lm)
-{
-    int e = 0;
-    frexpf(lm, &e);  // lm < 2^e
-    return e + 4;
-}
-
-template <int EB, int MB>
-__device__ __forceinline__ uint64_t encode_record(float2 v, int E, uint32_t row)
-{
-    const float m = fmaxf(fabsf(v.x), fabsf(v.y));
-    uint64_t rec = row;
-    if (m > 0.0f) {
-        int k = 0;
-        frexpf(m, &k);  // 2^(k-1) <= m < 2^k
-        // the larger one can round up to 2^(MB-1), one past the field: it is
-        // held at 2^(MB-1) - 1 (an error of one unit in its last place)
-        constexpr float kMax = (float)((1u << (MB - 1)) - 1u);
-        const float rx = fminf(fmaxf(rintf(ldexpf(v.x, MB - 1 - k)), -kMax), kMax);
-        const float ry = fminf(fmaxf(rintf(ldexpf(v.y, MB - 1 - k)), -kMax), kMax);
-        const int r = E - k;
-        constexpr uint32_t kMant = (1u << MB) - 1u;
-        if (r >= 0 && r < (1 << EB))
-            rec |= (uint64_t)r << kTileBits | (uint64_t)((uint32_t)(int32_t)rx & kMant) << (kTileBits + EB) |
-                   (uint64_t)((uint32_t)(int32_t)ry & kMant) << (kTileBits + EB + MB);
-    }
-    return rec;
-}
-
-// Fields of record word w (format EB, MB): row key, exponent offset, mantissas.
-template <int EB, int MB>
-__device__ __forceinline__ void decode_record(uint64_t w, uint32_t& key, int& r, long long& qx, long long& qy)
-{
-    key = (uint32_t)w & (kTileRows - 1);
-    r = (int)((w >> kTileBits) & ((1u << EB) - 1u));
-    qx = (long long)(w << (64 - kTileBits - EB - MB)) >> (64 - MB);
-    qy = (long long)(w << (64 - kTileBits - EB - 2 * MB)) >> (64 - MB);
-}
-
-// q * 2^sh rounded to an integer (halves upward), for |q| <= 2^21, sh <= 37.
-__device__ __forceinline__ long long scale_mantissa(long long q, int sh)
-{
-    if (sh >= 0) return q * (1ll << min(sh, 40));  // (the clamp only matters for non-finite gradients)
-    const int d = -sh;
-    return d > 62 ? 0ll : (q + (1ll << (d - 1))) >> d;
-}
 static_assert(kTileBits + kRecExpBitsC + 2 * kRecMantBitsC == 48, "compact record fields fill 48 bits");
 static_assert(kTileBits + kRecExpBits + 2 * kRecMantBits == 64, "record fields fill one word");
 
+// Record exponent E of a block whose largest |dy| is bm: a record sums at most
+// 8 contributions w dy with 0 <= w <= 1, so |record| <= 8 bm < 2^(E - 1).
+__device__ __forceinline__ int block_rec_exp(float bm)
+{
+    int e = 0;
+    frexpf(bm, &e);  // bm < 2^e
+    return e + 4;
+}
+
+// Words of the record (lo: bits 0-31, hi: the rest).  The mantissas are
+// rounded to nearest by adding 1.5 * 2^23 (the sum's unit in the last place is
+// 1, its low bits the two's complement of the integer); the larger one can
+// round up to 2^(MB-1), one past the field: it is held at 2^(MB-1) - 1 (an
+// error of one unit in its last place).  Features below 2^-105 are scaled as
+// if they were that large, so the scale stays a normal number.
+template <int EB, int MB>
+__device__ __forceinline__ void encode_record(float2 v, int E, uint32_t row, uint32_t& lo, uint32_t& hi)
+{
+    int k = 0;
+    frexpf(fmaxf(fabsf(v.x), fabsf(v.y)), &k);  // 2^(k-1) <= larger feature < 2^k
+    k = max(k, MB - 1 - 126);
+    const float scale = __uint_as_float((uint32_t)(MB - 1 - k + 127) << 23);
+    constexpr float kMagic = 12582912.0f, kMax = (float)((1u << (MB - 1)) - 1u);
+    const uint32_t bx = __float_as_uint(fminf(fmaxf(fmaf(v.x, scale, kMagic), kMagic - kMax), kMagic + kMax));
+    const uint32_t by = __float_as_uint(fminf(fmaxf(fmaf(v.y, scale, kMagic), kMagic - kMax), kMagic + kMax));
+    const uint32_t r = (uint32_t)(E - k);
+    constexpr int kX = kTileBits + EB;      // first bit of qx
+    constexpr int kXl = 32 - kX;            // its bits in the low word
+    constexpr uint32_t kXh = (1u << (MB - kXl)) - 1u;
+    const bool ok = r < (1u << EB);
+    lo = ok ? (bx << kX) | (r << kTileBits) | row : row;
+    hi = ok ? ((bx >> kXl) & kXh) | (by << (MB - kXl)) : 0u;
+}
+
+// Fields of a record's words: row key, exponent offset, mantissas.
+template <int EB, int MB>
+__device__ __forceinline__ void decode_record(uint32_t lo, uint32_t hi, uint32_t& key, int& r, int& qx, int& qy)
+{
+    const uint64_t w = (uint64_t)hi << 32 | lo;
+    key = lo & (kTileRows - 1);
+    r = (int)((lo >> kTileBits) & ((1u << EB) - 1u));
+    qx = (int)((uint32_t)(w >> (kTileBits + EB)) << (32 - MB)) >> (32 - MB);
+    qy = (int)((uint32_t)(w >> (kTileBits + EB + MB)) << (32 - MB)) >> (32 - MB);
+}
+
+// q * 2^sh rounded to an integer (halves upward), for |q| <= 2^21, sh <= 37
+// (larger shifts only come from non-finite gradients, and are held there).
+__device__ __forceinline__ long long scale_mantissa(int q, int sh)
+{
+    const int d = min(max(40 - sh, 2), 63);
+    return (((long long)q << 40) + (1ll << (d - 1))) >> d;
+}
 
 // ---------------------------------------------------------------- object lookup
 // Index of the last object whose `field` is <= v (fields ascend with the index).
@@ -158,386 +164,99 @@ __device__ __forceinline__ const ScatterObj& sobj(const ScatterArgs& a, int i)
         return a.one;
 }
 
-template <bool kMany>
-__device__ __forceinline__ int obj_of_item(const ScatterArgs& a, int64_t item)
-{
-    return last_le<kMany>(a, item, [](const ScatterObj& o) { return o.item_off; });
-}
-
-template <bool kMany>
-__device__ __forceinline__ int obj_of_tile(const ScatterArgs& a, int64_t tile)
-{
-    return last_le<kMany>(a, tile, [](const ScatterObj& o) { return o.tile_off; });
-}
-
-template <bool kMany>
-__device__ __forceinline__ int obj_of_level(const ScatterArgs& a, int64_t pair)
-{
-    return last_le<kMany>(a, pair, [](const ScatterObj& o) { return (int64_t)o.lev_off; });
-}
-
-// Level of local tile lt of object o.
-__device__ __forceinline__ int level_of_tile(const ScatterObj& o, int lt)
+// Last level whose first entry in `base` is <= v.
+__device__ __forceinline__ int level_of(const int32_t* base, int n_levels, int v)
 {
     int l = 0;
-    while (l + 1 < o.grid.n_levels && o.tile_base[l + 1] <= lt) ++l;
+    while (l + 1 < n_levels && base[l + 1] <= v) ++l;
     return l;
 }
 
-// Ray of global sample gs (S samples per ray); 32-bit division when it fits.
-__device__ __forceinline__ int64_t ray_of_sample(int64_t gs, int S)
+// First entry of item (level l, block bx) of object o in the segment starts:
+// tiles[l] + 1 of them per item.
+__device__ __forceinline__ int64_t seg_index(const ScatterObj& o, int l, int bx)
 {
-    return gs < ((int64_t)1 << 32) ? (int64_t)((uint32_t)gs / (uint32_t)S) : gs / S;
+    return o.seg_off + (int64_t)o.n_blocks * (o.tile_base[l] + l) + (int64_t)bx * (o.tiles[l] + 1);
 }
 
-// Feature gradient and corners of local sample s on level l of object o;
-// false when dy == 0 (the sample contributes nothing and is skipped by count
-// and place alike).  The gradient, t and the ray are loaded together and the
-// corners computed whatever dy is, so the loads are not serialised behind the
-// test.
-__device__ __forceinline__ bool load_contrib(const ScatterArgs& a, const ScatterObj& o, int l, int64_t s, float2& d,
-                                             Corners& c)
+// Dynamic LDS of the place kernel for levels of at most nt tiles: staged
+// records, histogram (then segment starts, and the total).
+__host__ __device__ constexpr size_t place_lds_bytes(int nt, bool compact)
 {
-    const int64_t gs = o.s_begin + s;
-    const float* ro = a.ray_obj + 6 * ray_of_sample(gs, a.S);
-    d = a.dy[o.dy_off + (int64_t)l * o.n_s + s];
-    const float ts = a.t[gs];
-    level_corners(o.grid, l, sample_coord(ts, ro[3], ro[0]), sample_coord(ts, ro[4], ro[1]),
-                  sample_coord(ts, ro[5], ro[2]), c);
-    return d.x != 0.0f || d.y != 0.0f;
+    return (size_t)kRecordsPerBlock * (compact ? 6 : 8) + (size_t)(nt + 1) * 4;
 }
 
-// Level and sample block of count/place item `rem` of an object (fits 32 bits).
-__device__ __forceinline__ void split_item(int64_t rem, int n_blocks, int& l, int& bx)
-{
-    const uint32_t r = (uint32_t)rem;
-    l = (int)(r / (uint32_t)n_blocks);
-    bx = (int)(r - (uint32_t)l * (uint32_t)n_blocks);
-}
-
-template <bool kMany>
-__global__ __launch_bounds__(kPlaceThreads) void k_scatter_count(ScatterArgs a)
-{
-    __shared__ uint32_t hist[kMaxTilesPerLevel];
-    __shared__ float wmax[kPlaceThreads / 64];
-    const int64_t item = blockIdx.x;
-    const ScatterObj& o = sobj<kMany>(a, obj_of_item<kMany>(a, item));
-    int l, bx;
-    split_item(item - o.item_off, o.n_blocks, l, bx);
-    const int nt = o.tiles[l];
-    for (int i = threadIdx.x; i < nt; i += kPlaceThreads) hist[i] = 0;
-    __syncthreads();
-    float m = 0.0f;
-    const int64_t s = (int64_t)bx * kSamplesPerBlock + threadIdx.x;
-    float2 d;
-    Corners c{};  // lanes past the samples take part in the wave's count with no records
-    bool has;
-    uint32_t heads = 0xffu;
-    if (a.merge_runs) {  // every sample, runs of a repeated corner as one record
-        has = s < o.n_s;
-        load_contrib(a, o, l, has ? s : o.n_s - 1, d, c);
-        heads = run_heads(c, has);
-    } else {
-        has = s < o.n_s && load_contrib(a, o, l, s, d, c);
-    }
-    if (a.nonfinite && s < o.n_s && !(isfinite(d.x) && isfinite(d.y))) a.nonfinite[0] = 1;
-    if (has) m = fmaxf(fabsf(d.x), fabsf(d.y));
-    count_records(hist, c, has ? heads : 0u, nt);
-#pragma unroll
-    for (int dd = 32; dd >= 1; dd >>= 1) m = fmaxf(m, __shfl_xor(m, dd));
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
-    __syncthreads();
-    uint32_t* out = a.counts + o.count_off + (int64_t)o.tile_base[l] * o.n_blocks + bx;
-    for (int i = threadIdx.x; i < nt; i += kPlaceThreads) out[(int64_t)i * o.n_blocks] = hist[i];
-    if (threadIdx.x == 0) {
-        float bm = 0.0f;
-        for (int w = 0; w < kPlaceThreads / 64; ++w) bm = fmaxf(bm, wmax[w]);
-        a.block_max[o.bmax_off + (int64_t)l * o.n_blocks + bx] = bm;
-    }
-}
-
-// Max |dy| of each (object, level) over its sample blocks; one block per pair.
-// With fwd_counts the histograms exist already: per (level, sample block)
-// only the max |dy| that fixes the fixed-point scale.  A workgroup takes
-// kDymaxItems consecutive items (consecutive blocks of one level lie next to
-// each other in dy), with all their loads in flight at once.
-constexpr int kDymaxItems = 8;
-
-template <bool kMany>
-__global__ __launch_bounds__(kPlaceThreads) void k_scatter_dymax(ScatterArgs a)
-{
-    constexpr int kRows = kPlaceThreads / 16;  // 16-lane DPP rows per workgroup
-    __shared__ float wmax[kDymaxItems][kRows];
-    float m[kDymaxItems];
-    bool bad = false;
-    // object of the first item by search; the next items follow it (consecutive
-    // items belong to the same object or to the ones after it)
-    const int64_t item0 = (int64_t)blockIdx.x * kDymaxItems;
-    int oi = obj_of_item<kMany>(a, item0 < a.n_items ? item0 : a.n_items - 1);
-#pragma unroll
-    for (int j = 0; j < kDymaxItems; ++j) {
-        const int64_t item = item0 + j;
-        m[j] = 0.0f;
-        if (item < a.n_items) {
-            if constexpr (kMany)
-                while (oi + 1 < a.n_obj && a.objs[oi + 1].item_off <= item) ++oi;
-            const ScatterObj& o = sobj<kMany>(a, oi);
-            int l, bx;
-            split_item(item - o.item_off, o.n_blocks, l, bx);
-            const int64_t s = (int64_t)bx * kSamplesPerBlock + threadIdx.x;
-            if (s < o.n_s) {
-                const float2 d = a.dy[o.dy_off + (int64_t)l * o.n_s + s];
-                m[j] = fmaxf(fabsf(d.x), fabsf(d.y));
-                bad |= !(isfinite(d.x) && isfinite(d.y));
-            }
-        }
-    }
-    // a non-finite feature gradient (fmaxf would drop a NaN) marks the step
-    // for the loss scaler, which then skips the update
-    if (a.nonfinite && bad) a.nonfinite[0] = 1;
-    // Row maxima by DPP row shifts: lanes past the row's end read 0, the
-    // identity of a maximum of |dy| values; the row's first lane ends with it.
-#pragma unroll
-    for (int j = 0; j < kDymaxItems; ++j) {
-        m[j] = fmaxf(m[j], dpp_f32<0x101>(m[j]));
-        m[j] = fmaxf(m[j], dpp_f32<0x102>(m[j]));
-        m[j] = fmaxf(m[j], dpp_f32<0x104>(m[j]));
-        m[j] = fmaxf(m[j], dpp_f32<0x108>(m[j]));
-        if ((threadIdx.x & 15) == 0) wmax[j][threadIdx.x >> 4] = m[j];
-    }
-    __syncthreads();
-    if (threadIdx.x < kDymaxItems) {
-        const int64_t item = item0 + threadIdx.x;
-        if (item < a.n_items) {
-            const ScatterObj& o = sobj<kMany>(a, obj_of_item<kMany>(a, item));
-            int l, bx;
-            split_item(item - o.item_off, o.n_blocks, l, bx);
-            float bm = 0.0f;
-            for (int w = 0; w < kRows; ++w) bm = fmaxf(bm, wmax[threadIdx.x][w]);
-            a.block_max[o.bmax_off + (int64_t)l * o.n_blocks + bx] = bm;
-        }
-    }
-}
-
-// One workgroup per (object, level) of the pass; a pass has few of them, so
-// each takes 16 waves (a maximum does not depend on the order).
-constexpr int kLevelMaxThreads = 1024;
-template <bool kMany>
-__global__ __launch_bounds__(kLevelMaxThreads) void k_scatter_level_max(ScatterArgs a)
-{
-    __shared__ float red[kLevelMaxThreads / 64];
-    const int pair = blockIdx.x;
-    const ScatterObj& o = sobj<kMany>(a, obj_of_level<kMany>(a, pair));
-    const int l = pair - o.lev_off;
-    const float* bm = a.block_max + o.bmax_off + (int64_t)l * o.n_blocks;
-    float m = 0.0f;
-    for (int b = threadIdx.x; b < o.n_blocks; b += kLevelMaxThreads) m = fmaxf(m, bm[b]);
-#pragma unroll
-    for (int dd = 32; dd >= 1; dd >>= 1) m = fmaxf(m, __shfl_xor(m, dd));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float r = 0.0f;
-        for (int w = 0; w < kLevelMaxThreads / 64; ++w) r = fmaxf(r, red[w]);
-        a.level_max[pair] = r;
-    }
-}
-
-// Inclusive prefix sum over the 64 lanes of a wave.
-__device__ __forceinline__ uint64_t wave_incl_scan(uint64_t v, int lane)
-{
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint64_t up = __shfl_up(v, d);
-        if (lane >= d) v += up;
-    }
-    return v;
-}
-
-// Per tile: exclusive prefix of the per-block counts (into offsets, so the
-// forward's histograms survive for another backward) and the total.
-// Thread t owns a contiguous run of blocks; the runs' sums are scanned within
-// each wave, then across the block's waves.
-template <bool kMany>
-__global__ __launch_bounds__(kScanThreads) void k_scatter_scan_blocks(ScatterArgs a)
-{
-    constexpr int kWaves = kScanThreads / 64;
-    __shared__ uint64_t wave_tot[kWaves];
-    const int64_t tile = blockIdx.x;
-    const ScatterObj& o = sobj<kMany>(a, obj_of_tile<kMany>(a, tile));
-    const int nb = o.n_blocks;
-    const int64_t row0 = o.count_off + (tile - o.tile_off) * nb;
-    const uint32_t* row = a.counts + row0;
-    uint32_t* orow = a.offsets + row0;
-    const int per = (nb + kScanThreads - 1) / kScanThreads;
-    const int b0 = min((int)threadIdx.x * per, nb), b1 = min(b0 + per, nb);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint64_t sum = 0;
-    for (int b = b0; b < b1; ++b) sum += row[b];
-    const uint64_t incl = wave_incl_scan(sum, lane);
-    if (lane == 63) wave_tot[wave] = incl;
-    __syncthreads();
-    if (wave == 0) {
-        const uint64_t t = lane < kWaves ? wave_tot[lane] : 0;
-        const uint64_t ti = wave_incl_scan(t, lane);
-        if (lane < kWaves) wave_tot[lane] = ti - t;  // exclusive over waves
-        if (lane == kWaves - 1) a.tile_total[tile] = ti;
-    }
-    __syncthreads();
-    uint64_t run = wave_tot[wave] + incl - sum;
-    for (int b = b0; b < b1; ++b) {
-        orow[b] = (uint32_t)run;  // offsets within a tile fit 32 bits
-        run += row[b];
-    }
-}
-
-// Over all tiles: record bases, chunk counts and chunk bases, the fixed-point
-// exponent of each tile; resets the work counter.
-template <bool kMany>
-__global__ __launch_bounds__(kScanThreads) void k_scatter_scan_tiles(ScatterArgs a)
-{
-    __shared__ uint64_t prec[kScanThreads], pchk[kScanThreads];
-    const int64_t n = a.n_tiles;
-    const int64_t per = (n + kScanThreads - 1) / kScanThreads;
-    const int64_t t0 = threadIdx.x * per, t1 = min(t0 + per, n);
-    uint64_t rs = 0, cs = 0;
-    for (int64_t t = t0; t < t1; ++t) rs += a.tile_total[t];
-    prec[threadIdx.x] = rs;
-    __syncthreads();
-    for (int d = 1; d < kScanThreads; d <<= 1) {
-        const uint64_t v = threadIdx.x >= d ? prec[threadIdx.x - d] : 0;
-        __syncthreads();
-        prec[threadIdx.x] += v;
-        __syncthreads();
-    }
-    // chunk size from the pass's record total
-    const uint64_t per_item = prec[kScanThreads - 1] / ((uint64_t)a.reduce_blocks * kChunksPerBlock);
-    int cb = min(max(a.chunk_min_bits, kChunkMinBits), kChunkMaxBits);
-    while (cb < kChunkMaxBits && ((uint64_t)1 << cb) < per_item) ++cb;
-    const uint64_t chunk = (uint64_t)1 << cb;
-    for (int64_t t = t0; t < t1; ++t) cs += (a.tile_total[t] + chunk - 1) >> cb;
-    pchk[threadIdx.x] = cs;
-    __syncthreads();
-    for (int d = 1; d < kScanThreads; d <<= 1) {
-        const uint64_t w = threadIdx.x >= d ? pchk[threadIdx.x - d] : 0;
-        __syncthreads();
-        pchk[threadIdx.x] += w;
-        __syncthreads();
-    }
-    uint64_t r = prec[threadIdx.x] - rs, ck = pchk[threadIdx.x] - cs;
-    for (int64_t t = t0; t < t1; ++t) {
-        a.tile_start[t] = r;
-        a.chunk_start[t] = ck;
-        r += a.tile_total[t];
-        ck += (a.tile_total[t] + chunk - 1) >> cb;
-        // largest e with vmax * records * 2^e < 2^62 (bound on any row's
-        // |sum| * 2^e) and vmax * 2^e < 2^50 (bound on one record's fixed-point
-        // value, so a record's mantissa is shifted by at most 33 bits), vmax
-        // the largest record: max|dy|, or 8 max|dy| when repeated corners are
-        // merged
-        const ScatterObj& o = sobj<kMany>(a, obj_of_tile<kMany>(a, t));
-        const int l = level_of_tile(o, (int)(t - o.tile_off));
-        // (a merged record sums at most 8 contributions, one per lane of a group)
-        const double vmax = (double)a.level_max[o.lev_off + l] * (a.merge_runs ? 8.0 : 1.0);
-        const double bound = vmax * (double)a.tile_total[t];
-        int e = 0;
-        if (bound > 0.0) {
-            int ex, evx;
-            frexp(bound, &ex);  // bound < 2^ex
-            frexp(vmax, &evx);  // vmax < 2^evx
-            e = min(62 - ex, 50 - evx);
-        }
-        a.tile_exp[t] = e;
-    }
-    if (threadIdx.x == kScanThreads - 1) {
-        // Histograms from the forward cannot hold more records than there
-        // are corners of samples; if they do (a backward whose workspace
-        // holds no forward of these rays), no chunk is handed out and place
-        // stops at once.
-        const bool ok = !a.fwd_counts || prec[kScanThreads - 1] <= (uint64_t)a.n_records;
-        a.tile_start[n] = ok ? prec[kScanThreads - 1] : ~0ull;
-        a.chunk_start[n] = ok ? pchk[kScanThreads - 1] : 0ull;
-        a.chunk_start[n + 1] = (uint64_t)cb;
-        *a.work_counter = 0;
-    }
-}
-
-// Dynamic LDS of the place kernel for nt tiles of one level, with staged tile
-// ids of tile_bytes bytes: record bases, staged records, histogram, block
-// segments, the total, staged tile ids.
-__host__ __device__ constexpr size_t place_lds_bytes(int nt, int tile_bytes)
-{
-    return (size_t)nt * 8 + (size_t)kRecordsPerBlock * 8 + (size_t)nt * 8 + 16 + (size_t)kRecordsPerBlock * tile_bytes;
-}
-
-// TileT: type of the staged local tile ids (uint8_t when a level has at most
-// 256 tiles, which keeps the block's LDS under 40 KB: four blocks per CU).
-template <bool kMany, typename TileT>
+// Place is bound by its vector instructions (ranks, record encoding, corner
+// arithmetic).  A block's 4096 records fill 32 KB of LDS (24 KB compact), so
+// four workgroups of eight waves share a CU.
+template <bool kMany, bool kCompact>
 __global__ __launch_bounds__(kPlaceThreads) void k_scatter_place(ScatterArgs a)
 {
+    constexpr int EB = kCompact ? kRecExpBitsC : kRecExpBits, MB = kCompact ? kRecMantBitsC : kRecMantBits;
+    constexpr int kRows = kPlaceThreads / 16;  // 16-lane DPP rows per workgroup
     extern __shared__ __align__(16) unsigned char smem[];
-    const int nt_lds = a.tiles_max;
-    uint64_t* gbase = reinterpret_cast<uint64_t*>(smem);
-    uint64_t* s_rec = gbase + nt_lds;
-    uint32_t* hist = reinterpret_cast<uint32_t*>(s_rec + kRecordsPerBlock);
-    uint32_t* seg = hist + nt_lds;
-    uint32_t* p_total = seg + nt_lds;
-    TileT* s_tile = reinterpret_cast<TileT*>(p_total + 4);
+    __shared__ float wmax[kRows];
+    uint64_t* s_rec = reinterpret_cast<uint64_t*>(smem);  // full records
+    uint32_t* s_lo = reinterpret_cast<uint32_t*>(smem);   // compact records: low words, then high words
+    uint16_t* s_hi = reinterpret_cast<uint16_t*>(s_lo + kRecordsPerBlock);
+    uint32_t* hist = reinterpret_cast<uint32_t*>(smem + kRecordsPerBlock * (kCompact ? 6 : 8));
     const int64_t item = blockIdx.x;
-    const ScatterObj& o = sobj<kMany>(a, obj_of_item<kMany>(a, item));
-    int l, bx;
-    split_item(item - o.item_off, o.n_blocks, l, bx);
+    const ScatterObj& o = sobj<kMany>(a, last_le<kMany>(a, item, [](const ScatterObj& v) { return v.item_off; }));
+    const uint32_t rem = (uint32_t)(item - o.item_off);
+    const int l = (int)(rem / (uint32_t)o.n_blocks);
+    const int bx = (int)(rem - (uint32_t)l * (uint32_t)o.n_blocks);
     const int nt = o.tiles[l];
-    if (a.fwd_counts && a.tile_start[a.n_tiles] > (uint64_t)a.n_records) return;  // uniform: the scan's verdict
-    // Global start of this block's run in the thread's tile (thread i holds
-    // tile i; threads past the level's tiles load tile nt - 1 and ignore it).
-    // Loaded first, together with the contribution, so the block waits on
-    // global memory once.
-    const int tb = o.tile_base[l];
-    const int own = min((int)threadIdx.x, nt - 1);
-    const uint64_t own_start = a.tile_start[o.tile_off + tb + own];
-    const uint32_t own_off = a.offsets[o.count_off + (int64_t)(tb + own) * o.n_blocks + bx];
-    const int E = level_rec_exp(a.level_max[o.lev_off + l]);
-    for (int i = threadIdx.x; i < nt; i += kPlaceThreads) hist[i] = 0;
-    __syncthreads();
-    // pass 1: rank of each contribution within its tile (LDS atomics)
+    // The gradient, t and the ray are loaded together and the corners computed
+    // whatever dy is, so the loads are not serialised behind a test.
     const int64_t s = (int64_t)bx * kSamplesPerBlock + threadIdx.x;
-    float2 d;
+    const bool in = s < o.n_s;
+    const int64_t sl = in ? s : o.n_s - 1;
+    const int64_t gs = o.s_begin + sl;  // < 2^29 samples
+    const float* ro = a.ray_obj + 6 * (int64_t)((uint32_t)gs / (uint32_t)a.S);
+    const float2 d = a.dy[o.dy_off + (int64_t)l * o.n_s + sl];
+    const float ts = a.t[gs];
+    for (int i = threadIdx.x; i < nt; i += kPlaceThreads) hist[i] = 0;
     Corners c;
-    bool has;
-    uint32_t heads = 0xffu;  // corners that start a record
+    level_corners(o.grid, l, sample_coord(ts, ro[3], ro[0]), sample_coord(ts, ro[4], ro[1]),
+                  sample_coord(ts, ro[5], ro[2]), c);
+    const bool has = in && (d.x != 0.0f || d.y != 0.0f);
+    // a non-finite feature gradient (fmaxf would drop a NaN) marks the step
+    // for the loss scaler, which then skips the update
+    if (a.nonfinite && in && !(isfinite(d.x) && isfinite(d.y))) a.nonfinite[0] = 1;
+    // Row maxima by DPP row shifts: lanes past the row's end read 0, the
+    // identity of a maximum of |dy| values; the row's first lane ends with it.
+    float m = has ? fmaxf(fabsf(d.x), fabsf(d.y)) : 0.0f;
+    m = fmaxf(m, dpp_f32<0x101>(m));
+    m = fmaxf(m, dpp_f32<0x102>(m));
+    m = fmaxf(m, dpp_f32<0x104>(m));
+    m = fmaxf(m, dpp_f32<0x108>(m));
+    if ((threadIdx.x & 15) == 0) wmax[threadIdx.x >> 4] = m;
+    const uint32_t heads = run_heads(c, has);  // corners that start a record
     float2 val[8];
-    if (a.merge_runs) {
-        // every sample counted, repeated corners merged as the count (or the
-        // forward) did: samples are a prefix of the wave, every lane takes part
-        has = s < o.n_s;
-        load_contrib(a, o, l, has ? s : o.n_s - 1, d, c);
-        heads = run_heads(c, has);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            val[e] = has ? make_float2(c.w[e] * d.x, c.w[e] * d.y) : make_float2(0.0f, 0.0f);
-            const bool head = (heads >> e) & 1u;
-            if (__ballot(has && !head)) val[e] = run_sum(val[e], head || !has);
-        }
-    } else {
-        has = s < o.n_s && load_contrib(a, o, l, s, d, c);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) val[e] = make_float2(c.w[e] * d.x, c.w[e] * d.y);
-    }
-    uint32_t rank[8];
-    if (has) {
-        if (nt <= kAggregateTiles) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if ((heads >> e) & 1u) rank[e] = wave_aggregated_add(hist, c.row[e] >> kTileBits);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if ((heads >> e) & 1u) rank[e] = atomicAdd(&hist[c.row[e] >> kTileBits], 1u);
-        }
+    for (int e = 0; e < 8; ++e) {
+        val[e] = has ? make_float2(c.w[e] * d.x, c.w[e] * d.y) : make_float2(0.0f, 0.0f);
+        const bool head = (heads >> e) & 1u;
+        if (__ballot(has && !head)) val[e] = run_sum(val[e], head || !has);
     }
     __syncthreads();
-    // block-local segments: exclusive scan of hist (by one wave)
+    // rank of each record within its tile (LDS atomics)
+    uint32_t rank[8];
+    if (nt <= kAggregateTiles) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if ((heads >> e) & 1u) rank[e] = wave_aggregated_add(hist, c.row[e] >> kTileBits);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if ((heads >> e) & 1u) rank[e] = atomicAdd(&hist[c.row[e] >> kTileBits], 1u);
+    }
+    float bm = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) bm = fmaxf(bm, wmax[i]);
+    const int E = block_rec_exp(bm);
+    __syncthreads();
+    // segment starts: exclusive scan of the histogram in place (by one wave)
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         uint32_t carry = 0;
@@ -549,247 +268,284 @@ __global__ __launch_bounds__(kPlaceThreads) void k_scatter_place(ScatterArgs a)
                 const uint32_t up = __shfl_up(incl, dd);
                 if (lane >= dd) incl += up;
             }
-            if (i < nt) seg[i] = carry + incl - v;
+            if (i < nt) hist[i] = carry + incl - v;
             carry += __shfl(incl, 63);
         }
-        if (lane == 0) *p_total = carry;
-    }
-    __syncthreads();
-    // global position of record p of local tile tt: gbase[tt] + p
-    {
-        const uint32_t* cnt = a.offsets + o.count_off;
-        if ((int)threadIdx.x < nt) gbase[threadIdx.x] = own_start + own_off - seg[threadIdx.x];
-        for (int i = threadIdx.x + kPlaceThreads; i < nt; i += kPlaceThreads)
-            gbase[i] = a.tile_start[o.tile_off + tb + i] + cnt[(int64_t)(tb + i) * o.n_blocks + bx] - seg[i];
-    }
-    // pass 2: stage the encoded records sorted by tile (corners kept from pass 1)
-    if (has) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            if (!((heads >> e) & 1u)) continue;
-            const uint32_t tt = c.row[e] >> kTileBits;
-            const uint32_t p = seg[tt] + rank[e];
-            s_rec[p] = a.compact ? encode_record<kRecExpBitsC, kRecMantBitsC>(val[e], E, c.row[e] & (kTileRows - 1))
-                                 : encode_record<kRecExpBits, kRecMantBits>(val[e], E, c.row[e] & (kTileRows - 1));
-            s_tile[p] = (TileT)tt;
+        if (lane == 0) {
+            hist[nt] = carry;
+            a.block_max[item] = bm;
         }
     }
     __syncthreads();
-    // write each tile's run to its global range: consecutive threads, consecutive records
-    // The staging arrays hold kRecordsPerBlock entries, so the LDS reads of
-    // several records are issued before the guarded stores.
-    const uint32_t total = *p_total;
-    constexpr int kPer = kRecordsPerBlock / kPlaceThreads, kHalf = kPer / 2;
+    // stage the encoded records sorted by tile
 #pragma unroll
-    for (int h = 0; h < kPer; h += kHalf) {
-        if (h * kPlaceThreads >= (int)total) break;
-        uint32_t tt[kHalf];
-        uint64_t rec[kHalf];
-#pragma unroll
-        for (int k = 0; k < kHalf; ++k) {
-            const uint32_t p = threadIdx.x + (h + k) * kPlaceThreads;
-            tt[k] = s_tile[p];
-            rec[k] = s_rec[p];
+    for (int e = 0; e < 8; ++e) {
+        if (!((heads >> e) & 1u)) continue;
+        const uint32_t p = hist[c.row[e] >> kTileBits] + rank[e];
+        uint32_t lo, hi;
+        encode_record<EB, MB>(val[e], E, c.row[e] & (kTileRows - 1), lo, hi);
+        if constexpr (kCompact) {
+            s_lo[p] = lo;
+            s_hi[p] = (uint16_t)hi;
+        } else {
+            s_rec[p] = (uint64_t)hi << 32 | lo;
         }
-#pragma unroll
-        for (int k = 0; k < kHalf; ++k) {
-            const uint32_t p = threadIdx.x + (h + k) * kPlaceThreads;
-            const uint64_t dst = gbase[min(tt[k], (uint32_t)nt - 1u)] + p;
-            if (p < total && dst < (uint64_t)a.n_records) {
-                if (a.compact) {
-                    reinterpret_cast<uint32_t*>(a.recs)[dst] = (uint32_t)rec[k];
-                    reinterpret_cast<uint16_t*>(reinterpret_cast<uint32_t*>(a.recs) + a.n_records)[dst] =
-                        (uint16_t)(rec[k] >> 32);
-                } else {
-                    a.recs[dst] = rec[k];
-                }
-            }
-        }
+    }
+    uint16_t* seg = a.seg + seg_index(o, l, bx);
+    for (int i = threadIdx.x; i <= nt; i += kPlaceThreads) seg[i] = (uint16_t)hist[i];
+    __syncthreads();
+    // the block's records to its range of the record array, 16 bytes per lane
+    const uint32_t total = hist[nt];
+    if constexpr (kCompact) {
+        uint32_t* glo = reinterpret_cast<uint32_t*>(a.recs) + item * kRecordsPerBlock;
+        uint16_t* ghi = reinterpret_cast<uint16_t*>(reinterpret_cast<uint32_t*>(a.recs) + a.n_records) +
+                        item * kRecordsPerBlock;
+        for (uint32_t p = threadIdx.x * 4; p < total; p += kPlaceThreads * 4)
+            *reinterpret_cast<uint4*>(glo + p) = *reinterpret_cast<const uint4*>(s_lo + p);
+        for (uint32_t p = threadIdx.x * 8; p < total; p += kPlaceThreads * 8)
+            *reinterpret_cast<uint4*>(ghi + p) = *reinterpret_cast<const uint4*>(s_hi + p);
+    } else {
+        uint64_t* g = a.recs + item * kRecordsPerBlock;
+        for (uint32_t p = threadIdx.x * 2; p < total; p += kPlaceThreads * 2)
+            *reinterpret_cast<uint4*>(g + p) = *reinterpret_cast<const uint4*>(s_rec + p);
     }
 }
 
+// Fixed-point exponent of each (object, level): the largest e with
+//   sum over the blocks of 512 max|dy| * 2^e < 2^62  (bound on any row's sum)
+//   8 max|dy| * 2^e < 2^50                            (bound on one record)
+// One workgroup per pair; a pass has few of them, so each takes 16 waves.  The
+// sum of the maxima is taken in FP64 in a fixed order.
+template <bool kMany>
+__global__ __launch_bounds__(kLevelThreads) void k_scatter_level(ScatterArgs a)
+{
+    __shared__ float red[kLevelThreads / 64];
+    __shared__ double sum[kLevelThreads / 64];
+    const int pair = blockIdx.x;
+    const ScatterObj& o = sobj<kMany>(a, last_le<kMany>(a, pair, [](const ScatterObj& v) { return (int64_t)v.lev_off; }));
+    const int l = pair - o.lev_off;
+    const float* bm = a.block_max + o.item_off + (int64_t)l * o.n_blocks;
+    float m = 0.0f;
+    double t = 0.0;
+    for (int b = threadIdx.x; b < o.n_blocks; b += kLevelThreads) {
+        m = fmaxf(m, bm[b]);
+        t += (double)bm[b];
+    }
+#pragma unroll
+    for (int dd = 32; dd >= 1; dd >>= 1) {
+        m = fmaxf(m, __shfl_xor(m, dd));
+        t += __shfl_xor(t, dd);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = m;
+        sum[threadIdx.x >> 6] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float r = 0.0f;
+        double b = 0.0;
+        for (int w = 0; w < kLevelThreads / 64; ++w) {
+            r = fmaxf(r, red[w]);
+            b += sum[w];
+        }
+        int e = 0;
+        b *= (double)kSamplesPerBlock;
+        if (b > 0.0 && isfinite(b)) {
+            int ex, evx;
+            frexp(b, &ex);    // bound < 2^ex
+            frexpf(r, &evx);  // max|dy| < 2^evx
+            e = min(62 - ex, 47 - evx);
+        }
+        a.level_exp[pair] = e;
+    }
+}
+
+// One workgroup per reduce item: blocks [b0, b1) of one tile.  Its segments
+// are read 16 lanes each (128 contiguous bytes a load), the next step's records
+// requested before the current one's are added.  Bound by the LDS atomics
+// (two 64-bit adds per record).
 template <bool kMany, bool kCompact>
 __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a)
 {
     constexpr int EB = kCompact ? kRecExpBitsC : kRecExpBits, MB = kCompact ? kRecMantBitsC : kRecMantBits;
-    // a run's words: four 16-byte loads of 64-bit records, or two of 32-bit
-    // low words and one of 16-bit high words
-    constexpr int kLoads = kCompact ? 3 : kRun / 2;
     __shared__ unsigned long long acc[2 * kTileRows];  // fixed point: feature 0 rows, then feature 1 rows
-    __shared__ int64_t s_chunk;
-    const uint64_t n_chunks = a.chunk_start[a.n_tiles];
-    const int cb = (int)a.chunk_start[a.n_tiles + 1];
-    for (;;) {
-        if (threadIdx.x == 0) s_chunk = (int64_t)atomicAdd(a.work_counter, 1ull);
-        __syncthreads();
-        const int64_t chunk = s_chunk;
-        __syncthreads();
-        if ((uint64_t)chunk >= n_chunks) break;
-        // tile of this chunk: last t with chunk_start[t] <= chunk
-        int64_t lo = 0, hi = a.n_tiles - 1;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi + 1) >> 1;
-            if (a.chunk_start[mid] <= (uint64_t)chunk)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        const int64_t tile = lo;
-        const ScatterObj& o = sobj<kMany>(a, obj_of_tile<kMany>(a, tile));
-        const int lt = (int)(tile - o.tile_off);
-        const int l = level_of_tile(o, lt);
-        const int tt = lt - o.tile_base[l];
-        const int64_t row0 = (int64_t)tt << kTileBits;
-        const int n_rows = (int)min((int64_t)kTileRows, o.level_rows[l] - row0);
-        const uint64_t k0 = chunk - a.chunk_start[tile];
-        const uint64_t r_begin = a.tile_start[tile] + (k0 << cb);
-        const uint64_t r_end = min(r_begin + ((uint64_t)1 << cb), a.tile_start[tile + 1]);
-        const bool owner = (a.chunk_start[tile + 1] - a.chunk_start[tile]) == 1;
-        const int ex = a.tile_exp[tile];
-        // a record (qx, qy, r) is worth (qx, qy) 2^(E - r - (MB - 1)); in fixed
-        // point at 2^ex that is (qx, qy) 2^(sh0 - r)
-        const int sh0 = level_rec_exp(a.level_max[o.lev_off + l]) - (MB - 1) + ex;
-        for (int i = threadIdx.x; i < n_rows; i += kReduceThreads) {
-            acc[i] = 0ull;
-            acc[kTileRows + i] = 0ull;
-        }
-        __syncthreads();
-        // Each thread takes runs of kRun consecutive records (four 16-byte
-        // loads; runs start at multiples of kRun, so the loads are aligned and
-        // stay inside the record array, whose length is a multiple of kRun).
-        // Records of a run outside [r_begin, r_end) add zero.  Consecutive
-        // records often carry the same row (neighbouring samples of one ray on
-        // a coarse level); such repeats are summed in registers first, so one
-        // LDS atomic per row and run is issued instead of one per record.
-        const uint64_t q_begin = r_begin / kRun, q_end = (r_end + kRun - 1) / kRun;
-        for (uint64_t q0 = q_begin + threadIdx.x; q0 < q_end; q0 += (uint64_t)kReduceThreads * kRunsPerThread) {
-            uint4 rw[kRunsPerThread][kLoads];
+    const int64_t ritem = blockIdx.x;
+    const ScatterObj& o = sobj<kMany>(a, last_le<kMany>(a, ritem, [](const ScatterObj& v) { return v.ritem_off; }));
+    const int rl = (int)(ritem - o.ritem_off);
+    const int l = level_of(o.ritem_base, o.grid.n_levels, rl);
+    const int n_split = o.split[l];
+    const int tt = (rl - o.ritem_base[l]) / n_split;
+    const int part = (rl - o.ritem_base[l]) - tt * n_split;
+    const int nb = o.n_blocks;
+    const int per = (nb + n_split - 1) / n_split;
+    const int b0 = min(part * per, nb), b1 = min(b0 + per, nb);
+    const int64_t row0 = (int64_t)tt << kTileBits;
+    const int n_rows = (int)min((int64_t)kTileRows, o.level_rows[l] - row0);
+    const int ex = a.level_exp[o.lev_off + l];
+    for (int i = threadIdx.x; i < n_rows; i += kReduceThreads) {
+        acc[i] = 0ull;
+        acc[kTileRows + i] = 0ull;
+    }
+    __syncthreads();
+    if (b0 < b1) {
+        const int ln = threadIdx.x & (kSegLanes - 1);
+        const int nt1 = o.tiles[l] + 1;
+        const uint16_t* seg = a.seg + seg_index(o, l, 0) + tt;
+        const int64_t item0 = o.item_off + (int64_t)l * nb;
+        const float* bmx = a.block_max + item0;
+        // Segment of one block: the step's first record p, the end, the block's
+        // max |dy|.  Loads are unconditional, of clamped addresses, and what
+        // they return is looked at only when it is used, so that none waits for
+        // another.
+        struct Seg {
+            int p, end;
+            float bm;
+            int64_t base;
+        };
+        auto header = [&](int b) {
+            const int bc = min(b, b1 - 1);
+            Seg h;
+            h.p = seg[(int64_t)bc * nt1];
+            h.end = seg[(int64_t)bc * nt1 + 1];
+            h.bm = bmx[bc];
+            h.base = (item0 + bc) * kRecordsPerBlock;
+            return h;
+        };
+        auto load = [&](const Seg& h, uint32_t (&lo)[kSegStep], uint32_t (&hi)[kSegStep]) {
 #pragma unroll
-            for (int u = 0; u < kRunsPerThread; ++u) {
-                const uint64_t q = q0 + (uint64_t)u * kReduceThreads;
-                const uint64_t qc = q < q_end ? q : q_begin;
+            for (int u = 0; u < kSegStep; ++u) {
+                const int i = h.p + ln + u * kSegLanes;
+                // (a segment may be empty and start at the end of the block's range)
+                const int64_t at = h.base + (i < h.end ? i : min(h.p, kRecordsPerBlock - 1));
                 if constexpr (kCompact) {
-                    const uint32_t* lo = reinterpret_cast<const uint32_t*>(a.recs);
-                    const uint16_t* hi = reinterpret_cast<const uint16_t*>(lo + a.n_records);
-                    rw[u][0] = reinterpret_cast<const uint4*>(lo + qc * kRun)[0];
-                    rw[u][1] = reinterpret_cast<const uint4*>(lo + qc * kRun)[1];
-                    rw[u][2] = reinterpret_cast<const uint4*>(hi + qc * kRun)[0];
+                    const uint32_t* words = reinterpret_cast<const uint32_t*>(a.recs);
+                    lo[u] = words[at];
+                    hi[u] = reinterpret_cast<const uint16_t*>(words + a.n_records)[at];
                 } else {
-                    const uint4* rp = reinterpret_cast<const uint4*>(a.recs + qc * kRun);
-#pragma unroll
-                    for (int i = 0; i < kRun / 2; ++i) rw[u][i] = rp[i];
+                    const uint2 w = reinterpret_cast<const uint2*>(a.recs)[at];
+                    lo[u] = w.x;
+                    hi[u] = w.y;
                 }
             }
+        };
+        int b = b0 + (int)(threadIdx.x / kSegLanes);
+        Seg cur = header(b), nxt = header(b + kSegGroups);
+        // Requests the next step's records into lo2/hi2, then adds the current
+        // step's.  Two buffers take turns, so no step copies registers (a copy
+        // would wait for the loads).
+        auto advance = [&](const uint32_t (&lo)[kSegStep], const uint32_t (&hi)[kSegStep], uint32_t (&lo2)[kSegStep],
+                           uint32_t (&hi2)[kSegStep]) {
+            const int left = cur.end - cur.p - ln;  // the lane's records are u * kSegLanes < left
+            // a record (qx, qy, r) is worth (qx, qy) 2^(E - r - (MB - 1)); in
+            // fixed point at 2^ex that is (qx, qy) 2^(sh0 - r)
+            const int sh0 = block_rec_exp(cur.bm) - (MB - 1) + ex;
+            // the next step: the rest of this segment, or the next block's
+            cur.p += kSegStep * kSegLanes;
+            const bool done = cur.p >= cur.end;
+            if (done) cur = nxt;
+            b += done ? kSegGroups : 0;
+            load(cur, lo2, hi2);
+            nxt = header(b + kSegGroups);
 #pragma unroll
-            for (int u = 0; u < kRunsPerThread; ++u) {
-                const uint64_t q = q0 + (uint64_t)u * kReduceThreads;
-                const uint64_t rec0 = q * kRun;
-                uint32_t key[kRun];
-                long long sx[kRun], sy[kRun];
-#pragma unroll
-                for (int i = 0; i < kRun; ++i) {
-                    uint32_t lo, hi;
-                    if constexpr (kCompact) {
-                        const uint4& l4 = rw[u][i >> 2];
-                        lo = (i & 3) == 0 ? l4.x : (i & 3) == 1 ? l4.y : (i & 3) == 2 ? l4.z : l4.w;
-                        const uint4& h4 = rw[u][2];
-                        const uint32_t hw = (i >> 1) == 0 ? h4.x : (i >> 1) == 1 ? h4.y : (i >> 1) == 2 ? h4.z : h4.w;
-                        hi = (i & 1) ? hw >> 16 : hw & 0xffffu;
-                    } else {
-                        lo = (i & 1) ? rw[u][i >> 1].z : rw[u][i >> 1].x;
-                        hi = (i & 1) ? rw[u][i >> 1].w : rw[u][i >> 1].y;
-                    }
-                    int r;
-                    long long qx, qy;
-                    decode_record<EB, MB>((uint64_t)hi << 32 | lo, key[i], r, qx, qy);
-                    const int sh = sh0 - r;
-                    const bool ok = q < q_end && rec0 + i >= r_begin && rec0 + i < r_end;
-                    sx[i] = ok ? scale_mantissa(qx, sh) : 0ll;
-                    sy[i] = ok ? scale_mantissa(qy, sh) : 0ll;
-                }
-#pragma unroll
-                for (int i = 1; i < kRun; ++i) {
-                    if (key[i] == key[i - 1]) {
-                        sx[i] += sx[i - 1];
-                        sy[i] += sy[i - 1];
-                        sx[i - 1] = 0;
-                        sy[i - 1] = 0;
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < kRun; ++i) {
-                    if (sx[i] != 0) atomicAdd(&acc[key[i]], (unsigned long long)sx[i]);
-                    if (sy[i] != 0) atomicAdd(&acc[kTileRows + key[i]], (unsigned long long)sy[i]);
+            for (int u = 0; u < kSegStep; ++u) {
+                uint32_t key;
+                int r, qx, qy;
+                decode_record<EB, MB>(lo[u], hi[u], key, r, qx, qy);
+                if (u * kSegLanes < left) {
+                    atomicAdd(&acc[key], (unsigned long long)scale_mantissa(qx, sh0 - r));
+                    atomicAdd(&acc[kTileRows + key], (unsigned long long)scale_mantissa(qy, sh0 - r));
                 }
             }
+        };
+        uint32_t lo[2][kSegStep], hi[2][kSegStep];
+        load(cur, lo[0], hi[0]);
+        while (b < b1) {
+            advance(lo[0], hi[0], lo[1], hi[1]);
+            if (b >= b1) break;
+            advance(lo[1], hi[1], lo[0], hi[0]);
         }
-        __syncthreads();
-        float2* g = reinterpret_cast<float2*>(a.g_table + o.g_off) + ((int64_t)l << o.grid.log2_table) + row0;
+    }
+    __syncthreads();
+    if (n_split > 1) {
+        unsigned long long* out =
+            a.parts + (o.part_off + o.part_base[l] + (int64_t)tt * n_split + part) * (2 * kTileRows);
         for (int i = threadIdx.x; i < n_rows; i += kReduceThreads) {
-            const long long sx = (long long)acc[i], sy = (long long)acc[kTileRows + i];
-            if (sx == 0 && sy == 0) continue;
-            const float2 v = make_float2((float)ldexp((double)sx, -ex), (float)ldexp((double)sy, -ex));
-            if (owner) {
-                float2 w = g[i];
-                w.x += v.x;
-                w.y += v.y;
-                g[i] = w;
-            } else {
-                atomicAdd(&g[i].x, v.x);
-                atomicAdd(&g[i].y, v.y);
-            }
+            out[i] = acc[i];
+            out[kTileRows + i] = acc[kTileRows + i];
         }
-        __syncthreads();
+        return;
+    }
+    float2* g = reinterpret_cast<float2*>(a.g_table + o.g_off) + ((int64_t)l << o.grid.log2_table) + row0;
+    for (int i = threadIdx.x; i < n_rows; i += kReduceThreads) {
+        const long long sx = (long long)acc[i], sy = (long long)acc[kTileRows + i];
+        if (sx == 0 && sy == 0) continue;
+        float2 w = g[i];
+        w.x += (float)ldexp((double)sx, -ex);
+        w.y += (float)ldexp((double)sy, -ex);
+        g[i] = w;
     }
 }
+
+// Tiles reduced in several ranges: the ranges' 64-bit sums added, one thread
+// per row; blockIdx.y counts the pass's split tiles.
+template <bool kMany>
+__global__ __launch_bounds__(kCombineThreads) void k_scatter_combine(ScatterArgs a)
+{
+    const int64_t ct = blockIdx.y;
+    const ScatterObj& o = sobj<kMany>(a, last_le<kMany>(a, ct, [](const ScatterObj& v) { return v.ctile_off; }));
+    const int cl = (int)(ct - o.ctile_off);
+    const int l = level_of(o.ctile_base, o.grid.n_levels, cl);
+    const int n_split = o.split[l];
+    const int tt = cl - o.ctile_base[l];
+    const int64_t row0 = (int64_t)tt << kTileBits;
+    const int i = (int)(blockIdx.x * kCombineThreads + threadIdx.x);
+    if (i >= (int)min((int64_t)kTileRows, o.level_rows[l] - row0)) return;
+    const unsigned long long* in = a.parts + (o.part_off + o.part_base[l] + (int64_t)tt * n_split) * (2 * kTileRows) + i;
+    unsigned long long sx = 0, sy = 0;
+#pragma unroll 4
+    for (int k = 0; k < n_split; ++k) {
+        sx += in[(int64_t)k * 2 * kTileRows];
+        sy += in[(int64_t)k * 2 * kTileRows + kTileRows];
+    }
+    if (sx == 0 && sy == 0) return;
+    const int ex = a.level_exp[o.lev_off + l];
+    float2* g = reinterpret_cast<float2*>(a.g_table + o.g_off) + ((int64_t)l << o.grid.log2_table) + row0;
+    float2 w = g[i];
+    w.x += (float)ldexp((double)(long long)sx, -ex);
+    w.y += (float)ldexp((double)(long long)sy, -ex);
+    g[i] = w;
+}
+
+template <bool kMany, bool kCompact>
+hipError_t place_impl(const ScatterArgs& a, hipStream_t s)
+{
+    const size_t lds = place_lds_bytes(a.tiles_max, kCompact);
+    hipLaunchKernelGGL((k_scatter_place<kMany, kCompact>), dim3((uint32_t)a.n_items), dim3(kPlaceThreads), lds, s, a);
+    return hipGetLastError();
+}
+static_assert(place_lds_bytes(kMaxTilesPerLevel, false) <= 65536, "place LDS");
 
 template <bool kMany>
 hipError_t scatter_phase_impl(const ScatterArgs& a, int phase, hipStream_t s)
 {
     switch (phase) {
-        case 0:
-            if (a.fwd_counts)
-                hipLaunchKernelGGL(k_scatter_dymax<kMany>, dim3((uint32_t)((a.n_items + kDymaxItems - 1) / kDymaxItems)),
-                                   dim3(kPlaceThreads), 0, s, a);
-            else
-                hipLaunchKernelGGL(k_scatter_count<kMany>, dim3((uint32_t)a.n_items), dim3(kPlaceThreads), 0, s, a);
-            break;
+        case 0: return a.compact ? place_impl<kMany, true>(a, s) : place_impl<kMany, false>(a, s);
         case 1:
-            hipLaunchKernelGGL(k_scatter_level_max<kMany>, dim3((uint32_t)a.n_levels_total), dim3(kLevelMaxThreads), 0, s,
-                               a);
+            hipLaunchKernelGGL(k_scatter_level<kMany>, dim3((uint32_t)a.n_levels_total), dim3(kLevelThreads), 0, s, a);
             break;
         case 2:
-            hipLaunchKernelGGL(k_scatter_scan_blocks<kMany>, dim3((uint32_t)a.n_tiles), dim3(kScanThreads), 0, s, a);
+            if (a.compact)
+                hipLaunchKernelGGL((k_scatter_reduce<kMany, true>), dim3((uint32_t)a.n_ritems), dim3(kReduceThreads), 0,
+                                   s, a);
+            else
+                hipLaunchKernelGGL((k_scatter_reduce<kMany, false>), dim3((uint32_t)a.n_ritems), dim3(kReduceThreads), 0,
+                                   s, a);
             break;
         case 3:
-            hipLaunchKernelGGL(k_scatter_scan_tiles<kMany>, dim3(1), dim3(kScanThreads), 0, s, a);
+            hipLaunchKernelGGL(k_scatter_combine<kMany>, dim3(kTileRows / kCombineThreads, (uint32_t)a.n_ctiles),
+                               dim3(kCombineThreads), 0, s, a);
             break;
-        case 4: {
-            const bool narrow = a.tiles_max <= 256;
-            const size_t place_lds = place_lds_bytes(a.tiles_max, narrow ? 1 : 2);
-            const void* fn = narrow ? (const void*)k_scatter_place<kMany, uint8_t> : (const void*)k_scatter_place<kMany, uint16_t>;
-            hipError_t e;
-            if (place_lds > 65536 &&
-                (e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)place_lds)) != hipSuccess)
-                return e;
-            if (narrow)
-                hipLaunchKernelGGL((k_scatter_place<kMany, uint8_t>), dim3((uint32_t)a.n_items), dim3(kPlaceThreads),
-                                   place_lds, s, a);
-            else
-                hipLaunchKernelGGL((k_scatter_place<kMany, uint16_t>), dim3((uint32_t)a.n_items), dim3(kPlaceThreads),
-                                   place_lds, s, a);
-            break;
-        }
-        case 5:
-            if (a.compact)
-                hipLaunchKernelGGL((k_scatter_reduce<kMany, true>), dim3((uint32_t)a.reduce_blocks),
-                                   dim3(kReduceThreads), 0, s, a);
-            else
-                hipLaunchKernelGGL((k_scatter_reduce<kMany, false>), dim3((uint32_t)a.reduce_blocks),
-                                   dim3(kReduceThreads), 0, s, a);
-            break;
-        default:
-            return hipErrorInvalidValue;
+        default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
@@ -816,12 +572,38 @@ ScatterObj scatter_obj(const GridInfo& g, int64_t n_s)
 }
 
 int64_t scatter_items(const ScatterObj& o) { return (int64_t)o.grid.n_levels * o.n_blocks; }
+int64_t scatter_records(const ScatterObj& o) { return scatter_items(o) * kRecordsPerBlock; }
+int64_t scatter_segs(const ScatterObj& o) { return (int64_t)o.n_blocks * (o.n_tiles + o.grid.n_levels); }
 
-// A multiple of kRun: the reduce reads whole aligned runs.
-int64_t scatter_records(const ScatterObj& o) { return o.n_s * o.grid.n_levels * 8; }
-static_assert(8 % kRun == 0, "record arrays must hold whole runs");
+int64_t scatter_target(int64_t records)
+{
+    const int64_t t = records / kReduceItems;
+    return t > kReduceMinRecords ? t : kReduceMinRecords;
+}
 
-int scatter_max_tiles_per_level() { return kMaxTilesPerLevel; }
+// Every tile of a level is estimated at an even share of the level's records.
+void scatter_split(ScatterObj& o, int64_t target)
+{
+    o.n_ritems = o.n_ctiles = 0;
+    o.n_parts = 0;
+    for (int l = 0; l < o.grid.n_levels; ++l) {
+        const int64_t per_tile = (int64_t)o.n_blocks * kRecordsPerBlock / o.tiles[l];
+        int64_t k = (per_tile + target - 1) / target;
+        k = k < 1 ? 1 : k > o.n_blocks ? o.n_blocks : k;
+        if (k < 1) k = 1;
+        o.split[l] = (int32_t)k;
+        o.ritem_base[l] = o.n_ritems;
+        o.n_ritems += (int32_t)(o.tiles[l] * k);
+        o.part_base[l] = o.n_parts;
+        o.ctile_base[l] = o.n_ctiles;
+        if (k > 1) {
+            o.n_parts += (int32_t)(o.tiles[l] * k);
+            o.n_ctiles += o.tiles[l];
+        }
+    }
+}
+
+size_t scatter_part_bytes() { return sizeof(unsigned long long) * 2 * kTileRows; }
 
 int scatter_tiles_max(const ScatterObj& o)
 {
@@ -830,13 +612,12 @@ int scatter_tiles_max(const ScatterObj& o)
     return m;
 }
 
-const char* const kScatterPhaseNames[kScatterPhases] = {"k_scatter_count",      "k_scatter_level_max",
-                                                        "k_scatter_scan_blocks", "k_scatter_scan_tiles",
-                                                        "k_scatter_place",      "k_scatter_reduce"};
+const char* const kScatterPhaseNames[kScatterPhases] = {"k_scatter_place", "k_scatter_level", "k_scatter_reduce",
+                                                        "k_scatter_combine"};
 
 hipError_t launch_scatter_phase(const ScatterArgs& a, int phase, hipStream_t s)
 {
-    if (a.n_items == 0) return hipSuccess;
+    if (a.n_items == 0 || (phase == 3 && a.n_ctiles == 0)) return hipSuccess;
     return a.n_obj == 1 && a.objs == nullptr ? scatter_phase_impl<false>(a, phase, s)
                                              : scatter_phase_impl<true>(a, phase, s);
 }
