@@ -26,8 +26,13 @@ struct RowPair;
 template <>
 struct RowPair<float2> {
     typedef float4 type;
+    struct __attribute__((packed, aligned(8))) any {  // two rows at any row's address
+        float x, y, z, w;
+    };
     __device__ static float2 lo(float4 v) { return make_float2(v.x, v.y); }
     __device__ static float2 hi(float4 v) { return make_float2(v.z, v.w); }
+    __device__ static float2 lo(const any& v) { return make_float2(v.x, v.y); }
+    __device__ static float2 hi(const any& v) { return make_float2(v.z, v.w); }
     __device__ static float2 row(__amdgpu_buffer_rsrc_t r, uint32_t off)
     {
         const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
@@ -37,6 +42,11 @@ struct RowPair<float2> {
 template <>
 struct RowPair<half2_t> {
     typedef half4_t type;
+    struct __attribute__((packed, aligned(4))) any {
+        half2_t a, b;
+    };
+    __device__ static float2 lo(const any& v) { return to_f2(v.a); }
+    __device__ static float2 hi(const any& v) { return to_f2(v.b); }
     __device__ static float2 lo(half4_t v) { return make_float2((float)v[0], (float)v[1]); }
     __device__ static float2 hi(half4_t v) { return make_float2((float)v[2], (float)v[3]); }
     __device__ static float2 row(__amdgpu_buffer_rsrc_t r, uint32_t off)
@@ -118,22 +128,47 @@ __device__ __forceinline__ float2 gather_blend_pairs(const Row* __restrict__ lev
     return acc;
 }
 
-// Hashed levels of at least 2^kPairMinLog2 rows take the paired gather; the
-// others (dense levels, small tables), whose corner rows mostly hit in cache
-// anyway, take the plain one.  The choice is the same for the whole block.
-// Measured on gfx950 (single object, 65536 rays x 64 samples, 16 levels of
-// 2^19 rows): 1.11 ms paired against 1.24 ms plain.  The batched encode keeps
-// the plain gather: on 24 objects with tables of 2^14..2^19 rows the paired
-// one was slower at every threshold tried (3.84 ms from 2^17, 3.98 ms from
-// 2^14, against 3.69 ms plain).
+// Dense levels: the rows of corners 2p and 2p + 1 follow each other, so each
+// pair is one two-row load at the first row's address.
+template <typename Row>
+__device__ __forceinline__ float2 gather_blend_dense(const Row* __restrict__ level_table, const Corners& c)
+{
+    typedef RowPair<Row> RP;
+    typename RP::any v[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) v[p] = *reinterpret_cast<const typename RP::any*>(level_table + c.row[2 * p]);
+    float2 acc = make_float2(0.0f, 0.0f);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const float2 f0 = RP::lo(v[p]), f1 = RP::hi(v[p]);
+        acc.x = fmaf(c.w[2 * p], f0.x, acc.x);
+        acc.y = fmaf(c.w[2 * p], f0.y, acc.y);
+        acc.x = fmaf(c.w[2 * p + 1], f1.x, acc.x);
+        acc.y = fmaf(c.w[2 * p + 1], f1.y, acc.y);
+    }
+    return acc;
+}
+
+// The encoding is bound by the lines the L1 caches fetch: a wave's gather from
+// 64 lines takes 150 cycles whether 4, 8 or 16 bytes are read from each (64
+// bytes a cycle and CU), a gather that hits 40.  Hashed levels fetch four lines
+// a sample however they are read (x and x + 1 lie in one line 15 times out of
+// 16); reading them in pairs saves the hits.  Tables of fewer than
+// 2^kPairMinLog2 rows hit more, and the pairs' selects cost more than they save.
+// Measured on gfx950: dense levels in pairs 1.19 -> 1.17 ms (65536 rays x 64
+// samples, 16 levels of 2^19 rows), 11.89 -> 11.36 ms (48 objects, FP16 tables);
+// hashed levels in pairs from 2^10 rows on instead of 2^17: 0.282 against
+// 0.260 ms for a view over 2^15 rows.  The batch (kPairs false) reads hashed
+// levels plainly: in pairs from 2^17 rows on 11.38 against 11.36 ms, 24
+// objects 3.25 against 3.23 ms.
 constexpr int kPairMinLog2 = 17;
 
-template <typename Row>
+template <bool kPairs, typename Row>
 __device__ __forceinline__ float2 gather_blend(const Row* __restrict__ level_table, const GridInfo& g, int l,
                                                const Corners& c)
 {
-    const bool dense = (g.dense_mask >> l) & 1u;
-    if (!dense && g.log2_table >= kPairMinLog2) return gather_blend_pairs(level_table, 1u << g.log2_table, c);
+    if ((g.dense_mask >> l) & 1u) return gather_blend_dense(level_table, c);
+    if (kPairs && g.log2_table >= kPairMinLog2) return gather_blend_pairs(level_table, 1u << g.log2_table, c);
     return gather_blend_rows(level_table, c);
 }
 
@@ -152,7 +187,7 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_samples(GridInfo g, const 
     level_corners(g, l, sample_coord(ts, ro[3], ro[0]), sample_coord(ts, ro[4], ro[1]),
                   sample_coord(ts, ro[5], ro[2]), c);
     const Row* lt = table + ((int64_t)l << g.log2_table);
-    y[(int64_t)l * n_s + s] = gather_blend(lt, g, l, c);
+    y[(int64_t)l * n_s + s] = gather_blend<true>(lt, g, l, c);
 }
 
 // Batched: one block per item (object, level, block of kScatterBlockSamples
@@ -192,9 +227,9 @@ __global__ __launch_bounds__(kScatterBlockSamples) void k_encode_batch(const Obj
     const int64_t row0 = (int64_t)l << o.grid.log2_table;  // rows of float2 / half2
     float2 v;
     if (o.table_dtype == PRENOM_F16)
-        v = gather_blend_rows(params_f16 + o.param_off / 2 + row0, c);
+        v = gather_blend<false>(params_f16 + o.param_off / 2 + row0, o.grid, l, c);
     else
-        v = gather_blend_rows(reinterpret_cast<const float2*>(params + o.param_off) + row0, c);
+        v = gather_blend<false>(reinterpret_cast<const float2*>(params + o.param_off) + row0, o.grid, l, c);
     y[o.y_off / 2 + (int64_t)l * n_s + s] = v;
 }
 
@@ -211,7 +246,7 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_points(GridInfo g, const f
     level_corners(g, l, fminf(fmaxf(p[0], 0.0f), 1.0f), fminf(fmaxf(p[1], 0.0f), 1.0f),
                   fminf(fmaxf(p[2], 0.0f), 1.0f), c);
     const float2* lt = table + ((int64_t)l << g.log2_table);
-    y[(int64_t)l * n + i] = gather_blend(lt, g, l, c);
+    y[(int64_t)l * n + i] = gather_blend<true>(lt, g, l, c);
     if (corner_idx) {
         int32_t* ci = corner_idx + ((int64_t)l * n + i) * 8;
 #pragma unroll
@@ -235,7 +270,7 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_grid(GridInfo g, const Row
     Corners c;
     level_corners(g, l, (float)((double)i / d), (float)((double)j / d), (float)((double)k / d), c);
     const Row* lt = table + ((int64_t)l << g.log2_table);
-    y[(int64_t)l * cnt + q] = gather_blend(lt, g, l, c);
+    y[(int64_t)l * cnt + q] = gather_blend<true>(lt, g, l, c);
 }
 
 // out[p] = sigma of head output p (sc rows are (sigma, r, g, b)).
