@@ -357,11 +357,11 @@ typedef struct prenom_object {
 } prenom_object;
 
 /* Tile shape of the batched MLP launches for one MLP shape (chosen by an
- * autotuner; shapes without an entry use defaults).  fwd_tiles: 16-sample
- * tiles per forward block, a multiple of 4 in [4, 4096]; bwd_tiles: per
- * backward block (each writes one partial weight gradient and the maxima of
- * |dy| of its 512-sample blocks, which the table gradient's fixed-point scale
- * needs), a multiple of 32 in [32, 1024]. */
+ * autotuner; shapes without an entry use defaults).  fwd_tiles: at most so many
+ * 16-sample tiles per forward block, a multiple of 4 in [4, 4096]; bwd_tiles:
+ * per backward block (each writes one partial weight gradient), a multiple of
+ * 32 in [32, 1024].  A launch whose objects would leave CUs idle with these
+ * takes shorter runs. */
 typedef struct prenom_mlp_tiles {
     int32_t in_dim, width, hidden, dtype;
     int32_t fwd_tiles, bwd_tiles;
