@@ -527,6 +527,7 @@ prenom_status prenom_render_bwd(const prenom_model* model, const prenom_render_c
                                                  model->grads + table_params(a), s));
         ScatterArgs sa{};
         sa.S = S;
+        sa.inv_S = 1.0f / (float)S;
         sa.n_obj = 1;
         sa.one = plan;
         sa.objs = nullptr;

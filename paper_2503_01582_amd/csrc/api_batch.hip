@@ -393,6 +393,7 @@ ScatterArgs scatter_args(const Plan& p, const ScatterGroup& g, void* ws, const f
 {
     ScatterArgs sa{};
     sa.S = p.S;
+    sa.inv_S = 1.0f / (float)p.S;
     sa.n_obj = g.count;
     sa.objs = at<ScatterObj>(ws, p.o_sc_pass) + g.first;
     sa.tiles_max = p.tiles_max;

@@ -46,10 +46,11 @@ __device__ __forceinline__ void lattice_cell(float x, int N, uint32_t& c, float&
     f = fmaf(x, Nf, -cf);
 }
 
-// The 8 cell corners of x on level l: table rows and trilinear weights
-// (corner e = (e & 1, e >> 1 & 1, e >> 2 & 1)).  Used by the forward encoding
-// and by both passes of the scatter, so all of them agree bit for bit.
+// The 8 cell corners of x on level l: the cell, table rows and trilinear
+// weights (corner e = (e & 1, e >> 1 & 1, e >> 2 & 1)).  Used by the forward
+// encoding and by the scatter, so they agree bit for bit.
 struct Corners {
+    uint32_t cell[3];
     uint32_t row[8];
     float w[8];
 };
@@ -60,37 +61,50 @@ __device__ __forceinline__ float sample_coord(float t, float d, float o)
     return fminf(fmaxf(fmaf(t, d, o), 0.0f), 1.0f);
 }
 
+template <bool kBranch = false>
 __device__ __forceinline__ void level_corners(const GridInfo& g, int l, float x0, float x1, float x2, Corners& c)
 {
     const int N = g.res[l];
     const bool dense = (g.dense_mask >> l) & 1u;
-    const uint32_t side = (uint32_t)N + 1u;
-    uint32_t cx, cy, cz;
-    float fx, fy, fz;
-    lattice_cell(x0, N, cx, fx);
-    lattice_cell(x1, N, cy, fy);
-    lattice_cell(x2, N, cz, fz);
+    float f[3];
+    lattice_cell(x0, N, c.cell[0], f[0]);
+    lattice_cell(x1, N, c.cell[1], f[1]);
+    lattice_cell(x2, N, c.cell[2], f[2]);
     // Rows of the 8 corners from two products per level (corner_row of each
     // corner, strength-reduced): (c + 1) P = c P + P modulo 2^32 for the hash,
     // and the 1:1 row of a corner is the cell's row plus 1, side or side^2.
-    uint32_t r0 = 0, ry = 0, rz = 0, hy[2] = {0, 0}, hz[2] = {0, 0};
-    if (dense) {
-        r0 = cx + side * (cy + side * cz);
-        ry = side;
-        rz = side * side;
-    } else {
-        hy[0] = cy * 2654435761u;
-        hy[1] = hy[0] + 2654435761u;
-        hz[0] = cz * 805459861u;
-        hz[1] = hz[0] + 805459861u;
-    }
-    const uint32_t mask = (1u << g.log2_table) - 1u;
+    // kBranch: one uniform branch instead of a select per corner (fewer vector
+    // instructions, which bind the scatter; the encoding, bound by its gathers,
+    // is faster without: 11.4 against 12.2 ms on 48 objects).
+    const uint32_t mask = (1u << g.log2_table) - 1u, side = (uint32_t)N + 1u;
+    auto dense_row = [&](uint32_t r0, int e) { return r0 + (e & 1) + (e & 2 ? side : 0u) + (e & 4 ? side * side : 0u); };
+    auto hash_row = [&](uint32_t hy, uint32_t hz, int e) {
+        return ((c.cell[0] + (e & 1)) ^ (e & 2 ? hy + 2654435761u : hy) ^ (e & 4 ? hz + 805459861u : hz)) & mask;
+    };
+    if constexpr (kBranch) {
+        if (dense) {
+            const uint32_t r0 = c.cell[0] + side * (c.cell[1] + side * c.cell[2]);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const uint32_t ex = e & 1, ey = (e >> 1) & 1, ez = (e >> 2) & 1;
-        c.row[e] = dense ? r0 + ex + (ey ? ry : 0u) + (ez ? rz : 0u) : ((cx + ex) ^ hy[ey] ^ hz[ez]) & mask;
-        c.w[e] = (ex ? fx : 1.0f - fx) * (ey ? fy : 1.0f - fy) * (ez ? fz : 1.0f - fz);
+            for (int e = 0; e < 8; ++e) c.row[e] = dense_row(r0, e);
+        } else {
+            const uint32_t hy = c.cell[1] * 2654435761u, hz = c.cell[2] * 805459861u;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) c.row[e] = hash_row(hy, hz, e);
+        }
+    } else {
+        uint32_t r0 = 0, hy = 0, hz = 0;
+        if (dense) {
+            r0 = c.cell[0] + side * (c.cell[1] + side * c.cell[2]);
+        } else {
+            hy = c.cell[1] * 2654435761u;
+            hz = c.cell[2] * 805459861u;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) c.row[e] = dense ? dense_row(r0, e) : hash_row(hy, hz, e);
     }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        c.w[e] = (e & 1 ? f[0] : 1.0f - f[0]) * (e & 2 ? f[1] : 1.0f - f[1]) * (e & 4 ? f[2] : 1.0f - f[2]);
 }
 
 // ------------------------------------------------------------------ table tiles
@@ -108,8 +122,8 @@ constexpr int kScatterBlockSamples = 512;
 // up to 4 hashed or 16 dense, 15.7 ms up to 2).
 constexpr int kAggregateTiles = 2;
 
-// Adds 1 to hist[tile] for every active lane and returns the lane's rank
-// among the additions to that tile.  Lanes of the wave that share the tile of
+// Adds `unit` to hist[tile] for every active lane and returns the lane's rank
+// among the additions to that tile, in units.  Lanes of the wave that share the tile of
 // the first remaining lane are combined into one LDS atomic issued by that
 // lane (same-address atomics of one instruction would otherwise serialise);
 // after kAggregateRounds such rounds the lanes left use plain LDS atomics, so
@@ -118,7 +132,7 @@ constexpr int kAggregateTiles = 2;
 // way a lane takes.
 constexpr int kAggregateRounds = 2;
 
-__device__ __forceinline__ uint32_t wave_aggregated_add(uint32_t* hist, uint32_t tile)
+__device__ __forceinline__ uint32_t wave_aggregated_add(uint32_t* hist, uint32_t tile, uint32_t unit)
 {
     const int lane = threadIdx.x & 63;
     const uint64_t lane_lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -132,15 +146,15 @@ __device__ __forceinline__ uint32_t wave_aggregated_add(uint32_t* hist, uint32_t
         const uint32_t lt = __shfl(tile, leader);
         const uint64_t mask = __ballot(tile == lt);
         uint32_t base = 0;
-        if (lane == leader) base = atomicAdd(&hist[lt], (uint32_t)__popcll(mask));
+        if (lane == leader) base = atomicAdd(&hist[lt], unit * (uint32_t)__popcll(mask));
         base = __shfl(base, leader);
         if (tile == lt) {
-            rank = base + (uint32_t)__popcll(mask & lane_lt);
+            rank = base + unit * (uint32_t)__popcll(mask & lane_lt);
             placed = true;
         }
         remaining &= ~mask;
     }
-    if (!placed) rank = atomicAdd(&hist[tile], 1u);
+    if (!placed) rank = atomicAdd(&hist[tile], unit);
     return rank;
 }
 
@@ -159,32 +173,25 @@ __device__ __forceinline__ float dpp_f32(float v)
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xf, 0xf, true));
 }
 
-// Merging repeated corners.  Consecutive samples of a ray often share a cell
-// on the coarser levels, so the same corner row repeats on neighbouring
-// lanes; such a run becomes one record (the sum of its contributions).  Runs
-// stay inside groups of 8 lanes.  Bit e of the result is set when the lane's
-// corner e starts a run: the lane has a contribution and is the first of its
-// group of 8, or lane - 1 has none, or lane - 1's corner e has another row.
-// Every lane of the wave must call it.
-__device__ __forceinline__ uint32_t run_heads(const Corners& c, bool has)
+// Merging repeated cells.  Consecutive samples of a ray often share a cell on
+// the coarser levels, so all eight corner rows repeat on neighbouring lanes;
+// such a run becomes one record per corner (the sum of its contributions).
+// Runs stay inside groups of 8 lanes.  True when the lane starts a run: it has
+// a contribution and is the first of its group of 8, or lane - 1 has none or
+// another cell.  Every lane of the wave must call it.
+__device__ __forceinline__ bool run_head(const Corners& c, bool has)
 {
-    const uint64_t B = __ballot(has);
-    const int lane = threadIdx.x & 63;
-    const bool first = (lane & 7) == 0 || ((B << 1 >> lane) & 1ull) == 0;
-    uint32_t m = 0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const uint32_t prev = dpp_u32<0x111>(c.row[e]);
-        if (has && (first || prev != c.row[e])) m |= 1u << e;
-    }
-    return m;
+    const uint32_t x = has ? c.cell[0] : 0xffffffffu;  // no lattice coordinate is as large
+    const uint32_t other = (dpp_u32<0x111>(x) ^ x) | (dpp_u32<0x111>(c.cell[1]) ^ c.cell[1]) |
+                           (dpp_u32<0x111>(c.cell[2]) ^ c.cell[2]);
+    return has && ((threadIdx.x & 7) == 0 || other != 0u);
 }
 
-// Per lane that starts a run (boundary set): the sum of v over its run (the
+// Per lane that starts a run (boundary set): the sums of v over its run (the
 // lane and the following lanes of its group of 8 up to the next boundary); a
 // segmented suffix scan in three steps, in a fixed order.  Lanes without a
 // contribution pass v = 0 and boundary = true.  Every lane of the wave must call it.
-__device__ __forceinline__ float2 run_sum(float2 v, bool boundary)
+__device__ __forceinline__ void run_sum(float2 (&v)[8], bool boundary)
 {
     const int g = threadIdx.x & 7;
     const int lane = threadIdx.x & 63;
@@ -193,15 +200,24 @@ __device__ __forceinline__ float2 run_sum(float2 v, bool boundary)
     const bool c1 = g + 1 < 8 && ((B >> (lane + 1)) & 1ull) == 0;
     const bool c2 = g + 2 < 8 && ((B >> (lane + 1)) & 3ull) == 0;
     const bool c4 = g + 4 < 8 && ((B >> (lane + 1)) & 15ull) == 0;
-    float ox = dpp_f32<0x101>(v.x), oy = dpp_f32<0x101>(v.y);
-    if (c1) { v.x += ox; v.y += oy; }
-    ox = dpp_f32<0x102>(v.x);
-    oy = dpp_f32<0x102>(v.y);
-    if (c2) { v.x += ox; v.y += oy; }
-    ox = dpp_f32<0x104>(v.x);
-    oy = dpp_f32<0x104>(v.y);
-    if (c4) { v.x += ox; v.y += oy; }
-    return v;
+    // A product with 0 or 1, its addition and the lane exchange are one
+    // instruction (v_fmac with a DPP operand), a third of what an exchange, a
+    // select and an addition take.  An exchanged operand may be read two
+    // instructions after it was written: the 16 values of a step lie between.
+    const float m1 = c1 ? 1.0f : 0.0f, m2 = c2 ? 1.0f : 0.0f, m4 = c4 ? 1.0f : 0.0f;
+#define PRENOM_RUN1(i, m, n) "v_fmac_f32_dpp %" #i ", %" #i ", %" #m " row_shl:" #n " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"
+#define PRENOM_RUN16(m, n)                                                                                    \
+    PRENOM_RUN1(0, m, n) PRENOM_RUN1(1, m, n) PRENOM_RUN1(2, m, n) PRENOM_RUN1(3, m, n) PRENOM_RUN1(4, m, n)   \
+    PRENOM_RUN1(5, m, n) PRENOM_RUN1(6, m, n) PRENOM_RUN1(7, m, n) PRENOM_RUN1(8, m, n) PRENOM_RUN1(9, m, n)   \
+    PRENOM_RUN1(10, m, n) PRENOM_RUN1(11, m, n) PRENOM_RUN1(12, m, n) PRENOM_RUN1(13, m, n)                    \
+    PRENOM_RUN1(14, m, n) PRENOM_RUN1(15, m, n)
+    asm("s_nop 4\n\t" PRENOM_RUN16(16, 1) PRENOM_RUN16(17, 2) PRENOM_RUN16(18, 4) "s_nop 1"
+        : "+v"(v[0].x), "+v"(v[0].y), "+v"(v[1].x), "+v"(v[1].y), "+v"(v[2].x), "+v"(v[2].y), "+v"(v[3].x),
+          "+v"(v[3].y), "+v"(v[4].x), "+v"(v[4].y), "+v"(v[5].x), "+v"(v[5].y), "+v"(v[6].x), "+v"(v[6].y),
+          "+v"(v[7].x), "+v"(v[7].y)
+        : "v"(m1), "v"(m2), "v"(m4));
+#undef PRENOM_RUN16
+#undef PRENOM_RUN1
 }
 
 // ------------------------------------------------------------------ batches
@@ -322,9 +338,11 @@ size_t scatter_part_bytes();                     // one partial sum
 
 struct ScatterArgs {
     int32_t S;
+    float inv_S;                // 1 / S
     int32_t n_obj;              // 1: `one` holds the object; else `objs` (device) holds n_obj of them
     int32_t tiles_max;          // max tiles of one level over all objects
     int32_t n_levels_total;     // (object, level) pairs
+    int32_t pad_;
     int64_t n_items;            // (object, level, sample block) items
     int64_t n_ritems;           // reduce items
     int64_t n_ctiles;           // tiles reduced in several ranges

@@ -69,8 +69,8 @@ constexpr int64_t kReduceMinRecords = 1 << 15;
 // A record holds the row within the tile (bits 0-12), an exponent offset r
 // (EB bits) and the two's-complement mantissas qx, qy (MB bits each); its
 // value is (qx, qy) * 2^(E - r - (MB - 1)), E being the record exponent of
-// its item (level, sample block), and a record whose larger feature lies below
-// 2^(E - 2^EB - 1) (r beyond EB bits) is dropped.  Two formats:
+// its item (level, sample block).  A record whose larger feature lies below
+// 2^(E - 2^EB) has the largest r and fewer significant bits.  Two formats:
 //   full:    EB = 7, MB = 22, one 64-bit word (21 significant bits);
 //   compact: EB = 5, MB = 15, 48 bits kept as a 32-bit word (bits 0-31) in
 //            one array and a 16-bit word (bits 32-47) in another (14
@@ -84,36 +84,52 @@ static_assert(kTileBits + kRecExpBits + 2 * kRecMantBits == 64, "record fields f
 
 // Record exponent E of a block whose largest |dy| is bm: a record sums at most
 // 8 contributions w dy with 0 <= w <= 1, so |record| <= 8 bm < 2^(E - 1).
+// Held at 2^kExpFloor, so that every scale stays a normal number.
+constexpr int kExpFloor = -100;
 __device__ __forceinline__ int block_rec_exp(float bm)
 {
     int e = 0;
     frexpf(bm, &e);  // bm < 2^e
-    return e + 4;
+    return max(e + 4, kExpFloor);
+}
+
+// max(|x|, |y|) in one instruction (fmaxf would first quiet both operands).
+__device__ __forceinline__ float max_abs(float x, float y)
+{
+    float m;
+    asm("v_max_f32_e64 %0, |%1|, |%2|" : "=v"(m) : "v"(x), "v"(y));
+    return m;
+}
+
+// min(max(v, 0), hi) for hi >= 0 in one instruction.
+__device__ __forceinline__ int clamp0(int v, int hi)
+{
+    int r;
+    asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(v), "v"(hi));
+    return r;
 }
 
 // Words of the record (lo: bits 0-31, hi: the rest).  The mantissas are
 // rounded to nearest by adding 1.5 * 2^23 (the sum's unit in the last place is
 // 1, its low bits the two's complement of the integer); the larger one can
 // round up to 2^(MB-1), one past the field: it is held at 2^(MB-1) - 1 (an
-// error of one unit in its last place).  Features below 2^-105 are scaled as
-// if they were that large, so the scale stays a normal number.
+// error of one unit in its last place).  r_max: the largest exponent offset,
+// by the field and by kExpFloor; a smaller record keeps it and fewer bits.
 template <int EB, int MB>
-__device__ __forceinline__ void encode_record(float2 v, int E, uint32_t row, uint32_t& lo, uint32_t& hi)
+__device__ __forceinline__ void encode_record(float2 v, int E, int r_max, uint32_t row, uint32_t& lo, uint32_t& hi)
 {
     int k = 0;
-    frexpf(fmaxf(fabsf(v.x), fabsf(v.y)), &k);  // 2^(k-1) <= larger feature < 2^k
-    k = max(k, MB - 1 - 126);
-    const float scale = __uint_as_float((uint32_t)(MB - 1 - k + 127) << 23);
+    frexpf(max_abs(v.x, v.y), &k);  // 2^(k-1) <= larger feature < 2^k
+    const uint32_t r = (uint32_t)clamp0(E - k, r_max);  // (a zero record has k = 0)
+    const float scale = __uint_as_float((r << 23) + ((uint32_t)(MB - 1 + 127 - E) << 23));  // 2^(MB - 1 - E + r)
     constexpr float kMagic = 12582912.0f, kMax = (float)((1u << (MB - 1)) - 1u);
-    const uint32_t bx = __float_as_uint(fminf(fmaxf(fmaf(v.x, scale, kMagic), kMagic - kMax), kMagic + kMax));
-    const uint32_t by = __float_as_uint(fminf(fmaxf(fmaf(v.y, scale, kMagic), kMagic - kMax), kMagic + kMax));
-    const uint32_t r = (uint32_t)(E - k);
+    const uint32_t bx = __float_as_uint(__builtin_amdgcn_fmed3f(fmaf(v.x, scale, kMagic), kMagic - kMax, kMagic + kMax));
+    const uint32_t by = __float_as_uint(__builtin_amdgcn_fmed3f(fmaf(v.y, scale, kMagic), kMagic - kMax, kMagic + kMax));
     constexpr int kX = kTileBits + EB;      // first bit of qx
     constexpr int kXl = 32 - kX;            // its bits in the low word
     constexpr uint32_t kXh = (1u << (MB - kXl)) - 1u;
-    const bool ok = r < (1u << EB);
-    lo = ok ? (bx << kX) | (r << kTileBits) | row : row;
-    hi = ok ? ((bx >> kXl) & kXh) | (by << (MB - kXl)) : 0u;
+    lo = (bx << kX) | (r << kTileBits) | row;
+    hi = ((bx >> kXl) & kXh) | (by << (MB - kXl));
 }
 
 // Fields of a record's words: row key, exponent offset, mantissas.
@@ -193,12 +209,12 @@ template <bool kMany, bool kCompact>
 __global__ __launch_bounds__(kPlaceThreads) void k_scatter_place(ScatterArgs a)
 {
     constexpr int EB = kCompact ? kRecExpBitsC : kRecExpBits, MB = kCompact ? kRecMantBitsC : kRecMantBits;
-    constexpr int kRows = kPlaceThreads / 16;  // 16-lane DPP rows per workgroup
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ float wmax[kRows];
-    uint64_t* s_rec = reinterpret_cast<uint64_t*>(smem);  // full records
-    uint32_t* s_lo = reinterpret_cast<uint32_t*>(smem);   // compact records: low words, then high words
-    uint16_t* s_hi = reinterpret_cast<uint16_t*>(s_lo + kRecordsPerBlock);
+    __shared__ uint32_t s_max;
+    // full records; or compact ones: low words, then high words
+    const uint64_t* s_rec = reinterpret_cast<const uint64_t*>(smem);
+    const uint32_t* s_lo = reinterpret_cast<const uint32_t*>(smem);
+    const uint16_t* s_hi = reinterpret_cast<const uint16_t*>(s_lo + kRecordsPerBlock);
     uint32_t* hist = reinterpret_cast<uint32_t*>(smem + kRecordsPerBlock * (kCompact ? 6 : 8));
     const int64_t item = blockIdx.x;
     const ScatterObj& o = sobj<kMany>(a, last_le<kMany>(a, item, [](const ScatterObj& v) { return v.item_off; }));
@@ -206,56 +222,69 @@ __global__ __launch_bounds__(kPlaceThreads) void k_scatter_place(ScatterArgs a)
     const int l = (int)(rem / (uint32_t)o.n_blocks);
     const int bx = (int)(rem - (uint32_t)l * (uint32_t)o.n_blocks);
     const int nt = o.tiles[l];
-    // The gradient, t and the ray are loaded together and the corners computed
-    // whatever dy is, so the loads are not serialised behind a test.
-    const int64_t s = (int64_t)bx * kSamplesPerBlock + threadIdx.x;
-    const bool in = s < o.n_s;
-    const int64_t sl = in ? s : o.n_s - 1;
-    const int64_t gs = o.s_begin + sl;  // < 2^29 samples
-    const float* ro = a.ray_obj + 6 * (int64_t)((uint32_t)gs / (uint32_t)a.S);
-    const float2 d = a.dy[o.dy_off + (int64_t)l * o.n_s + sl];
-    const float ts = a.t[gs];
+    // Samples of the block, its first ray and the position of its first sample
+    // on that ray; a lane's ray follows from its distance, below 2^10, by a
+    // product with 1 / S (exact: the quotients' fractions stay 1 / (2 S) away
+    // from an integer).  The gradient, t and the ray are loaded together and
+    // the corners computed whatever dy is, so the loads are not serialised
+    // behind a test.
+    const int64_t s0 = (int64_t)bx * kSamplesPerBlock;
+    const uint32_t n_in = (uint32_t)min((int64_t)kSamplesPerBlock, o.n_s - s0);
+    const uint32_t gs0 = (uint32_t)(o.s_begin + s0);  // < 2^29 samples
+    const uint32_t ray0 = gs0 / (uint32_t)a.S;
+    const bool in = threadIdx.x < n_in;
+    const uint32_t sl = min(threadIdx.x, n_in - 1u);
+    const uint32_t lray = (uint32_t)(((float)(gs0 - ray0 * (uint32_t)a.S + sl) + 0.5f) * a.inv_S);
+    const float* ro = a.ray_obj + 6 * (int64_t)ray0 + 6u * lray;
+    float2 d = (a.dy + o.dy_off + (int64_t)l * o.n_s + s0)[sl];
+    const float ts = (a.t + gs0)[sl];
     for (int i = threadIdx.x; i < nt; i += kPlaceThreads) hist[i] = 0;
+    if (threadIdx.x == 0) s_max = 0u;
     Corners c;
-    level_corners(o.grid, l, sample_coord(ts, ro[3], ro[0]), sample_coord(ts, ro[4], ro[1]),
+    level_corners<true>(o.grid, l, sample_coord(ts, ro[3], ro[0]), sample_coord(ts, ro[4], ro[1]),
                   sample_coord(ts, ro[5], ro[2]), c);
-    const bool has = in && (d.x != 0.0f || d.y != 0.0f);
+    if (!in) d = make_float2(0.0f, 0.0f);
+    const bool has = d.x != 0.0f || d.y != 0.0f;
     // a non-finite feature gradient (fmaxf would drop a NaN) marks the step
     // for the loss scaler, which then skips the update
-    if (a.nonfinite && in && !(isfinite(d.x) && isfinite(d.y))) a.nonfinite[0] = 1;
-    // Row maxima by DPP row shifts: lanes past the row's end read 0, the
-    // identity of a maximum of |dy| values; the row's first lane ends with it.
-    float m = has ? fmaxf(fabsf(d.x), fabsf(d.y)) : 0.0f;
-    m = fmaxf(m, dpp_f32<0x101>(m));
-    m = fmaxf(m, dpp_f32<0x102>(m));
-    m = fmaxf(m, dpp_f32<0x104>(m));
-    m = fmaxf(m, dpp_f32<0x108>(m));
-    if ((threadIdx.x & 15) == 0) wmax[threadIdx.x >> 4] = m;
-    const uint32_t heads = run_heads(c, has);  // corners that start a record
+    if (a.nonfinite && !(isfinite(d.x) && isfinite(d.y))) a.nonfinite[0] = 1;
+    const bool head = run_head(c, has);
     float2 val[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        val[e] = has ? make_float2(c.w[e] * d.x, c.w[e] * d.y) : make_float2(0.0f, 0.0f);
-        const bool head = (heads >> e) & 1u;
-        if (__ballot(has && !head)) val[e] = run_sum(val[e], head || !has);
+    for (int e = 0; e < 8; ++e)
+        val[e] = make_float2(c.w[e] * d.x, c.w[e] * d.y);
+    if (__ballot(has && !head)) run_sum(val, head || !has);
+    // Wave maximum of |dy| by DPP (row shifts, whose lanes past the row's end
+    // read 0, the identity of a maximum of absolute values; then each row's
+    // last lane into the next rows): the last lane ends with it.
+    float m = max_abs(d.x, d.y);
+    m = fmaxf(m, dpp_f32<0x111>(m));
+    m = fmaxf(m, dpp_f32<0x112>(m));
+    m = fmaxf(m, dpp_f32<0x114>(m));
+    m = fmaxf(m, dpp_f32<0x118>(m));
+    m = fmaxf(m, dpp_f32<0x142>(m));
+    m = fmaxf(m, dpp_f32<0x143>(m));
+    __syncthreads();
+    if ((threadIdx.x & 63) == 63) atomicMax(&s_max, __float_as_uint(m));  // (m >= 0: ordered as its bits)
+    // Rank of each record within its tile (LDS atomics), in units of kUnit; the
+    // histogram counts in those units, so that a segment's start and a rank add
+    // up to the record's LDS address (compact: to its high word's).
+    constexpr uint32_t kUnit = kCompact ? 2 : 8;
+    uint32_t rank[8], tile[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) tile[e] = c.row[e] >> kTileBits;
+    if (head) {
+        if (nt <= kAggregateTiles) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) rank[e] = wave_aggregated_add(hist, tile[e], kUnit);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) rank[e] = atomicAdd(&hist[tile[e]], kUnit);
+        }
     }
     __syncthreads();
-    // rank of each record within its tile (LDS atomics)
-    uint32_t rank[8];
-    if (nt <= kAggregateTiles) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if ((heads >> e) & 1u) rank[e] = wave_aggregated_add(hist, c.row[e] >> kTileBits);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if ((heads >> e) & 1u) rank[e] = atomicAdd(&hist[c.row[e] >> kTileBits], 1u);
-    }
-    float bm = 0.0f;
-#pragma unroll
-    for (int i = 0; i < kRows; ++i) bm = fmaxf(bm, wmax[i]);
-    const int E = block_rec_exp(bm);
-    __syncthreads();
+    const float bm = __uint_as_float(s_max);
+    const int E = block_rec_exp(bm), r_max = min((1 << EB) - 1, E - kExpFloor);
     // segment starts: exclusive scan of the histogram in place (by one wave)
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
@@ -278,24 +307,25 @@ __global__ __launch_bounds__(kPlaceThreads) void k_scatter_place(ScatterArgs a)
     }
     __syncthreads();
     // stage the encoded records sorted by tile
+    if (head) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        if (!((heads >> e) & 1u)) continue;
-        const uint32_t p = hist[c.row[e] >> kTileBits] + rank[e];
-        uint32_t lo, hi;
-        encode_record<EB, MB>(val[e], E, c.row[e] & (kTileRows - 1), lo, hi);
-        if constexpr (kCompact) {
-            s_lo[p] = lo;
-            s_hi[p] = (uint16_t)hi;
-        } else {
-            s_rec[p] = (uint64_t)hi << 32 | lo;
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t p = hist[tile[e]] + rank[e];
+            uint32_t lo, hi;
+            encode_record<EB, MB>(val[e], E, r_max, c.row[e] & (kTileRows - 1), lo, hi);
+            if constexpr (kCompact) {
+                *reinterpret_cast<uint32_t*>(smem + 2 * p) = lo;
+                *reinterpret_cast<uint16_t*>(smem + kRecordsPerBlock * 4 + p) = (uint16_t)hi;
+            } else {
+                *reinterpret_cast<uint64_t*>(smem + p) = (uint64_t)hi << 32 | lo;
+            }
         }
     }
     uint16_t* seg = a.seg + seg_index(o, l, bx);
-    for (int i = threadIdx.x; i <= nt; i += kPlaceThreads) seg[i] = (uint16_t)hist[i];
+    for (int i = threadIdx.x; i <= nt; i += kPlaceThreads) seg[i] = (uint16_t)(hist[i] / kUnit);
     __syncthreads();
     // the block's records to its range of the record array, 16 bytes per lane
-    const uint32_t total = hist[nt];
+    const uint32_t total = hist[nt] / kUnit;
     if constexpr (kCompact) {
         uint32_t* glo = reinterpret_cast<uint32_t*>(a.recs) + item * kRecordsPerBlock;
         uint16_t* ghi = reinterpret_cast<uint16_t*>(reinterpret_cast<uint32_t*>(a.recs) + a.n_records) +
