@@ -137,6 +137,9 @@ __device__ __forceinline__ float2 gather_blend_dense(const Row* __restrict__ lev
     typename RP::any v[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) v[p] = *reinterpret_cast<const typename RP::any*>(level_table + c.row[2 * p]);
+    // (keeps the compiler from joining these loads with the plain gather's,
+    // which split them into their rows again)
+    asm volatile("" ::: "memory");
     float2 acc = make_float2(0.0f, 0.0f);
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
@@ -155,13 +158,15 @@ __device__ __forceinline__ float2 gather_blend_dense(const Row* __restrict__ lev
 // a sample however they are read (x and x + 1 lie in one line 15 times out of
 // 16); reading them in pairs saves the hits.  Tables of fewer than
 // 2^kPairMinLog2 rows hit more, and the pairs' selects cost more than they save.
-// Measured on gfx950: dense levels in pairs 1.19 -> 1.17 ms (65536 rays x 64
-// samples, 16 levels of 2^19 rows), 11.89 -> 11.36 ms (48 objects, FP16 tables);
-// hashed levels in pairs from 2^10 rows on instead of 2^17: 0.282 against
-// 0.260 ms for a view over 2^15 rows.  The batch (kPairs false) reads hashed
-// levels plainly: in pairs from 2^17 rows on 11.38 against 11.36 ms, 24
-// objects 3.25 against 3.23 ms.
-constexpr int kPairMinLog2 = 17;
+// Measured on gfx950 (us): 65536 rays x 64 samples, 16 levels of 2^19 rows, 1167
+// in pairs against 1297 plain; FP16 tables of 2^18 rows 1976 against 2058; 30011
+// rays, 12 levels of 2^17, 317 against 306; a view over 2^15 rows 278 against
+// 259.  The batch (kPairs false) reads hashed levels plainly, as one kernel
+// serves tables of all sizes and types and the pairs' code costs the others: 24
+// objects 3090 in pairs from 2^19 rows on against 2747 plain, 48 objects with
+// FP16 tables 11344 against 11460.  Dense levels in pairs: 48 objects 11.9 ->
+// 11.4 ms.
+constexpr int kPairMinLog2 = 18;
 
 template <bool kPairs, typename Row>
 __device__ __forceinline__ float2 gather_blend(const Row* __restrict__ level_table, const GridInfo& g, int l,
