@@ -56,6 +56,7 @@ constexpr int kSegGroups = kReduceThreads / kSegLanes;  // segments in flight pe
 // Records in flight per lane: a step covers 80 records of a segment, so the
 // segments of a 2^19-row level (4096 / 64 = 64 records on average) take one.
 constexpr int kSegStep = 5;
+constexpr int kHeads = 2048;  // blocks whose segment bounds a workgroup holds in LDS
 constexpr int kLevelThreads = 1024;
 constexpr int kCombineThreads = 256;
 // Reduce items of a pass (scatter_split): about kReduceItems of even size, so
@@ -399,6 +400,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a
 {
     constexpr int EB = kCompact ? kRecExpBitsC : kRecExpBits, MB = kCompact ? kRecMantBitsC : kRecMantBits;
     __shared__ unsigned long long acc[2 * kTileRows];  // fixed point: feature 0 rows, then feature 1 rows
+    __shared__ uint2 head[kHeads];  // segments of kHeads blocks: start and end, max |dy| of the block
     const int64_t ritem = blockIdx.x;
     const ScatterObj& o = sobj<kMany>(a, last_le<kMany>(a, ritem, [](const ScatterObj& v) { return v.ritem_off; }));
     const int rl = (int)(ritem - o.ritem_off);
@@ -416,84 +418,87 @@ __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a
         acc[i] = 0ull;
         acc[kTileRows + i] = 0ull;
     }
-    __syncthreads();
-    if (b0 < b1) {
-        const int ln = threadIdx.x & (kSegLanes - 1);
-        const int nt1 = o.tiles[l] + 1;
-        const uint16_t* seg = a.seg + seg_index(o, l, 0) + tt;
-        const int64_t item0 = o.item_off + (int64_t)l * nb;
-        const float* bmx = a.block_max + item0;
-        // Segment of one block: the step's first record p, the end, the block's
-        // max |dy|.  Loads are unconditional, of clamped addresses, and what
-        // they return is looked at only when it is used, so that none waits for
-        // another.
-        struct Seg {
-            int p, end;
-            float bm;
-            int64_t base;
+    const int ln = threadIdx.x & (kSegLanes - 1);
+    const int nt1 = o.tiles[l] + 1;
+    const uint16_t* seg = a.seg + seg_index(o, l, 0) + tt;
+    const int64_t item0 = o.item_off + (int64_t)l * nb;
+    for (int c0 = b0; c0 < b1; c0 += kHeads) {
+        const int n = min(kHeads, b1 - c0);
+        for (int i = threadIdx.x; i < n; i += kReduceThreads) {
+            const uint16_t* p = seg + (int64_t)(c0 + i) * nt1;
+            head[i] = make_uint2((uint32_t)p[0] | (uint32_t)p[1] << 16, __float_as_uint(a.block_max[item0 + c0 + i]));
+        }
+        __syncthreads();  // (also orders the cleared accumulators before the additions)
+        // Steps of up to kSegStep * kSegLanes records of one segment: the lane's
+        // records are u * kSegLanes < left.  Loads are unconditional, of clamped
+        // addresses, and looked at two steps later, so that none waits for
+        // another; the steps' registers take turns, for the same reason.
+        struct Step {
+            uint32_t lo[kSegStep], hi[kSegStep];
+            int left, sh0;
+            bool any;
         };
-        auto header = [&](int b) {
-            const int bc = min(b, b1 - 1);
-            Seg h;
-            h.p = seg[(int64_t)bc * nt1];
-            h.end = seg[(int64_t)bc * nt1 + 1];
-            h.bm = bmx[bc];
-            h.base = (item0 + bc) * kRecordsPerBlock;
-            return h;
-        };
-        auto load = [&](const Seg& h, uint32_t (&lo)[kSegStep], uint32_t (&hi)[kSegStep]) {
-#pragma unroll
-            for (int u = 0; u < kSegStep; ++u) {
-                const int i = h.p + ln + u * kSegLanes;
-                // (a segment may be empty and start at the end of the block's range)
-                const int64_t at = h.base + (i < h.end ? i : min(h.p, kRecordsPerBlock - 1));
-                if constexpr (kCompact) {
-                    const uint32_t* words = reinterpret_cast<const uint32_t*>(a.recs);
-                    lo[u] = words[at];
-                    hi[u] = reinterpret_cast<const uint16_t*>(words + a.n_records)[at];
-                } else {
-                    const uint2 w = reinterpret_cast<const uint2*>(a.recs)[at];
-                    lo[u] = w.x;
-                    hi[u] = w.y;
-                }
-            }
-        };
-        int b = b0 + (int)(threadIdx.x / kSegLanes);
-        Seg cur = header(b), nxt = header(b + kSegGroups);
-        // Requests the next step's records into lo2/hi2, then adds the current
-        // step's.  Two buffers take turns, so no step copies registers (a copy
-        // would wait for the loads).
-        auto advance = [&](const uint32_t (&lo)[kSegStep], const uint32_t (&hi)[kSegStep], uint32_t (&lo2)[kSegStep],
-                           uint32_t (&hi2)[kSegStep]) {
-            const int left = cur.end - cur.p - ln;  // the lane's records are u * kSegLanes < left
+        int b = (int)(threadIdx.x / kSegLanes), p = 0, end = 0;
+        uint2 h = head[min(b, n - 1)];
+        p = (int)(h.x & 0xffffu);
+        end = (int)(h.x >> 16);
+        auto fetch = [&](Step& st) {
+            const int64_t base = (item0 + c0 + min(b, n - 1)) * kRecordsPerBlock;
+            st.any = b < n;
+            st.left = b < n ? end - p - ln : 0;
             // a record (qx, qy, r) is worth (qx, qy) 2^(E - r - (MB - 1)); in
             // fixed point at 2^ex that is (qx, qy) 2^(sh0 - r)
-            const int sh0 = block_rec_exp(cur.bm) - (MB - 1) + ex;
+            st.sh0 = block_rec_exp(__uint_as_float(h.y)) - (MB - 1) + ex;
+#pragma unroll
+            for (int u = 0; u < kSegStep; ++u) {
+                const int i = p + ln + u * kSegLanes;
+                // (a segment may be empty and start at the end of the block's range)
+                const int64_t at = base + (i < end ? i : min(p, kRecordsPerBlock - 1));
+                if constexpr (kCompact) {
+                    const uint32_t* words = reinterpret_cast<const uint32_t*>(a.recs);
+                    st.lo[u] = words[at];
+                    st.hi[u] = reinterpret_cast<const uint16_t*>(words + a.n_records)[at];
+                } else {
+                    const uint2 w = reinterpret_cast<const uint2*>(a.recs)[at];
+                    st.lo[u] = w.x;
+                    st.hi[u] = w.y;
+                }
+            }
             // the next step: the rest of this segment, or the next block's
-            cur.p += kSegStep * kSegLanes;
-            const bool done = cur.p >= cur.end;
-            if (done) cur = nxt;
-            b += done ? kSegGroups : 0;
-            load(cur, lo2, hi2);
-            nxt = header(b + kSegGroups);
+            p += kSegStep * kSegLanes;
+            if (p >= end) {
+                b += kSegGroups;
+                h = head[min(b, n - 1)];
+                p = (int)(h.x & 0xffffu);
+                end = (int)(h.x >> 16);
+            }
+        };
+        auto add = [&](const Step& st) {
 #pragma unroll
             for (int u = 0; u < kSegStep; ++u) {
                 uint32_t key;
                 int r, qx, qy;
-                decode_record<EB, MB>(lo[u], hi[u], key, r, qx, qy);
-                if (u * kSegLanes < left) {
-                    atomicAdd(&acc[key], (unsigned long long)scale_mantissa(qx, sh0 - r));
-                    atomicAdd(&acc[kTileRows + key], (unsigned long long)scale_mantissa(qy, sh0 - r));
+                decode_record<EB, MB>(st.lo[u], st.hi[u], key, r, qx, qy);
+                if (u * kSegLanes < st.left) {
+                    atomicAdd(&acc[key], (unsigned long long)scale_mantissa(qx, st.sh0 - r));
+                    atomicAdd(&acc[kTileRows + key], (unsigned long long)scale_mantissa(qy, st.sh0 - r));
                 }
             }
         };
-        uint32_t lo[2][kSegStep], hi[2][kSegStep];
-        load(cur, lo[0], hi[0]);
-        while (b < b1) {
-            advance(lo[0], hi[0], lo[1], hi[1]);
-            if (b >= b1) break;
-            advance(lo[1], hi[1], lo[0], hi[0]);
+        Step s0, s1, s2;
+        fetch(s0);
+        fetch(s1);
+        while (s0.any) {
+            fetch(s2);
+            add(s0);
+            if (!s1.any) break;
+            fetch(s0);
+            add(s1);
+            if (!s2.any) break;
+            fetch(s1);
+            add(s2);
         }
+        __syncthreads();
     }
     __syncthreads();
     if (n_split > 1) {
