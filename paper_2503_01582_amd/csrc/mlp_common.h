@@ -46,7 +46,7 @@ constexpr int kStagePad = 4;      // floats of padding per staged row
 inline int bwd_blocks(int64_t n_s)
 {
     const int64_t n_tiles = (n_s + 15) / 16;
-    int64_t b = (n_tiles + kBwdWaves * 16 - 1) / (kBwdWaves * 16);  // >= 16 tiles per wave
+    int64_t b = (n_tiles + kBwdWaves * 2 - 1) / (kBwdWaves * 2);  // >= 16 tiles per wave
     b = b < 1 ? 1 : b;
     return (int)(b > kBwdMaxBlocks ? kBwdMaxBlocks : b);
 }
