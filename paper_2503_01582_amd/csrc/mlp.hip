@@ -204,8 +204,14 @@ __device__ __forceinline__ void mlp_fwd_tiles(const float* __restrict__ frag, co
     }
 }
 
+// Threads of a forward (and of the 128-wide chain) block.  The 128-wide
+// fragments (up to 88 KB) leave room for one block per CU: eight waves share
+// them, two a SIMD, so that one's LDS and global waits overlap the other's
+// MFMAs.
+constexpr int fwd_threads(int width) { return width >= kWideWidth ? 512 : 256; }
+
 template <int IN, int W, int D>
-__global__ __launch_bounds__(256) void k_mlp_fwd(const float* __restrict__ w, const float* __restrict__ y,
+__global__ __launch_bounds__(fwd_threads(W)) void k_mlp_fwd(const float* __restrict__ w, const float* __restrict__ y,
                                                  int64_t n_s, float4* __restrict__ sc, float* __restrict__ act)
 {
     using N = Net<IN, W, D>;
@@ -221,7 +227,7 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float* __restrict__ w, co
 // work[b].obj, whose weights start at w_off[obj] and whose features and head
 // outputs live at y_off / s_off (activations at a_off when act is given).
 template <int IN, int W, int D>
-__global__ __launch_bounds__(256) void k_mlp_fwd_batch(const MlpWork* __restrict__ work, const float* __restrict__ params,
+__global__ __launch_bounds__(fwd_threads(W)) void k_mlp_fwd_batch(const MlpWork* __restrict__ work, const float* __restrict__ params,
                                                        const float* __restrict__ y, float4* __restrict__ sc,
                                                        float* __restrict__ act)
 {
@@ -609,9 +615,13 @@ __device__ __forceinline__ void mlp_dw_range(float* __restrict__ lds, const floa
 #pragma unroll
             for (int t = 0; t < N::OT; ++t) aH[k][a][t] = {0.0f, 0.0f, 0.0f, 0.0f};
     }
+    // the next chunk's global loads overlap the current chunk's MFMAs
+    DwRegs<W, D, PY> R;
+    if (s_begin < s_end) dw_load<IN, W, D, PY>(R, y, sc, dout, act, dlt, n_s, s_begin, s_end);
     for (int64_t c0 = s_begin; c0 < s_end; c0 += kDwChunk) {
-        dw_stage<IN, W, D, PW, PY>(lds, y, sc, dout, act, dlt, n_s, c0, s_end);
+        dw_store<W, D, PW, PY>(lds, R);
         __syncthreads();
+        if (c0 + kDwChunk < s_end) dw_load<IN, W, D, PY>(R, y, sc, dout, act, dlt, n_s, c0 + kDwChunk, s_end);
 #pragma unroll 2
         for (int ks = 0; ks < kDwChunk / 4; ++ks) {
             const int r = 4 * ks + q;  // the lane's sample within the chunk
@@ -676,7 +686,7 @@ constexpr size_t dw_lds_bytes()
 }
 
 template <int IN, int W, int D>
-__global__ __launch_bounds__(256) void k_mlp_chain_bwd(const float* __restrict__ w, const float4* __restrict__ sc,
+__global__ __launch_bounds__(fwd_threads(W)) void k_mlp_chain_bwd(const float* __restrict__ w, const float4* __restrict__ sc,
                                                        const float4* __restrict__ dout, float* __restrict__ act,
                                                        int64_t n_s, float2* __restrict__ dy)
 {
@@ -690,7 +700,7 @@ __global__ __launch_bounds__(256) void k_mlp_chain_bwd(const float* __restrict__
 }
 
 template <int IN, int W, int D>
-__global__ __launch_bounds__(256) void k_mlp_chain_bwd_batch(const MlpWork* __restrict__ work,
+__global__ __launch_bounds__(fwd_threads(W)) void k_mlp_chain_bwd_batch(const MlpWork* __restrict__ work,
                                                              const float* __restrict__ params,
                                                              const float4* __restrict__ sc,
                                                              const float4* __restrict__ dout, float* __restrict__ act,
@@ -785,12 +795,13 @@ template <int IN, int W, int D>
 hipError_t fwd_impl(const float* w, const float* y, int64_t n_s, float* sc, float* act, hipStream_t s)
 {
     const int64_t n_tiles = (n_s + 15) / 16;
-    int64_t blocks = (n_tiles + 3) / 4;
+    constexpr int kWaves = fwd_threads(W) / 64;
+    int64_t blocks = (n_tiles + kWaves - 1) / kWaves;
     blocks = blocks > 2048 ? 2048 : blocks;
     const size_t lds = fwd_lds_bytes<IN, W, D>();
     hipError_t e = set_lds(k_mlp_fwd<IN, W, D>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_mlp_fwd<IN, W, D>), dim3((uint32_t)blocks), dim3(256), lds, s, w, y, n_s, (float4*)sc,
+    hipLaunchKernelGGL((k_mlp_fwd<IN, W, D>), dim3((uint32_t)blocks), dim3(fwd_threads(W)), lds, s, w, y, n_s, (float4*)sc,
                        W >= kWideWidth ? act : nullptr);
     return hipGetLastError();
 }
@@ -807,12 +818,13 @@ hipError_t bwd_impl(const float* w, const float* y, const float* dout, const flo
 {
     if constexpr (W >= kWideWidth) {
         const int64_t n_tiles = (n_s + 15) / 16;
-        int64_t blocks = (n_tiles + 3) / 4;
+        constexpr int kWaves = fwd_threads(W) / 64;
+        int64_t blocks = (n_tiles + kWaves - 1) / kWaves;
         blocks = blocks > 2048 ? 2048 : blocks;
         const size_t lds = chain_bwd_lds_bytes<IN, W, D>();
         hipError_t e = set_lds(k_mlp_chain_bwd<IN, W, D>, lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_mlp_chain_bwd<IN, W, D>), dim3((uint32_t)blocks), dim3(256), lds, s, w,
+        hipLaunchKernelGGL((k_mlp_chain_bwd<IN, W, D>), dim3((uint32_t)blocks), dim3(fwd_threads(W)), lds, s, w,
                            (const float4*)sc, (const float4*)dout, act, n_s, (float2*)dy);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         const int nb = bwd_blocks(n_s);
@@ -840,7 +852,7 @@ hipError_t fwd_batch_impl(const MlpWork* work, int n_blocks, const float* params
     const size_t lds = fwd_lds_bytes<IN, W, D>();
     hipError_t e = set_lds(k_mlp_fwd_batch<IN, W, D>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_mlp_fwd_batch<IN, W, D>), dim3((uint32_t)n_blocks), dim3(256), lds, s, work, params, y,
+    hipLaunchKernelGGL((k_mlp_fwd_batch<IN, W, D>), dim3((uint32_t)n_blocks), dim3(fwd_threads(W)), lds, s, work, params, y,
                        (float4*)sc, W >= kWideWidth ? act : nullptr);
     return hipGetLastError();
 }
@@ -853,7 +865,7 @@ hipError_t bwd_batch_impl(const MlpWork* work, int n_blocks, const float* params
         const size_t lds = chain_bwd_lds_bytes<IN, W, D>();
         hipError_t e = set_lds(k_mlp_chain_bwd_batch<IN, W, D>, lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_mlp_chain_bwd_batch<IN, W, D>), dim3((uint32_t)n_blocks), dim3(256), lds, s, work,
+        hipLaunchKernelGGL((k_mlp_chain_bwd_batch<IN, W, D>), dim3((uint32_t)n_blocks), dim3(fwd_threads(W)), lds, s, work,
                            params, (const float4*)sc, (const float4*)dout, act, (float2*)dy);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         const size_t dwl = dw_lds_bytes<IN, W, D>();

@@ -106,55 +106,75 @@ struct DwStage {
     static constexpr int FLOATS = DO + kDwChunk * 4;
 };
 
-// Input features and head adjoint of samples [s0, min(s0 + kDwChunk, s_end))
-// into LDS (zeros past the end; input columns >= IN zero).  y: level-major
-// [L][n_s][2].
-template <int IN, int W, int D, int PW, int PY>
-__device__ __forceinline__ void dw_stage_inputs(float* __restrict__ lds, const float* __restrict__ y,
-                                                const float4* __restrict__ sc, const float4* __restrict__ dout,
-                                                int64_t n_s, int64_t s0, int64_t s_end)
+// Staging of samples [s0, min(s0 + kDwChunk, s_end)) in two halves: dw_load
+// reads a thread's share into registers, dw_store writes it to LDS (zeros past
+// the end; input columns >= IN zero).  y: level-major [L][n_s][2]; act, dlt: rows
+// of W floats, [D][n_s][W].  kDwThreads threads.
+constexpr int kDwThreads = 256;
+
+template <int W, int D, int PY>
+struct DwRegs {
+    static constexpr int V = W / 4;  // float4 per row
+    static constexpr int N_ROW = D * kDwChunk * V, PER = N_ROW / kDwThreads;
+    static constexpr int N_Y = kDwChunk * (PY / 2), PER_Y = N_Y / kDwThreads;
+    static_assert(N_ROW % kDwThreads == 0 && N_Y % kDwThreads == 0, "whole shares");
+    floatx4 a[PER], d[PER];
+    float2 yv[PER_Y];
+    float4 g, v;  // head adjoint inputs of one sample (threads < kDwChunk)
+};
+
+template <int IN, int W, int D, int PY>
+__device__ __forceinline__ void dw_load(DwRegs<W, D, PY>& R, const float* __restrict__ y, const float4* __restrict__ sc,
+                                        const float4* __restrict__ dout, const float* __restrict__ act,
+                                        const float* __restrict__ dlt, int64_t n_s, int64_t s0, int64_t s_end)
 {
-    using St = DwStage<W, D, PW, PY>;
-    for (int i = threadIdx.x; i < kDwChunk * (PY / 2); i += blockDim.x) {
-        const int r = i / (PY / 2), l = i % (PY / 2);
+    using Rg = DwRegs<W, D, PY>;
+#pragma unroll
+    for (int u = 0; u < Rg::PER; ++u) {
+        const int i = threadIdx.x + kDwThreads * u;
+        const int k = i / (kDwChunk * Rg::V), rem = i % (kDwChunk * Rg::V), r = rem / Rg::V, c = rem % Rg::V;
         const int64_t s = s0 + r;
-        float2 v = make_float2(0.0f, 0.0f);
-        if (s < s_end && 2 * l < IN) v = reinterpret_cast<const float2*>(y)[(int64_t)l * n_s + s];
-        *reinterpret_cast<float2*>(lds + St::Y + r * PY + 2 * l) = v;
-    }
-    if (threadIdx.x < kDwChunk) {
-        const int r = threadIdx.x;
-        const int64_t s = s0 + r;
-        floatx4 o = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (s < s_end) {  // d sigma / d o0 = sigma, d c / d o = c (1 - c)
-            const float4 g = dout[s], v = sc[s];
-            o = {g.x * v.x, g.y * v.y * (1.0f - v.y), g.z * v.z * (1.0f - v.z), g.w * v.w * (1.0f - v.w)};
+        R.a[u] = R.d[u] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (s < s_end) {
+            R.a[u] = *reinterpret_cast<const floatx4*>(act + ((int64_t)k * n_s + s) * W + 4 * c);
+            R.d[u] = *reinterpret_cast<const floatx4*>(dlt + ((int64_t)k * n_s + s) * W + 4 * c);
         }
-        *reinterpret_cast<floatx4*>(lds + St::DO + r * 4) = o;
     }
+#pragma unroll
+    for (int u = 0; u < Rg::PER_Y; ++u) {
+        const int i = threadIdx.x + kDwThreads * u, r = i / (PY / 2), l = i % (PY / 2);
+        const int64_t s = s0 + r;
+        R.yv[u] = s < s_end && 2 * l < IN ? reinterpret_cast<const float2*>(y)[(int64_t)l * n_s + s]
+                                          : make_float2(0.0f, 0.0f);
+    }
+    const int64_t s = s0 + threadIdx.x;
+    const bool ok = threadIdx.x < kDwChunk && s < s_end;
+    R.g = ok ? dout[s] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    R.v = ok ? sc[s] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 }
 
-// Every layer's activation and delta rows (FP32, [D][n_s][W]) of the chunk.
-template <int IN, int W, int D, int PW, int PY>
-__device__ __forceinline__ void dw_stage(float* __restrict__ lds, const float* __restrict__ y,
-                                         const float4* __restrict__ sc, const float4* __restrict__ dout,
-                                         const float* __restrict__ act, const float* __restrict__ dlt, int64_t n_s,
-                                         int64_t s0, int64_t s_end)
+template <int W, int D, int PW, int PY>
+__device__ __forceinline__ void dw_store(float* __restrict__ lds, const DwRegs<W, D, PY>& R)
 {
     using St = DwStage<W, D, PW, PY>;
-    constexpr int V = W / 4;  // float4 per row
-    for (int i = threadIdx.x; i < D * kDwChunk * V; i += blockDim.x) {
-        const int k = i / (kDwChunk * V), rem = i % (kDwChunk * V), r = rem / V, c = rem % V;
-        const int64_t s = s0 + r;
-        floatx4 a = {0.0f, 0.0f, 0.0f, 0.0f}, d = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (s < s_end) {
-            a = *reinterpret_cast<const floatx4*>(act + ((int64_t)k * n_s + s) * W + 4 * c);
-            d = *reinterpret_cast<const floatx4*>(dlt + ((int64_t)k * n_s + s) * W + 4 * c);
-        }
-        *reinterpret_cast<floatx4*>(lds + St::AC + (k * kDwChunk + r) * PW + 4 * c) = a;
-        *reinterpret_cast<floatx4*>(lds + St::DL + (k * kDwChunk + r) * PW + 4 * c) = d;
+    using Rg = DwRegs<W, D, PY>;
+#pragma unroll
+    for (int u = 0; u < Rg::PER; ++u) {
+        const int i = threadIdx.x + kDwThreads * u;
+        const int k = i / (kDwChunk * Rg::V), rem = i % (kDwChunk * Rg::V), r = rem / Rg::V, c = rem % Rg::V;
+        *reinterpret_cast<floatx4*>(lds + St::AC + (k * kDwChunk + r) * PW + 4 * c) = R.a[u];
+        *reinterpret_cast<floatx4*>(lds + St::DL + (k * kDwChunk + r) * PW + 4 * c) = R.d[u];
     }
-    dw_stage_inputs<IN, W, D, PW, PY>(lds, y, sc, dout, n_s, s0, s_end);
+#pragma unroll
+    for (int u = 0; u < Rg::PER_Y; ++u) {
+        const int i = threadIdx.x + kDwThreads * u, r = i / (PY / 2), l = i % (PY / 2);
+        *reinterpret_cast<float2*>(lds + St::Y + r * PY + 2 * l) = R.yv[u];
+    }
+    if (threadIdx.x < kDwChunk) {  // d sigma / d o0 = sigma, d c / d o = c (1 - c)
+        const float4 g = R.g, v = R.v;
+        *reinterpret_cast<floatx4*>(lds + St::DO + threadIdx.x * 4) =
+            floatx4{g.x * v.x, g.y * v.y * (1.0f - v.y), g.z * v.z * (1.0f - v.z), g.w * v.w * (1.0f - v.w)};
+    }
 }
 
 }  // namespace prenom
