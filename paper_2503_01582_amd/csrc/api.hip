@@ -98,14 +98,14 @@ MlpShape mlp_shape(const prenom_arch* a)
 hipError_t mlp_fwd_any(const MlpShape& m, const float* w, const float* y, int64_t n_s, float* sc, float* act,
                        hipStream_t s)
 {
-    return m.dtype == PRENOM_F32 ? launch_mlp_fwd(m, w, y, n_s, sc, act, s) : launch_mlp_fwd_lp(m, w, y, n_s, sc, act, s);
+    return m.dtype == PRENOM_F32 ? launch_mlp_fwd(m, w, y, n_s, sc, act, s) : launch_mlp_fwd_lp(m, w, y, n_s, sc, s);
 }
 
 hipError_t mlp_bwd_any(const MlpShape& m, const float* w, const float* y, const float* dout, const float* sc,
                        int64_t n_s, float* dy, float* partial, float* act, hipStream_t s)
 {
     return m.dtype == PRENOM_F32 ? launch_mlp_bwd(m, w, y, dout, sc, n_s, dy, partial, act, s)
-                                 : launch_mlp_bwd_lp(m, w, y, dout, sc, n_s, dy, partial, act, s);
+                                 : launch_mlp_bwd_lp(m, w, y, dout, sc, n_s, dy, partial, s);
 }
 
 prenom_status check_supported(const prenom_arch* a)

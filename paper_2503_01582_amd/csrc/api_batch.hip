@@ -105,11 +105,8 @@ constexpr int64_t kCus = 256;
 constexpr int64_t kFwdQuantum = 4, kBwdQuantum = 8;
 
 // Backward blocks that one CU's LDS holds at a time: the 32-wide kernels' 50 KB
-// and the 16-bit 128-wide ones' leave room for two.
-int64_t bwd_blocks_per_cu(const MlpShape& m)
-{
-    return m.width <= 32 || (m.width >= kWideWidth && m.dtype != PRENOM_F32) ? 2 : 1;
-}
+// leave room for two.
+int64_t bwd_blocks_per_cu(const MlpShape& m) { return m.width <= 32 ? 2 : 1; }
 
 // Tiles per work item of a launch over objects of `tiles` 16-sample tiles.
 int64_t run_length(const std::vector<int64_t>& tiles, int64_t most, int64_t quantum, int64_t target)
@@ -431,8 +428,7 @@ prenom_status fwd_features(const prenom_batch* b, const Plan& p, const float* ra
         PRENOM_LAUNCH("k_mlp_fwd", s,
                       g.shape.dtype == PRENOM_F32
                           ? launch_mlp_fwd_batch(g.shape, work, (int)g.n_fwd, b->params, y, sc, at<float>(ws, p.act), s)
-                          : launch_mlp_fwd_lp_batch(g.shape, work, (int)g.n_fwd, b->params, y, sc, at<float>(ws, p.act),
-                                                    s));
+                          : launch_mlp_fwd_lp_batch(g.shape, work, (int)g.n_fwd, b->params, y, sc, s));
     }
     return PRENOM_OK;
 }
@@ -636,7 +632,7 @@ prenom_status prenom_batch_render_bwd(const prenom_batch* batch, const prenom_re
                           ? launch_mlp_bwd_batch(g.shape, work, (int)g.n_bwd, batch->params, y, c.dout, c.sc, dy,
                                                  partial + g.partial_off, n_mlp, at<float>(workspace, p.act), s)
                           : launch_mlp_bwd_lp_batch(g.shape, work, (int)g.n_bwd, batch->params, y, c.dout, c.sc, dy,
-                                                    partial + g.partial_off, n_mlp, at<float>(workspace, p.act), s));
+                                                    partial + g.partial_off, n_mlp, s));
     }
     PRENOM_LAUNCH("k_reduce_partials", s,
                   launch_reduce_partials_batch(at<const MlpRed>(workspace, p.o_red), p.n_obj, p.n_mlp_total, partial,

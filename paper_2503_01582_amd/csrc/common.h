@@ -380,49 +380,42 @@ bool mlp_supported(const MlpShape& m);
 // one object.  w_off (floats) locates the object's MLP weights in the batch
 // parameters, y_off (floats) its features (level-major [L][n_s][2]), s_off
 // (samples) its first sample in the per-sample arrays, a_off (floats) its
-// stored activations and deltas when the MLP is 128 wide.
+// stored activations and deltas when the MLP is 128 wide and FP32.
 struct MlpWork {
     int64_t w_off, y_off, s_off, n_s;
     int64_t tile_begin, tile_end;
     int64_t a_off;
 };
 
-// The 128-wide MLP stores its hidden activations in the forward and runs its
-// backward as a chain kernel (deltas, dy) and a weight-gradient kernel; the
-// two buffers hold act[D][n_s][W] and delta[D][n_s][W], FP32 in the FP32
-// form and already rounded to the MFMA type (16 bits) in the reduced form,
-// where they only ever enter the matrix cores rounded (and the ReLU masks
-// only need their sign).
+// The 128-wide FP32 MLP stores its hidden activations in the forward and runs
+// its backward as a chain kernel (deltas, dy) and a weight-gradient kernel; the
+// two buffers hold act[D][n_s][W] and delta[D][n_s][W].  The 16-bit form
+// recomputes them in one kernel.
 constexpr int kWideWidth = 128;
 inline int64_t mlp_act_floats(const MlpShape& m, int64_t n_s)
 {
-    if (m.width < kWideWidth) return 0;
-    // FP32: activations and deltas; 16-bit: both in the MFMA type (whole 16-sample
-    // tiles), plus the ReLU mask words
-    const int64_t n_sp = (n_s + 15) / 16 * 16;
-    return m.dtype == PRENOM_F32 ? 2 * (int64_t)m.hidden * n_s * m.width
-                                 : (int64_t)m.hidden * n_sp * (m.width + m.width / 32);
+    return m.width >= kWideWidth && m.dtype == PRENOM_F32 ? 2 * (int64_t)m.hidden * n_s * m.width : 0;
 }
 int mlp_bwd_waves(int64_t n_samples);  // partial-gradient slots (one per block) the bwd writes
-// act: activation/delta buffer of mlp_act_floats floats (128-wide MLPs; else unused)
+// act: activation/delta buffer of mlp_act_floats floats (128-wide FP32 MLPs; else unused)
 hipError_t launch_mlp_fwd(const MlpShape& m, const float* w, const float* y, int64_t n_s, float* sc, float* act,
                           hipStream_t s);
 hipError_t launch_mlp_bwd(const MlpShape& m, const float* w, const float* y, const float* dout, const float* sc,
                           int64_t n_s, float* dy, float* partial, float* act, hipStream_t s);
-hipError_t launch_mlp_fwd_lp(const MlpShape& m, const float* w, const float* y, int64_t n_s, float* sc, float* act,
+hipError_t launch_mlp_fwd_lp(const MlpShape& m, const float* w, const float* y, int64_t n_s, float* sc,
                              hipStream_t s);
 hipError_t launch_mlp_bwd_lp(const MlpShape& m, const float* w, const float* y, const float* dout, const float* sc,
-                             int64_t n_s, float* dy, float* partial, float* act, hipStream_t s);
+                             int64_t n_s, float* dy, float* partial, hipStream_t s);
 hipError_t launch_mlp_fwd_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
                                 const float* y, float* sc, float* act, hipStream_t s);
 hipError_t launch_mlp_bwd_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
                                 const float* y, const float* dout, const float* sc, float* dy, float* partial,
                                 int64_t slot_stride, float* act, hipStream_t s);
 hipError_t launch_mlp_fwd_lp_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
-                                   const float* y, float* sc, float* act, hipStream_t s);
+                                   const float* y, float* sc, hipStream_t s);
 hipError_t launch_mlp_bwd_lp_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
                                    const float* y, const float* dout, const float* sc, float* dy, float* partial,
-                                   int64_t slot_stride, float* act, hipStream_t s);
+                                   int64_t slot_stride, hipStream_t s);
 hipError_t launch_reduce_partials(const float* partial, int n_slots, int64_t n_mlp, float* g_mlp,
                                   hipStream_t s);
 

@@ -68,15 +68,16 @@ __device__ __forceinline__ floatx4 unpack(typename P::vec v)
     return {P::back(v[0]), P::back(v[1]), P::back(v[2]), P::back(v[3])};
 }
 
-// ReLU masks of the 128-wide MLP, kept beside its stored activations as bits
-// (the decision of the FP32 pre-activation, whatever the 16-bit activation
-// rounds to): one 32-bit word per (layer, sample, lane group q), bit 4 to + r
-// for neuron 16 to + 4 q + r.  The backward chain reads these 16 bytes per
-// sample and layer instead of the 256-byte activation row.
-__device__ __forceinline__ uint32_t relu_mask_bits(const floatx4* h, int n_tiles)
+// ReLU decisions of one sample and lane group q as bits: bit 4 to + r for neuron
+// 16 to + 4 q + r (the decision of the FP32 pre-activation, whatever the 16-bit
+// activation rounds to).
+template <int OT>
+__device__ __forceinline__ uint32_t relu_mask_bits(const floatx4 (&h)[OT])
 {
+    static_assert(4 * OT <= 32, "mask bits per lane");
     uint32_t m = 0;
-    for (int to = 0; to < n_tiles; ++to)
+#pragma unroll
+    for (int to = 0; to < OT; ++to)
 #pragma unroll
         for (int r = 0; r < 4; ++r) m |= (h[to][r] > 0.0f ? 1u : 0u) << (4 * to + r);
     return m;
@@ -86,31 +87,6 @@ __device__ __forceinline__ floatx4 mask_by_bits(floatx4 g, uint32_t m, int to)
 {
     return {(m >> (4 * to)) & 1u ? g[0] : 0.0f, (m >> (4 * to + 1)) & 1u ? g[1] : 0.0f,
             (m >> (4 * to + 2)) & 1u ? g[2] : 0.0f, (m >> (4 * to + 3)) & 1u ? g[3] : 0.0f};
-}
-
-// Layout of the 128-wide MLP's activation buffer (mlp_act_floats floats):
-// the activations, then the deltas, of every hidden layer in the MFMA type,
-// each in the accumulator layout of its 16-sample tiles (for layer k, tile
-// t, neuron tile to: 64 groups of 4 values, group 16 q + j holding neurons
-// 16 to + 4 q .. + 3 of sample 16 t + j, so one wave's store of a neuron tile
-// is 512 contiguous bytes); then the ReLU mask words [D][n_s][4].
-template <int W>
-__device__ __forceinline__ int64_t wide_vec(int k, int64_t n_s, int64_t s, int to, int q)
-{
-    const int64_t n_t = (n_s + 15) >> 4;
-    return (((int64_t)k * n_t + (s >> 4)) * (W / 16) + to) * 64 + q * 16 + (s & 15);
-}
-
-template <int W, int D, class P>
-__device__ __forceinline__ typename P::vec* wide_deltas(typename P::vec* a16, int64_t n_s)
-{
-    return a16 + (int64_t)D * ((n_s + 15) >> 4) * 4 * W;
-}
-
-template <int W, int D, class P>
-__device__ __forceinline__ uint32_t* wide_masks(typename P::vec* a16, int64_t n_s)
-{
-    return reinterpret_cast<uint32_t*>(a16 + (int64_t)2 * D * ((n_s + 15) >> 4) * 4 * W);
 }
 
 template <int IN, int W, int D>
@@ -190,8 +166,8 @@ __device__ __forceinline__ void load_inputs_lp(const float2* __restrict__ y, int
 
 // acc[to] = sum_ti A(fragment f0 + to * stride + ti) x b[ti], K-blocks outer
 // and output tiles inner (independent accumulators interleave), with a
-// scheduling fence every 4 K-blocks so fragment loads are not all hoisted.
-template <class P, int OT, int KT>
+// scheduling fence every kFence K-blocks so fragment loads are not all hoisted.
+template <class P, int OT, int KT, int kFence = 4>
 __device__ __forceinline__ void layer_lp_ks_outer(const typename P::vec* __restrict__ frag, int lane, int f0, int stride,
                                                   const typename P::vec (&b)[KT], floatx4 (&acc)[OT])
 {
@@ -201,7 +177,7 @@ __device__ __forceinline__ void layer_lp_ks_outer(const typename P::vec* __restr
     for (int ti = 0; ti < KT; ++ti) {
 #pragma unroll
         for (int to = 0; to < OT; ++to) acc[to] = P::mma(frag[(f0 + to * stride + ti) * 64 + lane], b[ti], acc[to]);
-        if ((ti & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        if (ti % kFence == kFence - 1) __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -256,7 +232,7 @@ __device__ __forceinline__ void chain_lp(const typename P::vec* __restrict__ fra
 template <int IN, int W, int D, class P>
 __device__ __forceinline__ void mlp_fwd_tiles_lp(const typename P::vec* __restrict__ frag,
                                                  const float2* __restrict__ y, int64_t n_s, float4* __restrict__ sc,
-                                                 float* __restrict__ act, int64_t tile0, int64_t end, int64_t step)
+                                                 int64_t tile0, int64_t end, int64_t step)
 {
     using N = NetLp<IN, W, D>;
     const int lane = threadIdx.x & 63, q = lane >> 4, j = lane & 15;
@@ -274,22 +250,12 @@ __device__ __forceinline__ void mlp_fwd_tiles_lp(const typename P::vec* __restri
         floatx4 o;
         chain_lp<IN, W, D, P>(frag, lane, yf, hs, o);
         if (q == 0 && valid) sc[s] = make_float4(__expf(o[0]), sigmoidf_(o[1]), sigmoidf_(o[2]), sigmoidf_(o[3]));
-        if (act && valid) {  // stored already rounded: the values every later use sees
-            typename P::vec* a16 = reinterpret_cast<typename P::vec*>(act);
-            uint32_t* masks = wide_masks<W, D, P>(a16, n_s);
-#pragma unroll
-            for (int k = 0; k < D; ++k) {
-#pragma unroll
-                for (int to = 0; to < N::OT; ++to) a16[wide_vec<W>(k, n_s, s, to, q)] = pack<P>(hs[k][to]);
-                masks[((int64_t)k * n_s + s) * 4 + q] = relu_mask_bits(hs[k], N::OT);
-            }
-        }
     }
 }
 
 template <int IN, int W, int D, class P>
 __global__ __launch_bounds__(256) void k_mlp_fwd_lp(const float* __restrict__ w, const float2* __restrict__ y,
-                                                    int64_t n_s, float4* __restrict__ sc, float* __restrict__ act)
+                                                    int64_t n_s, float4* __restrict__ sc)
 {
     using N = NetLp<IN, W, D>;
     extern __shared__ __align__(16) unsigned char smem_f[];
@@ -298,7 +264,7 @@ __global__ __launch_bounds__(256) void k_mlp_fwd_lp(const float* __restrict__ w,
     __syncthreads();
     const int64_t wave0 = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
     const int64_t n_waves = (int64_t)gridDim.x * (blockDim.x / 64);
-    mlp_fwd_tiles_lp<IN, W, D, P>(frag, y, n_s, sc, act, wave0, (n_s + 15) / 16, n_waves);
+    mlp_fwd_tiles_lp<IN, W, D, P>(frag, y, n_s, sc, wave0, (n_s + 15) / 16, n_waves);
 }
 
 // Three waves per SIMD: without the hint the 128-wide shapes take 154 VGPRs
@@ -308,7 +274,7 @@ __global__ __launch_bounds__(256) void k_mlp_fwd_lp(const float* __restrict__ w,
 template <int IN, int W, int D, class P>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_mlp_fwd_lp_batch(
     const MlpWork* __restrict__ work, const float* __restrict__ params, const float2* __restrict__ y,
-    float4* __restrict__ sc, float* __restrict__ act)
+    float4* __restrict__ sc)
 {
     using N = NetLp<IN, W, D>;
     extern __shared__ __align__(16) unsigned char smem_f[];
@@ -316,7 +282,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     const MlpWork wk = work[blockIdx.x];
     load_fragments_lp<IN, W, D, P>(params + wk.w_off, frag, N::N_FWD);
     __syncthreads();
-    mlp_fwd_tiles_lp<IN, W, D, P>(frag, y + wk.y_off / 2, wk.n_s, sc + wk.s_off, act ? act + wk.a_off : nullptr,
+    mlp_fwd_tiles_lp<IN, W, D, P>(frag, y + wk.y_off / 2, wk.n_s, sc + wk.s_off,
                                   wk.tile_begin + (threadIdx.x >> 6), wk.tile_end, blockDim.x / 64);
 }
 
@@ -514,392 +480,248 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd_lp_batch(const MlpWo
 }
 
 // ---------------------------------------------------------------- 128 wide
-// As in the FP32 form: the forward stores the hidden activations (in the
-// MFMA type, each unit's ReLU decision beside them as bits: relu_mask_bits); a chain
-// kernel with only the transposed fragments writes every layer's delta and
-// dy; a weight-gradient kernel contracts deltas with activations over the
-// block's samples (operands rounded to the MFMA type, FP32 accumulation),
-// the waves splitting the output rows.
-constexpr int kWideWavesLp = 4;
-constexpr int kDwThreadsLp = 64 * kWideWavesLp;
-
-// act16 / dlt16: the activations and deltas in the layout of wide_vec.
-template <int IN, int W, int D, class P>
-__device__ __forceinline__ void mlp_chain_bwd_tiles_lp(const typename P::vec* __restrict__ bfrag, const float4* __restrict__ sc,
-                                       const float4* __restrict__ dout, const typename P::vec* __restrict__ act16,
-                                       typename P::vec* __restrict__ dlt16, int64_t n_s, float2* __restrict__ dy,
-                                       int64_t tile0, int64_t end, int64_t step)
-{
-    using N = NetLp<IN, W, D>;
-    constexpr int BO = 0, BH = N::BH - N::N_FWD, B1 = N::B1 - N::N_FWD;
-    const int lane = threadIdx.x & 63, q = lane >> 4, j = lane & 15;
-    static_assert(N::OT * 4 <= 32, "mask bits per lane");
-    const uint32_t* masks = wide_masks<W, D, P>(const_cast<typename P::vec*>(act16), n_s);
-    // a tile's loads (head adjoint inputs on lanes q == 0, every layer's mask
-    // word), issued one tile ahead so they overlap the current tile's work
-    float4 gn = make_float4(0.0f, 0.0f, 0.0f, 0.0f), vn = gn;
-    uint32_t mn[D];
-    auto load_tile = [&](int64_t t) {
-        const int64_t st = t * 16 + j;
-        const bool ok = t < end && st < n_s;
-        gn = vn = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (ok && q == 0) {
-            gn = dout[st];
-            vn = sc[st];
-        }
-#pragma unroll
-        for (int k = 0; k < D; ++k) mn[k] = ok ? masks[((int64_t)k * n_s + st) * 4 + q] : 0u;
-    };
-    load_tile(tile0);
-    for (int64_t tile = tile0; tile < end; tile += step) {
-        const int64_t s = tile * 16 + j;
-        const bool valid = s < n_s;
-        const float4 g = gn, v = vn;
-        uint32_t mc[D];
-#pragma unroll
-        for (int k = 0; k < D; ++k) mc[k] = mn[k];
-        load_tile(tile + step);
-        const floatx4 dO = {g.x * v.x, g.y * v.y * (1.0f - v.y), g.z * v.z * (1.0f - v.z), g.w * v.w * (1.0f - v.w)};
-        const typename P::vec dOp = pack<P>(dO);
-        floatx4 delta[N::OT];
-        auto vi = [&](int k, int to) { return wide_vec<W>(k, n_s, s, to, q); };
-        auto mask_of = [&](int k) { return mc[k]; };
-        uint32_t mk = mask_of(D - 1);
-#pragma unroll
-        for (int to = 0; to < N::OT; ++to) {
-            floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            acc = P::mma(bfrag[(BO + to) * 64 + lane], dOp, acc);
-            delta[to] = mask_by_bits(acc, mk, to);
-            if (valid) dlt16[vi(D - 1, to)] = pack<P>(delta[to]);
-        }
-#pragma unroll
-        for (int k = D - 1; k >= 1; --k) {
-            mk = mask_of(k - 1);
-            typename P::vec dp[N::OT];
-#pragma unroll
-            for (int ti = 0; ti < N::OT; ++ti) dp[ti] = pack<P>(delta[ti]);
-            floatx4 nd[N::OT];
-            layer_lp_ks_outer<P, N::OT, N::OT>(bfrag, lane, BH + (k - 1) * N::OT * N::OT, N::OT, dp, nd);
-#pragma unroll
-            for (int to = 0; to < N::OT; ++to) {
-                delta[to] = mask_by_bits(nd[to], mk, to);
-                if (valid) dlt16[vi(k - 1, to)] = pack<P>(delta[to]);
-            }
-        }
-        typename P::vec dp[N::OT];
-#pragma unroll
-        for (int ti = 0; ti < N::OT; ++ti) dp[ti] = pack<P>(delta[ti]);
-        floatx4 gy[N::IT];
-        layer_lp_ks_outer<P, N::IT, N::OT>(bfrag, lane, B1, N::OT, dp, gy);
-#pragma unroll
-        for (int to = 0; to < N::IT; ++to) {
-            const int f = 16 * to + 4 * q;
-            if (valid && f < IN) {
-                dy[(int64_t)(f >> 1) * n_s + s] = make_float2(gy[to][0], gy[to][1]);
-                dy[(int64_t)((f >> 1) + 1) * n_s + s] = make_float2(gy[to][2], gy[to][3]);
-            }
-        }
-    }
-}
-
-// Weight gradient over samples [s_begin, s_end), staged kDwChunk samples at
-// a time in LDS: MFMA K = 16 consecutive samples (lane q holds samples
-// 4q .. 4q + 3 of the group of 16), operands rounded to the MFMA type.
-// The chunk of samples is staged in 16-bit form, neuron-major: row n of a
-// staged array holds neuron (or feature) n of the chunk's kDwChunk samples,
-// so the 4 consecutive samples an MFMA operand needs in a lane are one 8-byte
-// LDS read.  Rows are padded to kDwRowLp halfwords (80 bytes) to spread the 16
-// rows a wave reads over the banks.  Layout, in halfwords:
-//   DL [D][W][row]  deltas      AC [D][W][row]  activations
-//   Y  [32][row]    inputs (rows >= IN zero)
-//   DO [16][row]    head adjoint (rows >= 4 zero, written once)
-constexpr int kDwRowLp = kDwChunk + 8;
-
-template <int W, int D>
-struct DwStageLp {
-    static constexpr int DL = 0;
-    static constexpr int AC = DL + D * W * kDwRowLp;
-    static constexpr int Y = AC + D * W * kDwRowLp;
-    static constexpr int DO = Y + 32 * kDwRowLp;
-    static constexpr int HALVES = DO + 16 * kDwRowLp;
-};
-
-// 4 x 4 transpose of 16-bit values: in[r] holds columns 0..3 of row r (two
-// per 32-bit word); out[c] holds rows 0..3 of column c.
-__device__ __forceinline__ void transpose4x4_16(const uint2 (&in)[4], uint2 (&out)[4])
-{
-    out[0] = make_uint2((in[0].x & 0xffffu) | (in[1].x << 16), (in[2].x & 0xffffu) | (in[3].x << 16));
-    out[1] = make_uint2((in[0].x >> 16) | (in[1].x & 0xffff0000u), (in[2].x >> 16) | (in[3].x & 0xffff0000u));
-    out[2] = make_uint2((in[0].y & 0xffffu) | (in[1].y << 16), (in[2].y & 0xffffu) | (in[3].y << 16));
-    out[3] = make_uint2((in[0].y >> 16) | (in[1].y & 0xffff0000u), (in[2].y >> 16) | (in[3].y & 0xffff0000u));
-}
-
-template <class P>
-__device__ __forceinline__ uint2 bits(typename P::vec v)
-{
-    return __builtin_bit_cast(uint2, v);
-}
-
-// Staging of samples [s0, min(s0 + kDwChunk, s_end)) (zeros past the end),
-// in two halves so the next chunk's global loads overlap the current chunk's
-// MFMAs: dw_load_lp reads a thread's share into registers, dw_store_lp
-// writes it to LDS.  act16 / dlt16: as laid out by wide_vec; y: level-major
-// [L][n_s][2].  kDwThreadsLp threads.
-template <int W, int D>
-struct DwRegsLp {
-    static constexpr int SG = kDwChunk / 4;              // 4-sample groups per chunk
-    static constexpr int V = W / 4;                      // 4-neuron groups per row
-    static constexpr int N_AD = 2 * D * SG * V;          // 4 x 4 blocks of deltas and activations
-    static constexpr int PER = (N_AD + kDwThreadsLp - 1) / kDwThreadsLp;
-    uint2 ad[PER][4];  // rows r = 0..3 (samples) of each block
-    float2 yv[4];      // features 2l, 2l + 1 of 4 samples (threads < 16 SG)
-    float4 g, v;       // head adjoint inputs of one sample (threads < kDwChunk)
-};
-
-template <int IN, int W, int D, class P>
-__device__ __forceinline__ void dw_load_lp(DwRegsLp<W, D>& R, const float* __restrict__ y,
-                                           const float4* __restrict__ sc, const float4* __restrict__ dout,
-                                           const typename P::vec* __restrict__ act16,
-                                           const typename P::vec* __restrict__ dlt16, int64_t n_s, int64_t s0,
-                                           int64_t s_end)
-{
-    using Rg = DwRegsLp<W, D>;
-#pragma unroll
-    for (int u = 0; u < Rg::PER; ++u) {
-        const int i = threadIdx.x + kDwThreadsLp * u;
-        const int arr = i / (D * Rg::SG * Rg::V), rem = i % (D * Rg::SG * Rg::V);
-        const int k = rem / (Rg::SG * Rg::V), r2 = rem % (Rg::SG * Rg::V), sg = r2 / Rg::V, c = r2 % Rg::V;
-        const typename P::vec* src = arr == 0 ? dlt16 : act16;
-        // the 4 samples of the group are consecutive in one tile: two 16-byte loads
-        const int64_t sb = s0 + 4 * sg;
-        uint4 w0 = make_uint4(0u, 0u, 0u, 0u), w1 = w0;
-        if (i < Rg::N_AD && sb < s_end) {
-            const uint4* p = reinterpret_cast<const uint4*>(src + wide_vec<W>(k, n_s, sb, c >> 2, c & 3));
-            w0 = p[0];
-            w1 = p[1];
-        }
-        R.ad[u][0] = sb < s_end ? make_uint2(w0.x, w0.y) : make_uint2(0u, 0u);
-        R.ad[u][1] = sb + 1 < s_end ? make_uint2(w0.z, w0.w) : make_uint2(0u, 0u);
-        R.ad[u][2] = sb + 2 < s_end ? make_uint2(w1.x, w1.y) : make_uint2(0u, 0u);
-        R.ad[u][3] = sb + 3 < s_end ? make_uint2(w1.z, w1.w) : make_uint2(0u, 0u);
-    }
-    {
-        const int l = threadIdx.x / Rg::SG, sg = threadIdx.x % Rg::SG;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t s = s0 + 4 * sg + r;
-            R.yv[r] = threadIdx.x < 16 * Rg::SG && s < s_end && 2 * l < IN
-                          ? reinterpret_cast<const float2*>(y)[(int64_t)l * n_s + s]
-                          : make_float2(0.0f, 0.0f);
-        }
-    }
-    {
-        const int64_t s = s0 + threadIdx.x;
-        const bool ok = threadIdx.x < kDwChunk && s < s_end;
-        R.g = ok ? dout[s] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        R.v = ok ? sc[s] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
-}
-
-template <int IN, int W, int D, class P>
-__device__ __forceinline__ void dw_store_lp(uint16_t* __restrict__ lds, const DwRegsLp<W, D>& R)
-{
-    using St = DwStageLp<W, D>;
-    using Rg = DwRegsLp<W, D>;
-    // activations and deltas: one 4 x 4 block (4 samples x 4 neurons) per item
-#pragma unroll
-    for (int u = 0; u < Rg::PER; ++u) {
-        const int i = threadIdx.x + kDwThreadsLp * u;
-        if (i < Rg::N_AD) {
-            const int arr = i / (D * Rg::SG * Rg::V), rem = i % (D * Rg::SG * Rg::V);
-            const int k = rem / (Rg::SG * Rg::V), r2 = rem % (Rg::SG * Rg::V), sg = r2 / Rg::V, c = r2 % Rg::V;
-            uint2 out[4];
-            transpose4x4_16(R.ad[u], out);
-            uint16_t* base = lds + (arr == 0 ? St::DL : St::AC) + (k * W + 4 * c) * kDwRowLp + 4 * sg;
-#pragma unroll
-            for (int n = 0; n < 4; ++n) *reinterpret_cast<uint2*>(base + n * kDwRowLp) = out[n];
-        }
-    }
-    // inputs: features 2l, 2l + 1 of 4 samples per item (rounded to P)
-    if (threadIdx.x < 16 * Rg::SG) {
-        const int l = threadIdx.x / Rg::SG, sg = threadIdx.x % Rg::SG;
-        uint16_t* base = lds + St::Y + (2 * l) * kDwRowLp + 4 * sg;
-        *reinterpret_cast<uint2*>(base) = bits<P>(pack<P>(R.yv[0].x, R.yv[1].x, R.yv[2].x, R.yv[3].x));
-        *reinterpret_cast<uint2*>(base + kDwRowLp) = bits<P>(pack<P>(R.yv[0].y, R.yv[1].y, R.yv[2].y, R.yv[3].y));
-    }
-    // head adjoint (d sigma / d o0 = sigma, d c / d o = c (1 - c)) of one sample
-    if (threadIdx.x < kDwChunk) {
-        const float4 g = R.g, v = R.v;
-        const float o[4] = {g.x * v.x, g.y * v.y * (1.0f - v.y), g.z * v.z * (1.0f - v.z), g.w * v.w * (1.0f - v.w)};
-#pragma unroll
-        for (int n = 0; n < 4; ++n)
-            lds[St::DO + n * kDwRowLp + threadIdx.x] = __builtin_bit_cast(uint16_t, P::cvt(o[n]));
-    }
-}
-
-// Weight gradient over samples [s_begin, s_end): dW = sum_s delta(s) h(s)^T
-// per layer, MFMA K = 16 consecutive samples (lane q holds samples
-// 4q .. 4q + 3 of the group of 16), operands rounded to the MFMA type, the 4
-// waves splitting the output rows.  One partial per block.
-template <int IN, int W, int D, class P>
-__device__ __forceinline__ void mlp_dw_range_lp(uint16_t* __restrict__ lds, const float* __restrict__ y, const float4* __restrict__ sc,
-                                const float4* __restrict__ dout, const typename P::vec* __restrict__ act16,
-                                const typename P::vec* __restrict__ dlt16, int64_t n_s, int64_t s_begin,
-                                int64_t s_end, float* __restrict__ dst)
-{
-    using N = NetLp<IN, W, D>;
-    using St = DwStageLp<W, D>;
-    constexpr int RT = N::OT / kWideWavesLp;
-    static_assert(N::OT % kWideWavesLp == 0 && IN <= 32 && N::IT <= 2, "rows per wave, inputs");
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, j = lane & 15;
-    floatx4 aH[D > 1 ? D - 1 : 1][RT][N::OT], a1[RT][N::IT], aO[RT];
-#pragma unroll
-    for (int a = 0; a < RT; ++a) {
-        aO[a] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int t = 0; t < N::IT; ++t) a1[a][t] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int k = 0; k < (D > 1 ? D - 1 : 1); ++k)
-#pragma unroll
-            for (int t = 0; t < N::OT; ++t) aH[k][a][t] = {0.0f, 0.0f, 0.0f, 0.0f};
-    }
-    // rows 4..15 of the head adjoint stay zero (the A operand of the head's
-    // 16-row tile); rows 0..3 are restaged with every chunk
-    for (int i = threadIdx.x; i < 12 * kDwRowLp; i += blockDim.x) lds[St::DO + 4 * kDwRowLp + i] = 0;
-    // 4 samples of staged row `row`, as an MFMA operand
-    auto op = [&](int base, int row, int k0) {
-        return __builtin_bit_cast(typename P::vec, *reinterpret_cast<const uint2*>(lds + base + row * kDwRowLp + k0));
-    };
-    static_assert(kDwThreadsLp >= 16 * (kDwChunk / 4) && kDwThreadsLp >= kDwChunk, "staging threads");
-    DwRegsLp<W, D> R;
-    if (s_begin < s_end) dw_load_lp<IN, W, D, P>(R, y, sc, dout, act16, dlt16, n_s, s_begin, s_end);
-    for (int64_t c0 = s_begin; c0 < s_end; c0 += kDwChunk) {
-        dw_store_lp<IN, W, D, P>(lds, R);
-        __syncthreads();
-        if (c0 + kDwChunk < s_end) dw_load_lp<IN, W, D, P>(R, y, sc, dout, act16, dlt16, n_s, c0 + kDwChunk, s_end);
-#pragma unroll 1
-        for (int ks = 0; ks < kDwChunk / 16; ++ks) {  // not unrolled: bounds the operands in flight
-            const int k0 = 16 * ks + 4 * q;
-            const typename P::vec dOp = op(St::DO, j, k0);
-#pragma unroll
-            for (int a = 0; a < RT; ++a)
-                aO[a] = P::mma(dOp, op(St::AC + (D - 1) * W * kDwRowLp, 16 * (RT * wave + a) + j, k0), aO[a]);
-#pragma unroll
-            for (int k = 1; k < D; ++k) {
-                typename P::vec av[RT];
-#pragma unroll
-                for (int a = 0; a < RT; ++a) av[a] = op(St::DL + k * W * kDwRowLp, 16 * (RT * wave + a) + j, k0);
-#pragma unroll
-                for (int t = 0; t < N::OT; ++t) {
-                    const typename P::vec bv = op(St::AC + (k - 1) * W * kDwRowLp, 16 * t + j, k0);
-#pragma unroll
-                    for (int a = 0; a < RT; ++a) aH[k - 1][a][t] = P::mma(av[a], bv, aH[k - 1][a][t]);
-                }
-            }
-            {
-                typename P::vec av[RT], bv[N::IT];
-#pragma unroll
-                for (int a = 0; a < RT; ++a) av[a] = op(St::DL, 16 * (RT * wave + a) + j, k0);
-#pragma unroll
-                for (int t = 0; t < N::IT; ++t) bv[t] = op(St::Y, 16 * t + j, k0);
-#pragma unroll
-                for (int a = 0; a < RT; ++a)
-#pragma unroll
-                    for (int t = 0; t < N::IT; ++t) a1[a][t] = P::mma(av[a], bv[t], a1[a][t]);
-            }
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int a = 0; a < RT; ++a)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 16 * (RT * wave + a) + 4 * q + r;
-#pragma unroll
-            for (int t = 0; t < N::IT; ++t) {
-                const int col = 16 * t + j;
-                if (col < IN) dst[N::OFF_W1 + row * IN + col] = a1[a][t][r];
-            }
-#pragma unroll
-            for (int k = 1; k < D; ++k)
-#pragma unroll
-                for (int t = 0; t < N::OT; ++t) dst[N::OFF_H + (k - 1) * W * W + row * W + 16 * t + j] = aH[k - 1][a][t][r];
-            if (q == 0) dst[N::OFF_OUT + r * W + 16 * (RT * wave + a) + j] = aO[a][r];
-        }
-}
+// The 128-wide backward is one kernel: a block takes its samples 128 at a time,
+// one 16-sample tile per wave, recomputes the forward, runs the transposed chain
+// and accumulates the weight gradient, whose operands (four consecutive samples
+// of a neuron) go through LDS: deltas and activations of the 128 samples in the
+// MFMA type, neuron-major.  The waves split the output rows, 16 each, so the
+// block's partial is written without a merge.  Forward and transposed fragments
+// (86 KB with two layers) and the two staged arrays (68 KB) fill a CU's LDS.
+// Nothing but the features, the head outputs and their adjoint is read: storing
+// the activations in the forward and the deltas between a chain and a
+// weight-gradient kernel moved 2.5 KB a sample and ran at the HBM's rate (48
+// objects, 28.5 M samples 128 wide: forward 4.0 and backward 10.3 ms).
+constexpr int kWideWavesLp = 8;
+constexpr int kWideChunk = 16 * kWideWavesLp;  // samples staged at a time
+constexpr int kWidePitch = kWideChunk + 8;     // halfwords per staged row: 272 bytes, so that a
+                                               // half wave's 8-byte reads of 16 rows miss each other's banks
 
 template <int IN, int W, int D>
-constexpr size_t dw_lds_bytes_lp()
-{
-    return sizeof(uint16_t) * (size_t)DwStageLp<W, D>::HALVES;
-}
+struct WideLdsLp {
+    using N = NetLp<IN, W, D>;
+    static constexpr int N_FRAG = N::FO + (N::N_ALL - N::N_FWD);  // hidden forward fragments, then the transposed ones
+    // staged rows, in halfwords from the end of the fragments
+    static constexpr int A = 0;
+    static constexpr int B = A + W * kWidePitch;
+    static constexpr int DO = B + W * kWidePitch;           // head adjoint, 4 rows
+    static constexpr int Y = D == 1 ? DO + 4 * kWidePitch : B;  // inputs: beside the others, or in place of B
+    static constexpr int HALVES = D == 1 ? Y + 16 * N::IT * kWidePitch : DO + 4 * kWidePitch;
+    static constexpr size_t BYTES = (size_t)N_FRAG * 512 + sizeof(uint16_t) * (size_t)HALVES;
+    static_assert(BYTES <= 160 * 1024 && (IN <= 32 && D <= 2), "LDS of one CU");
+};
 
+// Tiles [tile0, tile1) of one object: dy of their samples and their share of
+// the weight gradient to dst.  Called by every thread of the block.
 template <int IN, int W, int D, class P>
-__global__ __launch_bounds__(256) void k_mlp_chain_bwd_lp(const float* __restrict__ w, const float4* __restrict__ sc,
-                                                          const float4* __restrict__ dout, float* __restrict__ act,
-                                                          int64_t n_s, float2* __restrict__ dy)
+__device__ __forceinline__ void mlp_wide_bwd_lp(unsigned char* __restrict__ smem, const float* __restrict__ w,
+                                                const float2* __restrict__ y, const float4* __restrict__ sc,
+                                                const float4* __restrict__ dout, int64_t n_s, float2* __restrict__ dy,
+                                                float* __restrict__ dst, int64_t tile0, int64_t tile1)
 {
     using N = NetLp<IN, W, D>;
-    extern __shared__ __align__(16) unsigned char smem_b[];
-    typename P::vec* frag = reinterpret_cast<typename P::vec*>(smem_b);
-    load_fragments_lp<IN, W, D, P>(w, frag, N::N_ALL - N::N_FWD, N::N_FWD);
+    using L = WideLdsLp<IN, W, D>;
+    using vec = typename P::vec;
+    constexpr int kFence = 2;  // (four would spill)
+    static_assert(N::OT == kWideWavesLp, "one row tile per wave");
+    vec* ffrag = reinterpret_cast<vec*>(smem);
+    vec* bfrag = ffrag + N::FO * 64;
+    uint16_t* st = reinterpret_cast<uint16_t*>(smem + (size_t)L::N_FRAG * 512);
+    constexpr int BO = 0, BH = N::BH - N::N_FWD, B1 = N::B1 - N::N_FWD;  // rebased to bfrag
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, j = lane & 15;
+    load_fragments_lp<IN, W, D, P>(w, ffrag, N::FO);
+    load_fragments_lp<IN, W, D, P>(w, bfrag, N::N_ALL - N::N_FWD, N::N_FWD);
+    const int col = 16 * wave + j;  // the lane's sample within the chunk
+    // rows 16 t + 4 q + r of a staged array: the lane's values of sample `col`
+    auto put = [&](int base, int t, vec v) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const auto x = v[r];
+            st[base + (16 * t + 4 * q + r) * kWidePitch + col] = __builtin_bit_cast(uint16_t, x);
+        }
+    };
+    // samples k0 .. k0 + 3 of row `row`: an MFMA operand
+    auto op = [&](int base, int row, int k0) {
+        return __builtin_bit_cast(vec, *reinterpret_cast<const uint2*>(st + base + row * kWidePitch + k0));
+    };
+    floatx4 aH[N::OT], a1[N::IT], aO = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int t = 0; t < N::OT; ++t) aH[t] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int t = 0; t < N::IT; ++t) a1[t] = {0.0f, 0.0f, 0.0f, 0.0f};
+    // W_out: A[i][k] = dO_i (rows i >= 4 zero), B = the last layer's activations
+    auto add_out = [&](int hbase) {
+#pragma unroll 2
+        for (int ks = 0; ks < kWideChunk / 16; ++ks) {
+            const int k0 = 16 * ks + 4 * q;
+            vec d = op(L::DO, j & 3, k0);
+            if (j >= 4) d = pack<P>(0.0f, 0.0f, 0.0f, 0.0f);
+            aO = P::mma(d, op(hbase, 16 * wave + j, k0), aO);
+        }
+    };
+    auto add_in = [&](int dbase) {  // W_1
+#pragma unroll 2
+        for (int ks = 0; ks < kWideChunk / 16; ++ks) {
+            const int k0 = 16 * ks + 4 * q;
+            const vec av = op(dbase, 16 * wave + j, k0);
+#pragma unroll
+            for (int t = 0; t < N::IT; ++t) a1[t] = P::mma(av, op(L::Y, 16 * t + j, k0), a1[t]);
+        }
+    };
+    // the next tile's inputs, upstream gradient and head outputs, loaded while
+    // the current tile runs (lanes q == 0 hold the head's four outputs)
+    floatx4 yn[N::KB1];
+    float4 gn, vn;
+    auto load_tile = [&](int64_t t) {
+        const int64_t s = t * 16 + j;
+        const bool ok = t < tile1 && s < n_s;
+        load_inputs_lp<IN, N::KB1>(y, n_s, s, ok, q, yn);
+        gn = vn = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (ok && q == 0) {
+            gn = dout[s];
+            vn = sc[s];
+        }
+    };
+    load_tile(tile0 + wave);
     __syncthreads();
-    const int64_t wave0 = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-    typename P::vec* a16 = reinterpret_cast<typename P::vec*>(act);
-    mlp_chain_bwd_tiles_lp<IN, W, D, P>(frag, sc, dout, a16, wide_deltas<W, D, P>(a16, n_s), n_s, dy, wave0,
-                                        (n_s + 15) / 16, (int64_t)gridDim.x * (blockDim.x / 64));
+    for (int64_t c0 = tile0; c0 < tile1; c0 += kWideWavesLp) {
+        const int64_t tile = c0 + wave, s = tile * 16 + j;
+        const bool valid = tile < tile1 && s < n_s;
+        vec yp[N::KB1], hp[D][N::OT];
+        uint32_t mask[D];
+#pragma unroll
+        for (int m = 0; m < N::KB1; ++m) yp[m] = pack<P>(yn[m]);
+        const float4 g = gn, v = vn;
+        load_tile(tile + kWideWavesLp);
+        floatx4 acc[N::OT];
+        layer_lp_ks_outer<P, N::OT, N::KB1>(ffrag, lane, N::F1, N::KB1, yp, acc);
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            if (k > 0)
+                layer_lp_ks_outer<P, N::OT, N::OT, kFence>(ffrag, lane, N::FH + (k - 1) * N::OT * N::OT, N::OT, hp[k > 0 ? k - 1 : 0],
+                                                   acc);
+#pragma unroll
+            for (int to = 0; to < N::OT; ++to) acc[to] = relu4(acc[to]);
+            mask[k] = relu_mask_bits(acc);
+#pragma unroll
+            for (int to = 0; to < N::OT; ++to) hp[k][to] = pack<P>(acc[to]);
+        }
+        // head adjoint: d sigma / d o0 = sigma, d c / d o = c (1 - c)
+        const vec dO = pack<P>(g.x * v.x, g.y * v.y * (1.0f - v.y), g.z * v.z * (1.0f - v.z), g.w * v.w * (1.0f - v.w));
+        vec dp[N::OT];
+#pragma unroll
+        for (int to = 0; to < N::OT; ++to) {
+            const floatx4 d = P::mma(bfrag[(BO + to) * 64 + lane], dO, floatx4{0.0f, 0.0f, 0.0f, 0.0f});
+            dp[to] = pack<P>(mask_by_bits(d, mask[D - 1], to));
+        }
+        auto put_out = [&] {
+            if (q == 0) put(L::DO, 0, dO);
+        };
+        auto store_dy = [&] {
+            floatx4 gy[N::IT];
+            layer_lp_ks_outer<P, N::IT, N::OT, kFence>(bfrag, lane, B1, N::OT, dp, gy);
+#pragma unroll
+            for (int to = 0; to < N::IT; ++to) {
+                const int f = 16 * to + 4 * q;
+                if (valid && f < IN) {
+                    dy[(int64_t)(f >> 1) * n_s + s] = make_float2(gy[to][0], gy[to][1]);
+                    dy[(int64_t)((f >> 1) + 1) * n_s + s] = make_float2(gy[to][2], gy[to][3]);
+                }
+            }
+        };
+        __syncthreads();  // the previous chunk's operands have been read
+        if constexpr (D == 1) {
+#pragma unroll
+            for (int to = 0; to < N::OT; ++to) {
+                put(L::A, to, dp[to]);
+                put(L::B, to, hp[0][to]);
+            }
+#pragma unroll
+            for (int m = 0; m < N::KB1; ++m) put(L::Y, m, yp[m]);
+            put_out();
+            __syncthreads();
+            add_out(L::B);
+            store_dy();
+            add_in(L::A);
+        } else {
+            // the last activations in A until W_out's gradient has them, then the deltas
+#pragma unroll
+            for (int to = 0; to < N::OT; ++to) {
+                put(L::A, to, hp[D - 1][to]);
+                put(L::B, to, hp[0][to]);
+            }
+            put_out();
+            __syncthreads();
+            add_out(L::A);
+            layer_lp_ks_outer<P, N::OT, N::OT, kFence>(bfrag, lane, BH, N::OT, dp, acc);
+            __syncthreads();
+#pragma unroll
+            for (int to = 0; to < N::OT; ++to) {
+                put(L::A, to, dp[to]);
+                dp[to] = pack<P>(mask_by_bits(acc[to], mask[0], to));
+            }
+            __syncthreads();
+#pragma unroll 2
+            for (int ks = 0; ks < kWideChunk / 16; ++ks) {
+                const int k0 = 16 * ks + 4 * q;
+                const vec av = op(L::A, 16 * wave + j, k0);
+#pragma unroll
+                for (int t = 0; t < N::OT; ++t) aH[t] = P::mma(av, op(L::B, 16 * t + j, k0), aH[t]);
+            }
+            store_dy();
+            __syncthreads();
+#pragma unroll
+            for (int to = 0; to < N::OT; ++to) put(L::A, to, dp[to]);
+#pragma unroll
+            for (int m = 0; m < N::KB1; ++m) put(L::Y, m, yp[m]);
+            __syncthreads();
+            add_in(L::A);
+        }
+    }
+    // D layout: row 16 wave + 4 q + r, column 16 t + j
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = 16 * wave + 4 * q + r;
+#pragma unroll
+        for (int t = 0; t < N::IT; ++t)
+            if (16 * t + j < IN) dst[N::OFF_W1 + row * IN + 16 * t + j] = a1[t][r];
+        if constexpr (D > 1) {
+#pragma unroll
+            for (int t = 0; t < N::OT; ++t) dst[N::OFF_H + row * W + 16 * t + j] = aH[t][r];
+        }
+        if (q == 0) dst[N::OFF_OUT + r * W + 16 * wave + j] = aO[r];
+    }
 }
 
 template <int IN, int W, int D, class P>
-__global__ __launch_bounds__(256) void k_mlp_chain_bwd_lp_batch(const MlpWork* __restrict__ work,
-                                                                const float* __restrict__ params,
-                                                                const float4* __restrict__ sc,
-                                                                const float4* __restrict__ dout,
-                                                                float* __restrict__ act, float2* __restrict__ dy)
-{
-    using N = NetLp<IN, W, D>;
-    extern __shared__ __align__(16) unsigned char smem_b[];
-    typename P::vec* frag = reinterpret_cast<typename P::vec*>(smem_b);
-    const MlpWork wk = work[blockIdx.x];
-    load_fragments_lp<IN, W, D, P>(params + wk.w_off, frag, N::N_ALL - N::N_FWD, N::N_FWD);
-    __syncthreads();
-    typename P::vec* a16 = reinterpret_cast<typename P::vec*>(act + wk.a_off);
-    mlp_chain_bwd_tiles_lp<IN, W, D, P>(frag, sc + wk.s_off, dout + wk.s_off, a16, wide_deltas<W, D, P>(a16, wk.n_s),
-                                        wk.n_s, dy + wk.y_off / 2, wk.tile_begin + (threadIdx.x >> 6), wk.tile_end,
-                                        blockDim.x / 64);
-}
-
-template <int IN, int W, int D, class P>
-__global__ __launch_bounds__(64 * kWideWavesLp) void k_mlp_dw_lp(const float* __restrict__ y,
-                                                                 const float4* __restrict__ sc,
-                                                                 const float4* __restrict__ dout,
-                                                                 const float* __restrict__ act, int64_t n_s,
-                                                                 int64_t tiles_per_block, float* __restrict__ partial)
-{
-    using N = NetLp<IN, W, D>;
-    extern __shared__ __align__(16) uint16_t dw_lds[];
-    const int64_t b = (int64_t)blockIdx.x * tiles_per_block * 16;
-    const int64_t e = min(b + tiles_per_block * 16, n_s);
-    const typename P::vec* a16 = reinterpret_cast<const typename P::vec*>(act);
-    mlp_dw_range_lp<IN, W, D, P>(dw_lds, y, sc, dout, a16, wide_deltas<W, D, P>(const_cast<typename P::vec*>(a16), n_s), n_s, b, e,
-                                 partial + (int64_t)blockIdx.x * N::N_PARAMS);
-}
-
-template <int IN, int W, int D, class P>
-__global__ __launch_bounds__(64 * kWideWavesLp) void k_mlp_dw_lp_batch(const MlpWork* __restrict__ work,
-                                                                       const float* __restrict__ y,
+__global__ __launch_bounds__(64 * kWideWavesLp) void k_mlp_wide_bwd_lp(const float* __restrict__ w,
+                                                                       const float2* __restrict__ y,
                                                                        const float4* __restrict__ sc,
-                                                                       const float4* __restrict__ dout,
-                                                                       const float* __restrict__ act,
-                                                                       float* __restrict__ partial, int64_t slot_stride)
+                                                                       const float4* __restrict__ dout, int64_t n_s,
+                                                                       int64_t tiles_per_block,
+                                                                       float2* __restrict__ dy,
+                                                                       float* __restrict__ partial)
 {
-    extern __shared__ __align__(16) uint16_t dw_lds[];
+    extern __shared__ __align__(16) unsigned char smem_w[];
+    const int64_t n_t = (n_s + 15) / 16, t0 = min((int64_t)blockIdx.x * tiles_per_block, n_t);
+    mlp_wide_bwd_lp<IN, W, D, P>(smem_w, w, y, sc, dout, n_s, dy, partial + (int64_t)blockIdx.x * NetLp<IN, W, D>::N_PARAMS,
+                                 t0, min(t0 + tiles_per_block, n_t));
+}
+
+template <int IN, int W, int D, class P>
+__global__ __launch_bounds__(64 * kWideWavesLp) void k_mlp_wide_bwd_lp_batch(const MlpWork* __restrict__ work,
+                                                                             const float* __restrict__ params,
+                                                                             const float* __restrict__ y,
+                                                                             const float4* __restrict__ sc,
+                                                                             const float4* __restrict__ dout,
+                                                                             float2* __restrict__ dy,
+                                                                             float* __restrict__ partial,
+                                                                             int64_t slot_stride)
+{
+    extern __shared__ __align__(16) unsigned char smem_w[];
     const MlpWork wk = work[blockIdx.x];
-    const int64_t b = wk.tile_begin * 16, e = min(wk.tile_end * 16, wk.n_s);
-    const typename P::vec* a16 = reinterpret_cast<const typename P::vec*>(act + wk.a_off);
-    mlp_dw_range_lp<IN, W, D, P>(dw_lds, y + wk.y_off, sc + wk.s_off, dout + wk.s_off, a16,
-                                 wide_deltas<W, D, P>(const_cast<typename P::vec*>(a16), wk.n_s), wk.n_s, b, e,
-                                 partial + (int64_t)blockIdx.x * slot_stride);
+    mlp_wide_bwd_lp<IN, W, D, P>(smem_w, params + wk.w_off, reinterpret_cast<const float2*>(y + wk.y_off), sc + wk.s_off,
+                                 dout + wk.s_off, wk.n_s, dy + wk.y_off / 2, partial + (int64_t)blockIdx.x * slot_stride,
+                                 wk.tile_begin, wk.tile_end);
 }
 
 template <class K>
@@ -916,12 +738,6 @@ size_t fwd_lds_lp()
 }
 
 template <int IN, int W, int D, class P>
-size_t chain_lds_lp()
-{
-    return sizeof(typename P::vec) * (size_t)(NetLp<IN, W, D>::N_ALL - NetLp<IN, W, D>::N_FWD) * 64;
-}
-
-template <int IN, int W, int D, class P>
 size_t bwd_lds_lp()
 {
     return sizeof(typename P::vec) * (size_t)NetLp<IN, W, D>::N_ALL * 64 +
@@ -929,7 +745,7 @@ size_t bwd_lds_lp()
 }
 
 template <int IN, int W, int D, class P>
-hipError_t fwd_lp(const float* w, const float* y, int64_t n_s, float* sc, float* act, hipStream_t s)
+hipError_t fwd_lp(const float* w, const float* y, int64_t n_s, float* sc, hipStream_t s)
 {
     const int64_t n_tiles = (n_s + 15) / 16;
     int64_t blocks = (n_tiles + 3) / 4;
@@ -938,30 +754,22 @@ hipError_t fwd_lp(const float* w, const float* y, int64_t n_s, float* sc, float*
     hipError_t e = set_lds_lp(k_mlp_fwd_lp<IN, W, D, P>, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_mlp_fwd_lp<IN, W, D, P>), dim3((uint32_t)blocks), dim3(256), lds, s, w, (const float2*)y,
-                       n_s, (float4*)sc, W >= kWideWidth ? act : nullptr);
+                       n_s, (float4*)sc);
     return hipGetLastError();
 }
 
 template <int IN, int W, int D, class P>
 hipError_t bwd_lp(const float* w, const float* y, const float* dout, const float* sc, int64_t n_s, float* dy,
-                  float* partial, float* act, hipStream_t s)
+                  float* partial, hipStream_t s)
 {
     if constexpr (W >= kWideWidth) {
-        const int64_t n_tiles = (n_s + 15) / 16;
-        int64_t blocks = (n_tiles + 3) / 4;
-        blocks = blocks > 2048 ? 2048 : blocks;
-        const size_t lds = chain_lds_lp<IN, W, D, P>();
-        hipError_t e = set_lds_lp(k_mlp_chain_bwd_lp<IN, W, D, P>, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_mlp_chain_bwd_lp<IN, W, D, P>), dim3((uint32_t)blocks), dim3(256), lds, s, w,
-                           (const float4*)sc, (const float4*)dout, act, n_s, (float2*)dy);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
         const int nb = bwd_blocks(n_s);
-        const int64_t per = (n_tiles + nb - 1) / nb;
-        const size_t dwl = dw_lds_bytes_lp<IN, W, D>();
-        if ((e = set_lds_lp(k_mlp_dw_lp<IN, W, D, P>, dwl)) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_mlp_dw_lp<IN, W, D, P>), dim3((uint32_t)nb), dim3(64 * kWideWavesLp), dwl, s, y,
-                           (const float4*)sc, (const float4*)dout, act, n_s, per, partial);
+        const int64_t per = ((n_s + 15) / 16 + nb - 1) / nb;
+        constexpr size_t lds = WideLdsLp<IN, W, D>::BYTES;
+        const hipError_t e = set_lds_lp(k_mlp_wide_bwd_lp<IN, W, D, P>, lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_mlp_wide_bwd_lp<IN, W, D, P>), dim3((uint32_t)nb), dim3(64 * kWideWavesLp), lds, s, w,
+                           (const float2*)y, (const float4*)sc, (const float4*)dout, n_s, per, (float2*)dy, partial);
         return hipGetLastError();
     } else {
         const size_t lds = bwd_lds_lp<IN, W, D, P>();
@@ -975,32 +783,26 @@ hipError_t bwd_lp(const float* w, const float* y, const float* dout, const float
 }
 
 template <int IN, int W, int D, class P>
-hipError_t fwd_lp_batch(const MlpWork* work, int n_blocks, const float* params, const float* y, float* sc, float* act,
-                        hipStream_t s)
+hipError_t fwd_lp_batch(const MlpWork* work, int n_blocks, const float* params, const float* y, float* sc, hipStream_t s)
 {
     const size_t lds = fwd_lds_lp<IN, W, D, P>();
     hipError_t e = set_lds_lp(k_mlp_fwd_lp_batch<IN, W, D, P>, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_mlp_fwd_lp_batch<IN, W, D, P>), dim3((uint32_t)n_blocks), dim3(256), lds, s, work, params,
-                       (const float2*)y, (float4*)sc, W >= kWideWidth ? act : nullptr);
+                       (const float2*)y, (float4*)sc);
     return hipGetLastError();
 }
 
 template <int IN, int W, int D, class P>
 hipError_t bwd_lp_batch(const MlpWork* work, int n_blocks, const float* params, const float* y, const float* dout,
-                        const float* sc, float* dy, float* partial, int64_t slot_stride, float* act, hipStream_t s)
+                        const float* sc, float* dy, float* partial, int64_t slot_stride, hipStream_t s)
 {
     if constexpr (W >= kWideWidth) {
-        const size_t lds = chain_lds_lp<IN, W, D, P>();
-        hipError_t e = set_lds_lp(k_mlp_chain_bwd_lp_batch<IN, W, D, P>, lds);
+        constexpr size_t lds = WideLdsLp<IN, W, D>::BYTES;
+        const hipError_t e = set_lds_lp(k_mlp_wide_bwd_lp_batch<IN, W, D, P>, lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_mlp_chain_bwd_lp_batch<IN, W, D, P>), dim3((uint32_t)n_blocks), dim3(256), lds, s, work,
-                           params, (const float4*)sc, (const float4*)dout, act, (float2*)dy);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        const size_t dwl = dw_lds_bytes_lp<IN, W, D>();
-        if ((e = set_lds_lp(k_mlp_dw_lp_batch<IN, W, D, P>, dwl)) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_mlp_dw_lp_batch<IN, W, D, P>), dim3((uint32_t)n_blocks), dim3(64 * kWideWavesLp), dwl, s,
-                           work, y, (const float4*)sc, (const float4*)dout, act, partial, slot_stride);
+        hipLaunchKernelGGL((k_mlp_wide_bwd_lp_batch<IN, W, D, P>), dim3((uint32_t)n_blocks), dim3(64 * kWideWavesLp), lds,
+                           s, work, params, y, (const float4*)sc, (const float4*)dout, (float2*)dy, partial, slot_stride);
         return hipGetLastError();
     } else {
         const size_t lds = bwd_lds_lp<IN, W, D, P>();
@@ -1034,11 +836,10 @@ hipError_t bwd_lp_batch(const MlpWork* work, int n_blocks, const float* params, 
     X(32, 128, 2)
 
 template <class P>
-hipError_t fwd_dispatch(const MlpShape& m, const float* w, const float* y, int64_t n_s, float* sc, float* act,
-                        hipStream_t s)
+hipError_t fwd_dispatch(const MlpShape& m, const float* w, const float* y, int64_t n_s, float* sc, hipStream_t s)
 {
 #define X(I, Wd, Dp) \
-    if (m.in_dim == I && m.width == Wd && m.hidden == Dp) return fwd_lp<I, Wd, Dp, P>(w, y, n_s, sc, act, s);
+    if (m.in_dim == I && m.width == Wd && m.hidden == Dp) return fwd_lp<I, Wd, Dp, P>(w, y, n_s, sc, s);
     PRENOM_FOR_EACH_MLP_LP(X)
 #undef X
     return hipErrorInvalidValue;
@@ -1046,11 +847,11 @@ hipError_t fwd_dispatch(const MlpShape& m, const float* w, const float* y, int64
 
 template <class P>
 hipError_t bwd_dispatch(const MlpShape& m, const float* w, const float* y, const float* dout, const float* sc,
-                        int64_t n_s, float* dy, float* partial, float* act, hipStream_t s)
+                        int64_t n_s, float* dy, float* partial, hipStream_t s)
 {
 #define X(I, Wd, Dp)                                        \
     if (m.in_dim == I && m.width == Wd && m.hidden == Dp) \
-        return bwd_lp<I, Wd, Dp, P>(w, y, dout, sc, n_s, dy, partial, act, s);
+        return bwd_lp<I, Wd, Dp, P>(w, y, dout, sc, n_s, dy, partial, s);
     PRENOM_FOR_EACH_MLP_LP(X)
 #undef X
     return hipErrorInvalidValue;
@@ -1058,11 +859,11 @@ hipError_t bwd_dispatch(const MlpShape& m, const float* w, const float* y, const
 
 template <class P>
 hipError_t fwd_batch_dispatch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params, const float* y,
-                              float* sc, float* act, hipStream_t s)
+                              float* sc, hipStream_t s)
 {
 #define X(I, Wd, Dp)                                        \
     if (m.in_dim == I && m.width == Wd && m.hidden == Dp) \
-        return fwd_lp_batch<I, Wd, Dp, P>(work, n_blocks, params, y, sc, act, s);
+        return fwd_lp_batch<I, Wd, Dp, P>(work, n_blocks, params, y, sc, s);
     PRENOM_FOR_EACH_MLP_LP(X)
 #undef X
     return hipErrorInvalidValue;
@@ -1071,11 +872,11 @@ hipError_t fwd_batch_dispatch(const MlpShape& m, const MlpWork* work, int n_bloc
 template <class P>
 hipError_t bwd_batch_dispatch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
                               const float* y, const float* dout, const float* sc, float* dy, float* partial,
-                              int64_t slot_stride, float* act, hipStream_t s)
+                              int64_t slot_stride, hipStream_t s)
 {
 #define X(I, Wd, Dp)                                                                                     \
     if (m.in_dim == I && m.width == Wd && m.hidden == Dp)                                              \
-        return bwd_lp_batch<I, Wd, Dp, P>(work, n_blocks, params, y, dout, sc, dy, partial, slot_stride, act, s);
+        return bwd_lp_batch<I, Wd, Dp, P>(work, n_blocks, params, y, dout, sc, dy, partial, slot_stride, s);
     PRENOM_FOR_EACH_MLP_LP(X)
 #undef X
     return hipErrorInvalidValue;
@@ -1083,42 +884,41 @@ hipError_t bwd_batch_dispatch(const MlpShape& m, const MlpWork* work, int n_bloc
 
 }  // namespace
 
-hipError_t launch_mlp_fwd_lp(const MlpShape& m, const float* w, const float* y, int64_t n_s, float* sc, float* act,
-                             hipStream_t s)
+hipError_t launch_mlp_fwd_lp(const MlpShape& m, const float* w, const float* y, int64_t n_s, float* sc, hipStream_t s)
 {
     if (n_s == 0) return hipSuccess;
-    if (m.dtype == PRENOM_BF16) return fwd_dispatch<Bf16Op>(m, w, y, n_s, sc, act, s);
-    if (m.dtype == PRENOM_F16) return fwd_dispatch<F16Op>(m, w, y, n_s, sc, act, s);
+    if (m.dtype == PRENOM_BF16) return fwd_dispatch<Bf16Op>(m, w, y, n_s, sc, s);
+    if (m.dtype == PRENOM_F16) return fwd_dispatch<F16Op>(m, w, y, n_s, sc, s);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_mlp_bwd_lp(const MlpShape& m, const float* w, const float* y, const float* dout, const float* sc,
-                             int64_t n_s, float* dy, float* partial, float* act, hipStream_t s)
+                             int64_t n_s, float* dy, float* partial, hipStream_t s)
 {
     if (n_s == 0) return hipSuccess;
-    if (m.dtype == PRENOM_BF16) return bwd_dispatch<Bf16Op>(m, w, y, dout, sc, n_s, dy, partial, act, s);
-    if (m.dtype == PRENOM_F16) return bwd_dispatch<F16Op>(m, w, y, dout, sc, n_s, dy, partial, act, s);
+    if (m.dtype == PRENOM_BF16) return bwd_dispatch<Bf16Op>(m, w, y, dout, sc, n_s, dy, partial, s);
+    if (m.dtype == PRENOM_F16) return bwd_dispatch<F16Op>(m, w, y, dout, sc, n_s, dy, partial, s);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_mlp_fwd_lp_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
-                                   const float* y, float* sc, float* act, hipStream_t s)
+                                   const float* y, float* sc, hipStream_t s)
 {
     if (n_blocks == 0) return hipSuccess;
-    if (m.dtype == PRENOM_BF16) return fwd_batch_dispatch<Bf16Op>(m, work, n_blocks, params, y, sc, act, s);
-    if (m.dtype == PRENOM_F16) return fwd_batch_dispatch<F16Op>(m, work, n_blocks, params, y, sc, act, s);
+    if (m.dtype == PRENOM_BF16) return fwd_batch_dispatch<Bf16Op>(m, work, n_blocks, params, y, sc, s);
+    if (m.dtype == PRENOM_F16) return fwd_batch_dispatch<F16Op>(m, work, n_blocks, params, y, sc, s);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_mlp_bwd_lp_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
                                    const float* y, const float* dout, const float* sc, float* dy, float* partial,
-                                   int64_t slot_stride, float* act, hipStream_t s)
+                                   int64_t slot_stride, hipStream_t s)
 {
     if (n_blocks == 0) return hipSuccess;
     if (m.dtype == PRENOM_BF16)
-        return bwd_batch_dispatch<Bf16Op>(m, work, n_blocks, params, y, dout, sc, dy, partial, slot_stride, act, s);
+        return bwd_batch_dispatch<Bf16Op>(m, work, n_blocks, params, y, dout, sc, dy, partial, slot_stride, s);
     if (m.dtype == PRENOM_F16)
-        return bwd_batch_dispatch<F16Op>(m, work, n_blocks, params, y, dout, sc, dy, partial, slot_stride, act, s);
+        return bwd_batch_dispatch<F16Op>(m, work, n_blocks, params, y, dout, sc, dy, partial, slot_stride, s);
     return hipErrorInvalidValue;
 }
 
