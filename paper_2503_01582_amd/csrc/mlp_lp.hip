@@ -549,8 +549,11 @@ __device__ __forceinline__ void mlp_wide_bwd_lp(unsigned char* __restrict__ smem
 #pragma unroll
     for (int t = 0; t < N::IT; ++t) a1[t] = {0.0f, 0.0f, 0.0f, 0.0f};
     // W_out: A[i][k] = dO_i (rows i >= 4 zero), B = the last layer's activations
+    // Two layers hold twice the sums, so their loops are not unrolled: with the
+    // registers of a second step 65536 rays x 48, 12 levels took 1264 us, without
+    // 1184; the one-layer kernel has them to spare (381 against 397).
     auto add_out = [&](int hbase) {
-#pragma unroll 2
+#pragma unroll(D == 1 ? 2 : 1)
         for (int ks = 0; ks < kWideChunk / 16; ++ks) {
             const int k0 = 16 * ks + 4 * q;
             vec d = op(L::DO, j & 3, k0);
@@ -559,7 +562,7 @@ __device__ __forceinline__ void mlp_wide_bwd_lp(unsigned char* __restrict__ smem
         }
     };
     auto add_in = [&](int dbase) {  // W_1
-#pragma unroll 2
+#pragma unroll(D == 1 ? 2 : 1)
         for (int ks = 0; ks < kWideChunk / 16; ++ks) {
             const int k0 = 16 * ks + 4 * q;
             const vec av = op(dbase, 16 * wave + j, k0);
@@ -660,7 +663,7 @@ __device__ __forceinline__ void mlp_wide_bwd_lp(unsigned char* __restrict__ smem
                 dp[to] = pack<P>(mask_by_bits(acc[to], mask[0], to));
             }
             __syncthreads();
-#pragma unroll 2
+#pragma unroll 1
             for (int ks = 0; ks < kWideChunk / 16; ++ks) {
                 const int k0 = 16 * ks + 4 * q;
                 const vec av = op(L::A, 16 * wave + j, k0);
