@@ -101,7 +101,6 @@ void tiles_for(const prenom_batch* b, const MlpShape& m, int& fwd, int& bwd)
 // 338571 rays 15.0 -> 12.5 ms, 48 objects in BF16 19.2 -> 18.9 ms; two rounds
 // in place of one (512 forward blocks) 0.56 against 0.51 ms on the 16 objects,
 // and 0.81 against 0.77 ms backward on a meta-iteration's 64-wide network.
-constexpr int64_t kCus = 256;
 constexpr int64_t kFwdQuantum = 4, kBwdQuantum = 8;
 
 // Backward blocks that one CU's LDS holds at a time: the 32-wide kernels' 50 KB

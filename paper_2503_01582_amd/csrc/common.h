@@ -11,6 +11,7 @@ namespace prenom {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWave = 64;
+constexpr int64_t kCus = 256;  // compute units of a gfx950 in one partition
 
 // Level table of a hash grid, passed by value to kernels.
 struct GridInfo {

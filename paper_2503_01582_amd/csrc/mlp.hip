@@ -796,9 +796,8 @@ hipError_t fwd_impl(const float* w, const float* y, int64_t n_s, float* sc, floa
 {
     const int64_t n_tiles = (n_s + 15) / 16;
     constexpr int kWaves = fwd_threads(W) / 64;
-    int64_t blocks = (n_tiles + kWaves - 1) / kWaves;
-    blocks = blocks > 2048 ? 2048 : blocks;
     const size_t lds = fwd_lds_bytes<IN, W, D>();
+    const int64_t blocks = fwd_blocks(n_tiles, kWaves, lds);
     hipError_t e = set_lds(k_mlp_fwd<IN, W, D>, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_mlp_fwd<IN, W, D>), dim3((uint32_t)blocks), dim3(fwd_threads(W)), lds, s, w, y, n_s, (float4*)sc,
@@ -819,9 +818,8 @@ hipError_t bwd_impl(const float* w, const float* y, const float* dout, const flo
     if constexpr (W >= kWideWidth) {
         const int64_t n_tiles = (n_s + 15) / 16;
         constexpr int kWaves = fwd_threads(W) / 64;
-        int64_t blocks = (n_tiles + kWaves - 1) / kWaves;
-        blocks = blocks > 2048 ? 2048 : blocks;
         const size_t lds = chain_bwd_lds_bytes<IN, W, D>();
+        const int64_t blocks = fwd_blocks(n_tiles, kWaves, lds);
         hipError_t e = set_lds(k_mlp_chain_bwd<IN, W, D>, lds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_mlp_chain_bwd<IN, W, D>), dim3((uint32_t)blocks), dim3(fwd_threads(W)), lds, s, w,

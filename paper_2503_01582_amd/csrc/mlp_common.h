@@ -46,9 +46,26 @@ constexpr int kStagePad = 4;      // floats of padding per staged row
 inline int bwd_blocks(int64_t n_s)
 {
     const int64_t n_tiles = (n_s + 15) / 16;
-    int64_t b = (n_tiles + kBwdWaves * 2 - 1) / (kBwdWaves * 2);  // >= 16 tiles per wave
+    int64_t b = (n_tiles + kBwdWaves * 2 - 1) / (kBwdWaves * 2);  // two tiles per wave
     b = b < 1 ? 1 : b;
     return (int)(b > kBwdMaxBlocks ? kBwdMaxBlocks : b);
+}
+
+// Blocks of a forward grid (and of the FP32 128-wide chain) whose blocks stage
+// `lds` bytes of weight fragments before their first tile.  A block's staging is
+// paid once however many tiles it walks, so the grid is the number of blocks that
+// share the chip at once, 256 CUs times one to four by their LDS, and the tiles are
+// dealt out evenly; a small launch keeps one tile a wave, the most CUs.  With up to
+// 2048 blocks instead, 4096 rays x 32 (128-wide, two layers): FP32 132 -> 84 us, BF16
+// 87 -> 39; 64-wide: FP32 47 -> 35; 65536 rays x 32: 128-wide FP32 1029 -> 920, BF16
+// 220 -> 199, 32-wide FP32 123 -> 114.  Fewer still leave SIMDs without waves: 64-wide
+// FP32 at 65536 rays with 512 blocks 331, with 1024 300.
+inline int64_t fwd_blocks(int64_t n_tiles, int waves, size_t lds)
+{
+    const size_t fit = (size_t)120 * 1024 / (lds ? lds : 1);
+    const int64_t most = kCus * (int64_t)(fit < 1 ? 1 : fit > 4 ? 4 : fit);
+    const int64_t per = (n_tiles + waves * most - 1) / (waves * most);
+    return (n_tiles + waves * per - 1) / (waves * per);
 }
 
 // Stage the tile's delta (D layout, out tiles) and h (D layout) for the

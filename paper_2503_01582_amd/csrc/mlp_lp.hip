@@ -751,9 +751,8 @@ template <int IN, int W, int D, class P>
 hipError_t fwd_lp(const float* w, const float* y, int64_t n_s, float* sc, hipStream_t s)
 {
     const int64_t n_tiles = (n_s + 15) / 16;
-    int64_t blocks = (n_tiles + 3) / 4;
-    blocks = blocks > 2048 ? 2048 : blocks;
     const size_t lds = fwd_lds_lp<IN, W, D, P>();
+    const int64_t blocks = fwd_blocks(n_tiles, 4, lds);
     hipError_t e = set_lds_lp(k_mlp_fwd_lp<IN, W, D, P>, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_mlp_fwd_lp<IN, W, D, P>), dim3((uint32_t)blocks), dim3(256), lds, s, w, (const float2*)y,
