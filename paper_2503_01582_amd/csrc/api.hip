@@ -648,7 +648,11 @@ prenom_status prenom_reptile_update(float* theta, float* tasks, int64_t n_params
 size_t prenom_canonical_yaw_workspace_size(int64_t n_points, int32_t n_yaw)
 {
     if (n_points < 1 || n_points > PRENOM_MAX_YAW_POINTS || n_yaw < 1 || n_yaw > PRENOM_MAX_YAWS) return 0;
-    return align_up((size_t)n_yaw * (size_t)yaw_chunks(n_points) * 7 * sizeof(double));
+    YawArgs a{};
+    a.n = n_points;
+    a.K = n_yaw;
+    yaw_split(a);
+    return align_up(yaw_doubles(a) * sizeof(double));
 }
 
 prenom_status prenom_canonical_yaw(const float* points, int64_t n_points, const float* prior, int32_t prior_res,
@@ -663,7 +667,6 @@ prenom_status prenom_canonical_yaw(const float* points, int64_t n_points, const 
         return fail(PRENOM_ERR_SHAPE, "prior_res %d outside [2, %d]", prior_res, PRENOM_MAX_PRIOR_RES);
     if (!points || !prior || !scores || !extents || !centers || !best)
         return fail(PRENOM_ERR_INVALID_ARG, "NULL array argument");
-    const int64_t C = yaw_chunks(n_points);
     const size_t need = prenom_canonical_yaw_workspace_size(n_points, n_yaw);
     if (!workspace || !aligned(workspace, kAlign)) return fail(PRENOM_ERR_WORKSPACE, "workspace NULL or not 256-byte aligned");
     if (ws_bytes < need) return fail(PRENOM_ERR_WORKSPACE, "workspace %zu bytes < %zu", ws_bytes, need);
@@ -673,9 +676,8 @@ prenom_status prenom_canonical_yaw(const float* points, int64_t n_points, const 
     a.F = prior;
     a.R = prior_res;
     a.K = n_yaw;
-    a.n_chunks = C;
-    a.part_ext = at<double>(workspace, 0);
-    a.part_sum = a.part_ext + (int64_t)n_yaw * C * 6;
+    yaw_split(a);
+    yaw_place(a, at<double>(workspace, 0));
     a.scores = scores;
     a.extents = extents;
     a.centers = centers;

@@ -543,21 +543,28 @@ __device__ inline double prior_at(const float* __restrict__ F, int R, const doub
     return s;
 }
 
-// Canonical yaw search (Eq. (3)); workspace: per (yaw, chunk) extents and sums.
+// Canonical yaw search (Eq. (3)).  yaw_split sets the split of a.n points and
+// a.K yaws; workspace: per (chunk, yaw) sums, per (extent chunk, yaw) extents.
 struct YawArgs {
     const float* pts;   // [n][3]
     int64_t n;
     const float* F;     // [R][R][R]
     int32_t R, K;
-    int64_t n_chunks;
-    double* part_ext;   // [K][n_chunks][6]: min xyz, max xyz
-    double* part_sum;   // [K][n_chunks]
+    int32_t log2_kl;             // yaws per wave
+    int64_t chunk, n_chunks;     // points per score block
+    int64_t ext_chunk, n_ext;    // points per extents block
+    double2* turn;      // [K] cos, sin
+    double* part_sum;   // [n_chunks][K]
+    double* part_ext;   // [n_ext + 1][4][K]: min x, min y, max x, max y
+    double* part_z;     // [n_ext + 1][2]: min z, max z
     double* scores;     // [K]
     double* extents;    // [K][3]
     double* centers;    // [K][3]
     int32_t* best;
 };
-int64_t yaw_chunks(int64_t n);
-hipError_t launch_canonical_yaw(const YawArgs& a, hipStream_t s);
+void yaw_split(YawArgs& a);
+size_t yaw_doubles(const YawArgs& a);
+void yaw_place(YawArgs& a, double* ws);
+hipError_t launch_canonical_yaw(YawArgs a, hipStream_t s);
 
 }  // namespace prenom
