@@ -15,11 +15,12 @@ from . import _lib as L
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()  # every entry point declares its argument types
 
 
-def _stream() -> C.c_void_p:
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    # torch.cuda.current_stream() without the Stream object: 0.3 us, not 2.7
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _check_rays(samp: "SampleOut", n: int, **arrays):
@@ -156,9 +157,7 @@ def sample_cfg(spec, world_to_obj, prior: Optional[torch.Tensor]) -> L.PrenomSam
     c.eps = spec.eps
     c.near_t = spec.near
     c.far_t = spec.far
-    A = np.asarray(world_to_obj, np.float32).reshape(12)
-    for i in range(12):
-        c.world_to_obj[i] = float(A[i])
+    c.world_to_obj[:] = np.asarray(world_to_obj, np.float32).reshape(12).tolist()
     if prior is not None:
         _dev(prior, torch.float32, "prior")
         if prior.dim() != 3 or len(set(prior.shape)) != 1:
