@@ -57,7 +57,7 @@ struct Plan {
     std::vector<MlpRed> red;
     std::vector<MlpWork> fwd, bwd;
     std::vector<Group> groups;
-    int64_t n_rays = 0, n_params = 0, n_mlp_total = 0, n_items = 0;
+    int64_t n_rays = 0, n_params = 0, n_mlp_total = 0, n_items = 0, n_lds = 0;
     int64_t y_floats = 0, partial_floats = 0, act_floats = 0;
     int64_t records = 0, pass_items = 0, pass_segs = 0, pass_parts = 0;  // largest of any scatter pass
     int32_t pass_levels = 0, tiles_max = 1;
@@ -198,7 +198,6 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
         so.s_begin = ray * S;
         so.dy_off = yoff / 2;
         so.g_off = param;
-        so.item_off = item;
         p.tiles_max = scatter_tiles_max(so) > p.tiles_max ? scatter_tiles_max(so) : p.tiles_max;
 
         MlpRed& r = p.red[i];
@@ -217,7 +216,7 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
     p.n_rays = ray;
     p.n_params = param;
     p.y_floats = yoff;
-    p.n_items = item;
+    encode_split(p.dev.data(), p.sc.data(), n, p.n_items, p.n_lds);
     p.n_mlp_total = mlp;
     if (item >= ((int64_t)1 << 31) || tile >= ((int64_t)1 << 31))
         return fail(PRENOM_ERR_SHAPE, "batch grid too large");
@@ -419,7 +418,7 @@ prenom_status fwd_features(const prenom_batch* b, const Plan& p, const float* ra
     const ObjDev* dev = at<const ObjDev>(ws, p.o_dev);
     float* y = at<float>(ws, p.y);
     PRENOM_LAUNCH("k_encode_fwd", s,
-                  launch_encode_batch(dev, at<const ScatterObj>(ws, p.o_sc), p.n_obj, p.n_items, b->params,
+                  launch_encode_batch(dev, at<const ScatterObj>(ws, p.o_sc), p.n_obj, p.n_items, p.n_lds, b->params,
                                       p.any_f16_table ? b->params_lp : nullptr, ray_obj, t, p.S, y, s));
     for (const Group& g : p.groups) {
         const MlpWork* work = at<const MlpWork>(ws, p.o_fwd) + g.fwd_first;

@@ -75,8 +75,9 @@ __device__ __forceinline__ void level_corners(const GridInfo& g, int l, float x0
     // corner, strength-reduced): (c + 1) P = c P + P modulo 2^32 for the hash,
     // and the 1:1 row of a corner is the cell's row plus 1, side or side^2.
     // kBranch: one uniform branch instead of a select per corner (fewer vector
-    // instructions, which bind the scatter; the encoding, bound by its gathers,
-    // is faster without: 11.4 against 12.2 ms on 48 objects).
+    // instructions, which bind the scatter and the encoding from LDS; the
+    // encoding that is bound by its gathers is faster without: 11.4 against 12.2 ms
+    // on 48 objects).
     const uint32_t mask = (1u << g.log2_table) - 1u, side = (uint32_t)N + 1u;
     auto dense_row = [&](uint32_t r0, int e) { return r0 + (e & 1) + (e & 2 ? side : 0u) + (e & 4 ? side * side : 0u); };
     auto hash_row = [&](uint32_t hy, uint32_t hz, int e) {
@@ -284,10 +285,12 @@ hipError_t launch_encode_points(const GridInfo& g, const float* table, const flo
                                 float* features, int32_t* corner_idx, hipStream_t s);
 
 struct ScatterObj;
-// Encoding of the rendered samples of every object of a batch: one block per
-// scatter item (object, level, sample block) of sobjs; FP16 tables come from
-// params_f16.
-hipError_t launch_encode_batch(const ObjDev* objs, const ScatterObj* sobjs, int n_obj, int64_t n_items,
+// Encoding of the rendered samples of every object of a batch (FP16 tables come
+// from params_f16).  encode_split shares the objects between the kernel that
+// stages tables in LDS (lds_off, n_runs, run of sobjs) and the one block per
+// (level, sample block) of the others (item_off); n_lds, n_items: their blocks.
+void encode_split(const ObjDev* objs, ScatterObj* sobjs, int n_obj, int64_t& n_items, int64_t& n_lds);
+hipError_t launch_encode_batch(const ObjDev* objs, const ScatterObj* sobjs, int n_obj, int64_t n_items, int64_t n_lds,
                                const float* params, const void* params_f16, const float* ray_obj, const float* t,
                                int32_t S, float* y, hipStream_t s);
 
@@ -324,6 +327,9 @@ struct ScatterObj {
     int64_t ritem_off;  // first reduce item
     int64_t part_off;   // first partial sum
     int64_t ctile_off;  // first split tile
+    int64_t lds_off;    // staged encoding: first (level, run) block,
+    int64_t run;        // samples per run, and
+    int32_t n_runs;     // runs per level (0: not staged)
 };
 // Fills the geometry of one object (offsets within the batch are left 0).
 ScatterObj scatter_obj(const GridInfo& g, int64_t n_s);

@@ -4,8 +4,11 @@
 //
 // Layout: tables [L][T][2] (one float2 per row), features y level-major
 // [L][n_samples][2], so a wavefront of one level writes 64 consecutive float2
-// (512 contiguous bytes).  The launch grid is (sample blocks, levels): one
-// thread per (sample, level), 8 float2 gathers each.
+// (512 contiguous bytes).  One thread per (sample, level): 8 corner rows,
+// gathered from memory (grid: sample blocks, levels) or, where a level's table
+// fits, from LDS.
+#include <type_traits>
+
 #include "common.h"
 
 namespace prenom {
@@ -195,9 +198,179 @@ __global__ __launch_bounds__(kEncBlock) void k_encode_samples(GridInfo g, const 
     y[(int64_t)l * n_s + s] = gather_blend<true>(lt, g, l, c);
 }
 
-// Batched: one block per item (object, level, block of kScatterBlockSamples
-// samples) of the batch's hash-table gradient (sobjs[i] and objs[i] describe
-// object i).
+// Encoding from LDS: a block stages a level's rows and encodes a long run of
+// samples against them.  The gathers above are bound by the lines the L1 caches
+// fetch, about 600 cycles of a CU for 64 samples of a level; from LDS the same
+// corners cost 125, the vector instructions that find and weigh them.  A table of
+// up to 256 KB takes two passes, one feature of its rows at a time: twice the
+// arithmetic (and half-line stores), still below the gathers.  The same products
+// in the same order, so the same bits.  Measured on gfx950 (us), gathers against
+// staged: 64777 rays x 33, FP32, 8 levels of 2^14 rows 125 / 54, 12 levels of
+// 2^15 (two passes) 248 / 185; FP16, 12 levels of 2^15 243 / 84, 16 of 2^16 (two
+// passes) 393 / 226; 48 objects with FP16 tables 11440 / 7863.  A run has to pay
+// for staging its level, 3 us a pass and 128 KB: 2048 rays x 33, 8 levels of 2^14
+// (2112 samples a CU) 12.4 / 10.0, 512 rays 7.0 / 7.4; in two passes 12288 rays x
+// 33, 12 levels of 2^15 55 / 50, 4096 rays 23 / 31.  Longer runs than kLdsMost
+// leave the last round of blocks emptier (256000 rays: 191 against 239 with
+// 131072).
+constexpr int kLdsThreads = 1024;
+constexpr uint32_t kLdsBytes = 128 * 1024;
+constexpr int64_t kLdsMost = 49152;                     // samples per staged level
+constexpr int64_t kLdsMinRun = 1024, kLdsMinRun2 = 16384;  // fewest that pay for it, in one pass and two
+
+// Passes over the samples that a level of 2^log2T rows needs: 1 if its rows fit
+// the staged bytes, 2 if one feature of each does, else 0 (not staged).
+__host__ __device__ constexpr int lds_planes(uint32_t row_bytes, int log2T)
+{
+    const uint64_t bytes = (uint64_t)row_bytes << log2T;
+    return bytes < 64 ? 0 : bytes <= kLdsBytes ? 1 : bytes <= 2 * kLdsBytes ? 2 : 0;
+}
+
+template <typename Row>
+struct Feature;
+template <>
+struct Feature<float2> {
+    typedef float type;
+    typedef float2 out;  // one feature of the rows in 16 bytes
+    __device__ static float2 pick(uint4 v, int f)
+    {
+        return f ? make_float2(__uint_as_float(v.y), __uint_as_float(v.w))
+                 : make_float2(__uint_as_float(v.x), __uint_as_float(v.z));
+    }
+};
+template <>
+struct Feature<half2_t> {
+    typedef _Float16 type;
+    typedef uint2 out;
+    __device__ static uint2 pick(uint4 v, int f)
+    {
+        return f ? make_uint2((v.x >> 16) | (v.y & 0xffff0000u), (v.z >> 16) | (v.w & 0xffff0000u))
+                 : make_uint2((v.x & 0xffffu) | (v.y << 16), (v.z & 0xffffu) | (v.w << 16));
+    }
+};
+
+// Samples [s0, s1) of one level; gs0: the global index of sample s0.
+template <typename Row, int kPlanes>
+__device__ __forceinline__ void encode_lds(uint4* __restrict__ smem, const GridInfo& g, int l,
+                                           const Row* __restrict__ level_table, const float* __restrict__ ray_obj,
+                                           const float* __restrict__ t, int64_t gs0, uint32_t n, int32_t S,
+                                           float inv_S, float2* __restrict__ y)
+{
+    const uint32_t side = (uint32_t)g.res[l] + 1u;
+    const uint32_t rows = (g.dense_mask >> l) & 1u ? side * side * side : 1u << g.log2_table;
+    const uint32_t vecs = (rows * (uint32_t)sizeof(Row) + 15u) / 16u;  // (a level's slice holds whole vectors)
+    const uint4* src = reinterpret_cast<const uint4*>(level_table);
+    const uint32_t ray0 = (uint32_t)gs0 / (uint32_t)S, off = (uint32_t)gs0 - ray0 * (uint32_t)S;
+    const float* ro0 = ray_obj + 6 * (int64_t)ray0;
+    t += gs0;
+    auto corners = [&](uint32_t i, Corners& c) {
+        const float* ro = ro0 + 6u * (uint32_t)(((float)(off + i) + 0.5f) * inv_S);
+        const float ts = t[i];
+        level_corners<true>(g, l, sample_coord(ts, ro[3], ro[0]), sample_coord(ts, ro[4], ro[1]),
+                            sample_coord(ts, ro[5], ro[2]), c);
+    };
+    if constexpr (kPlanes == 1) {
+#pragma unroll 8
+        for (uint32_t i = threadIdx.x; i < vecs; i += kLdsThreads) smem[i] = src[i];
+        __syncthreads();
+        const Row* tab = reinterpret_cast<const Row*>(smem);
+#pragma unroll 2
+        for (uint32_t i = threadIdx.x; i < n; i += kLdsThreads) {
+            Corners c;
+            corners(i, c);
+            y[i] = gather_blend_rows(tab, c);
+        }
+    } else {
+        typedef Feature<Row> F;
+        typename F::out* dst = reinterpret_cast<typename F::out*>(smem);
+        const typename F::type* tab = reinterpret_cast<const typename F::type*>(smem);
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            if (f) __syncthreads();
+#pragma unroll 8
+            for (uint32_t i = threadIdx.x; i < vecs; i += kLdsThreads) dst[i] = F::pick(src[i], f);
+            __syncthreads();
+#pragma unroll 2
+            for (uint32_t i = threadIdx.x; i < n; i += kLdsThreads) {
+                Corners c;
+                corners(i, c);
+                float v[8], acc = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = (float)tab[c.row[e]];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc = fmaf(c.w[e], v[e], acc);
+                reinterpret_cast<float*>(y)[2 * i + f] = acc;
+            }
+        }
+    }
+}
+
+template <typename Row, int kPlanes>
+__global__ __launch_bounds__(kLdsThreads) void k_encode_samples_lds(GridInfo g, const Row* __restrict__ table,
+                                                                  const float* __restrict__ ray_obj,
+                                                                  const float* __restrict__ t, int64_t n_s,
+                                                                  int64_t run, int32_t S, float inv_S,
+                                                                  float2* __restrict__ y)
+{
+    extern __shared__ uint4 smem[];
+    const int l = blockIdx.y;
+    const int64_t s0 = (int64_t)blockIdx.x * run;
+    const uint32_t n = (uint32_t)(n_s - s0 < run ? n_s - s0 : run);
+    encode_lds<Row, kPlanes>(smem, g, l, table + ((int64_t)l << g.log2_table), ray_obj, t, s0, n, S, inv_S,
+                             y + (int64_t)l * n_s + s0);
+}
+
+// Object of an item of a batched launch: the last whose first item (`off` of its
+// geometry) is not past it; objects without items have their successor's.
+__device__ __forceinline__ int item_object(const ScatterObj* __restrict__ sobjs, int n_obj,
+                                           int64_t ScatterObj::*off, int64_t item)
+{
+    int lo = 0, hi = n_obj - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (sobjs[mid].*off <= item)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return lo;
+}
+
+// Batched, staged objects: one block per item (object, level, run of samples).
+__global__ __launch_bounds__(kLdsThreads) void k_encode_batch_lds(const ObjDev* __restrict__ objs,
+                                                                const ScatterObj* __restrict__ sobjs, int n_obj,
+                                                                const float* __restrict__ params,
+                                                                const half2_t* __restrict__ params_f16,
+                                                                const float* __restrict__ ray_obj,
+                                                                const float* __restrict__ t, int32_t S, float inv_S,
+                                                                float2* __restrict__ y)
+{
+    extern __shared__ uint4 smem[];
+    const int64_t item = blockIdx.x;
+    const int k = item_object(sobjs, n_obj, &ScatterObj::lds_off, item);
+    const ScatterObj& so = sobjs[k];
+    const ObjDev& o = objs[k];
+    const uint32_t rem = (uint32_t)(item - so.lds_off);
+    const int l = (int)(rem / (uint32_t)so.n_runs);
+    const int64_t s0 = (int64_t)(rem - (uint32_t)l * (uint32_t)so.n_runs) * so.run;
+    const uint32_t n = (uint32_t)(so.n_s - s0 < so.run ? so.n_s - s0 : so.run);
+    const int64_t row0 = (int64_t)l << o.grid.log2_table, gs0 = so.s_begin + s0;
+    float2* out = y + o.y_off / 2 + (int64_t)l * so.n_s + s0;
+    auto encode = [&](auto* table) {
+        typedef std::remove_const_t<std::remove_pointer_t<decltype(table)>> Row;
+        if (lds_planes(sizeof(Row), o.grid.log2_table) == 1)
+            encode_lds<Row, 1>(smem, o.grid, l, table, ray_obj, t, gs0, n, S, inv_S, out);
+        else
+            encode_lds<Row, 2>(smem, o.grid, l, table, ray_obj, t, gs0, n, S, inv_S, out);
+    };
+    if (o.table_dtype == PRENOM_F16)
+        encode(params_f16 + o.param_off / 2 + row0);
+    else
+        encode(reinterpret_cast<const float2*>(params + o.param_off) + row0);
+}
+
+// Batched, the other objects: one block per item (object, level, block of
+// kScatterBlockSamples samples); sobjs[i] and objs[i] describe object i.
 __global__ __launch_bounds__(kScatterBlockSamples) void k_encode_batch(const ObjDev* __restrict__ objs,
                                                                    const ScatterObj* __restrict__ sobjs, int n_obj,
                                                                    const float* __restrict__ params,
@@ -207,14 +380,7 @@ __global__ __launch_bounds__(kScatterBlockSamples) void k_encode_batch(const Obj
                                                                    float2* __restrict__ y)
 {
     const int64_t item = blockIdx.x;
-    int lo = 0, hi = n_obj - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (sobjs[mid].item_off <= item)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
+    const int lo = item_object(sobjs, n_obj, &ScatterObj::item_off, item);
     const ScatterObj& so = sobjs[lo];
     const ObjDev& o = objs[lo];
     const uint32_t rem = (uint32_t)(item - so.item_off);
@@ -285,7 +451,50 @@ __global__ __launch_bounds__(256) void k_density_grid(const float4* __restrict__
     if (p < n) out[p] = sc[p].x;
 }
 
+template <typename Row, int kPlanes>
+hipError_t encode_samples_lds(const GridInfo& g, const Row* table, const float* ray_obj, const float* t, int64_t n_s,
+                              int64_t run, int32_t S, float2* y, hipStream_t s)
+{
+    auto kern = k_encode_samples_lds<Row, kPlanes>;
+    const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)((n_s + run - 1) / run), (uint32_t)g.n_levels), dim3(kLdsThreads),
+                       kLdsBytes, s, g, table, ray_obj, t, n_s, run, S, 1.0f / (float)S, y);
+    return hipGetLastError();
+}
+
+int64_t round_up(int64_t n, int64_t m) { return (n + m - 1) / m * m; }
+
 dim3 enc_grid(int64_t n, int L) { return dim3((uint32_t)((n + kEncBlock - 1) / kEncBlock), (uint32_t)L); }
+
+// Samples per staged block for `work` (level, sample) pairs: whole rounds of one
+// block a CU, at most kLdsMost each.
+int64_t lds_run(int64_t work)
+{
+    if (work == 0) return 0;
+    const int64_t rounds = (work + kCus * kLdsMost - 1) / (kCus * kLdsMost);
+    return (work + kCus * rounds - 1) / (kCus * rounds);
+}
+
+// Whether blocks of `run` samples pay for their staging.
+bool lds_pays(int planes, int64_t run) { return planes && run >= (planes == 1 ? kLdsMinRun : kLdsMinRun2); }
+
+template <typename Row>
+hipError_t encode_samples(const GridInfo& g, const Row* table, const float* ray_obj, const float* t, int64_t n_s,
+                          int32_t S, float2* y, hipStream_t s)
+{
+    const int planes = ((uintptr_t)table & 15) == 0 ? lds_planes(sizeof(Row), g.log2_table) : 0;
+    if (lds_pays(planes, lds_run(n_s * g.n_levels))) {
+        const int64_t rounds = (n_s * g.n_levels + kCus * kLdsMost - 1) / (kCus * kLdsMost);
+        const int64_t per_level = rounds * kCus / g.n_levels;  // blocks (L <= 16)
+        const int64_t run = round_up((n_s + per_level - 1) / per_level, 64);
+        return planes == 1 ? encode_samples_lds<Row, 1>(g, table, ray_obj, t, n_s, run, S, y, s)
+                           : encode_samples_lds<Row, 2>(g, table, ray_obj, t, n_s, run, S, y, s);
+    }
+    hipLaunchKernelGGL(k_encode_samples<Row>, enc_grid(n_s, g.n_levels), dim3(kEncBlock), 0, s, g, table, ray_obj, t,
+                       n_s, S, y);
+    return hipGetLastError();
+}
 
 }  // namespace
 
@@ -295,13 +504,8 @@ hipError_t launch_encode_samples(const GridInfo& g, const float* table, const vo
 {
     const int64_t n_s = n_rays * S;
     if (n_s == 0) return hipSuccess;
-    if (table_f16)
-        hipLaunchKernelGGL(k_encode_samples<half2_t>, enc_grid(n_s, g.n_levels), dim3(kEncBlock), 0, s, g,
-                           (const half2_t*)table_f16, ray_obj, t, n_s, S, (float2*)y);
-    else
-        hipLaunchKernelGGL(k_encode_samples<float2>, enc_grid(n_s, g.n_levels), dim3(kEncBlock), 0, s, g,
-                           (const float2*)table, ray_obj, t, n_s, S, (float2*)y);
-    return hipGetLastError();
+    return table_f16 ? encode_samples(g, (const half2_t*)table_f16, ray_obj, t, n_s, S, (float2*)y, s)
+                     : encode_samples(g, (const float2*)table, ray_obj, t, n_s, S, (float2*)y, s);
 }
 
 hipError_t launch_encode_grid(const GridInfo& g, const float* table, const void* table_f16, int32_t R, int64_t p0,
@@ -324,10 +528,51 @@ hipError_t launch_density_grid(const float* sc, int64_t n, float* out, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_encode_batch(const ObjDev* objs, const ScatterObj* sobjs, int n_obj, int64_t n_items,
+void encode_split(const ObjDev* objs, ScatterObj* sobjs, int n_obj, int64_t& n_items, int64_t& n_lds)
+{
+    auto planes = [&](int i) {
+        return lds_planes(objs[i].table_dtype == PRENOM_F16 ? 4 : 8, objs[i].grid.log2_table);
+    };
+    // The run of all objects that could be staged; if it is too short for those of
+    // two passes, that of the others.
+    auto run_of = [&](int most) {
+        int64_t work = 0;
+        for (int i = 0; i < n_obj; ++i)
+            if (planes(i) && planes(i) <= most) work += sobjs[i].n_s * sobjs[i].grid.n_levels;
+        return lds_run(work);
+    };
+    const int most = lds_pays(2, run_of(2)) ? 2 : 1;
+    const int64_t run = run_of(most);
+    n_items = n_lds = 0;
+    for (int i = 0; i < n_obj; ++i) {
+        ScatterObj& o = sobjs[i];
+        o.item_off = n_items;
+        o.lds_off = n_lds;
+        o.n_runs = 0;
+        o.run = 0;
+        if (o.n_s > 0 && planes(i) <= most && lds_pays(planes(i), run)) {
+            const int64_t runs = (o.n_s + run - 1) / run;  // even ones
+            o.run = round_up((o.n_s + runs - 1) / runs, 64);
+            o.n_runs = (int32_t)((o.n_s + o.run - 1) / o.run);
+            n_lds += (int64_t)o.n_runs * o.grid.n_levels;
+        } else {
+            n_items += scatter_items(o);
+        }
+    }
+}
+
+hipError_t launch_encode_batch(const ObjDev* objs, const ScatterObj* sobjs, int n_obj, int64_t n_items, int64_t n_lds,
                                const float* params, const void* params_f16, const float* ray_obj, const float* t,
                                int32_t S, float* y, hipStream_t s)
 {
+    if (n_lds > 0) {
+        hipError_t e = hipFuncSetAttribute((const void*)k_encode_batch_lds, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           kLdsBytes);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_encode_batch_lds, dim3((uint32_t)n_lds), dim3(kLdsThreads), kLdsBytes, s, objs, sobjs,
+                           n_obj, params, (const half2_t*)params_f16, ray_obj, t, S, 1.0f / (float)S, (float2*)y);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     if (n_items == 0) return hipSuccess;
     hipLaunchKernelGGL(k_encode_batch, dim3((uint32_t)n_items), dim3(kScatterBlockSamples), 0, s, objs, sobjs, n_obj,
                        params, (const half2_t*)params_f16, ray_obj, t, S, (float2*)y);
