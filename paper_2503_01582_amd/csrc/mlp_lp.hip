@@ -25,10 +25,6 @@ typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 struct Bf16Op {
     using vec = short4_t;
     static __device__ __forceinline__ short cvt(float x) { return __builtin_bit_cast(short, (__bf16)x); }
-    static __device__ __forceinline__ float back(short h)
-    {
-        return __builtin_bit_cast(float, (uint32_t)(uint16_t)h << 16);
-    }
     static __device__ __forceinline__ floatx4 mma(vec a, vec b, floatx4 c)
     {
         return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
@@ -38,7 +34,6 @@ struct Bf16Op {
 struct F16Op {
     using vec = half4_t;
     static __device__ __forceinline__ _Float16 cvt(float x) { return (_Float16)x; }
-    static __device__ __forceinline__ float back(_Float16 h) { return (float)h; }
     static __device__ __forceinline__ floatx4 mma(vec a, vec b, floatx4 c)
     {
         return __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, c, 0, 0, 0);
@@ -60,12 +55,6 @@ template <class P>
 __device__ __forceinline__ typename P::vec pack(floatx4 x)
 {
     return pack<P>(x[0], x[1], x[2], x[3]);
-}
-
-template <class P>
-__device__ __forceinline__ floatx4 unpack(typename P::vec v)
-{
-    return {P::back(v[0]), P::back(v[1]), P::back(v[2]), P::back(v[3])};
 }
 
 // ReLU decisions of one sample and lane group q as bits: bit 4 to + r for neuron
@@ -286,27 +275,49 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
                                   wk.tile_begin + (threadIdx.x >> 6), wk.tile_end, blockDim.x / 64);
 }
 
+// The weight gradient contracts over samples, so its operands hold four samples
+// of a neuron, where the tiles hold four neurons of a sample.  The arrays are
+// staged in LDS in the MFMA type, a row per sample, and read transposed: a lane
+// writes its four neurons in 8 bytes, and ds_read_b64_tr_b16 hands lane (q, j) of
+// a 16-lane group neuron j of the four rows whose 8-byte pieces the group's
+// lanes address (lane 4 r + c: row r, piece c).  Rows are 8 banks apart modulo
+// the 64 banks, so that the reads of 8 rows meet no bank twice.
+constexpr int lds_pitch(int halves)  // of a staged row, in halfwords: 16 modulo 32
+{
+    return (halves + 31) / 32 * 32 + 16;
+}
+
+template <class V>
+__device__ __forceinline__ V read_transposed(const uint16_t* p)
+{
+    return __builtin_bit_cast(
+        V, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_t*)p));
+}
+
+template <class V>
+__device__ __forceinline__ void write_staged(uint16_t* p, V v)
+{
+    *reinterpret_cast<uint2*>(p) = __builtin_bit_cast(uint2, v);
+}
+
 template <int IN, int W, int D>
 struct BwdLdsLp {
     static constexpr int IP = 16 * NetLp<IN, W, D>::IT;
-    static constexpr int HW = (W > IP ? W : IP) + kStagePad;
-    static constexpr int DW = W + kStagePad;
-    static constexpr int PER_WAVE = 16 * (HW + DW);  // floats
+    static constexpr int PITCH = lds_pitch(W > IP ? W : IP);
+    static constexpr int PER_WAVE = 16 * PITCH;  // floats: two staged arrays of 16 rows of halfwords
 };
 
-template <int OTILES, int ITILES, int DP, int HP, class P>
-__device__ __forceinline__ void accumulate_dw_lp(const float* __restrict__ sD, const float* __restrict__ sH,
-                                                 floatx4 (&dw)[OTILES][ITILES], int q, int j)
+// dw += delta h^T over the wave's 16 staged samples; dp and hp are where the
+// lane's transposed reads begin.
+template <int OTILES, int ITILES, class P>
+__device__ __forceinline__ void accumulate_dw_lp(const uint16_t* __restrict__ dp, const uint16_t* __restrict__ hp,
+                                                 floatx4 (&dw)[OTILES][ITILES])
 {
     typename P::vec a[OTILES], b[ITILES];
 #pragma unroll
-    for (int to = 0; to < OTILES; ++to)
-        a[to] = pack<P>(sD[(4 * q) * DP + 16 * to + j], sD[(4 * q + 1) * DP + 16 * to + j],
-                        sD[(4 * q + 2) * DP + 16 * to + j], sD[(4 * q + 3) * DP + 16 * to + j]);
+    for (int to = 0; to < OTILES; ++to) a[to] = read_transposed<typename P::vec>(dp + 16 * to);
 #pragma unroll
-    for (int ti = 0; ti < ITILES; ++ti)
-        b[ti] = pack<P>(sH[(4 * q) * HP + 16 * ti + j], sH[(4 * q + 1) * HP + 16 * ti + j],
-                        sH[(4 * q + 2) * HP + 16 * ti + j], sH[(4 * q + 3) * HP + 16 * ti + j]);
+    for (int ti = 0; ti < ITILES; ++ti) b[ti] = read_transposed<typename P::vec>(hp + 16 * ti);
 #pragma unroll
     for (int to = 0; to < OTILES; ++to)
 #pragma unroll
@@ -325,8 +336,9 @@ __device__ __forceinline__ void mlp_bwd_tiles_lp(unsigned char* __restrict__ sme
     const typename P::vec* frag = reinterpret_cast<const typename P::vec*>(smem_lp);
     float* stage = reinterpret_cast<float*>(smem_lp + sizeof(typename P::vec) * N::N_ALL * 64);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, j = lane & 15;
-    float* sD = stage + wave * B::PER_WAVE;
-    float* sH = sD + 16 * B::DW;
+    uint16_t* sD = reinterpret_cast<uint16_t*>(stage + wave * B::PER_WAVE);
+    uint16_t* sH = sD + 16 * B::PITCH;
+    const int wr = j * B::PITCH + 4 * q, rd = (4 * q + j / 4) * B::PITCH + 4 * (j & 3);  // the lane's writes and reads
 
     floatx4 dW1[N::OT][N::IT];
     floatx4 dWh[D > 1 ? D - 1 : 1][N::OT][N::OT];
@@ -371,13 +383,15 @@ __device__ __forceinline__ void mlp_bwd_tiles_lp(unsigned char* __restrict__ sme
             const float c1 = sigmoidf_(o[1]), c2 = sigmoidf_(o[2]), c3 = sigmoidf_(o[3]);
             dO[0] = {g.x * __expf(o[0]), g.y * c1 * (1.0f - c1), g.z * c2 * (1.0f - c2), g.w * c3 * (1.0f - c3)};
         }
+        const typename P::vec dOp = pack<P>(dO[0]);
         wave_lds_sync();
-        stage_dw<1, N::OT, B::DW, B::HW>(sD, sH, dO, hs[D - 1], q, j);
+        write_staged(sD + wr, dOp);
+#pragma unroll
+        for (int ti = 0; ti < N::OT; ++ti) write_staged(sH + wr + 16 * ti, pack<P>(hs[D - 1][ti]));
         wave_lds_sync();
-        accumulate_dw_lp<1, N::OT, B::DW, B::HW, P>(sD, sH, dWo, q, j);
+        accumulate_dw_lp<1, N::OT, P>(sD + rd, sH + rd, dWo);
 
         floatx4 delta[N::OT];
-        const typename P::vec dOp = pack<P>(dO[0]);
 #pragma unroll
         for (int to = 0; to < N::OT; ++to) {
             floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -386,13 +400,17 @@ __device__ __forceinline__ void mlp_bwd_tiles_lp(unsigned char* __restrict__ sme
         }
 #pragma unroll
         for (int k = D - 1; k >= 1; --k) {
-            wave_lds_sync();
-            stage_dw<N::OT, N::OT, B::DW, B::HW>(sD, sH, delta, hs[k - 1], q, j);
-            wave_lds_sync();
-            accumulate_dw_lp<N::OT, N::OT, B::DW, B::HW, P>(sD, sH, dWh[k - 1], q, j);
             typename P::vec dp[N::OT];
 #pragma unroll
             for (int ti = 0; ti < N::OT; ++ti) dp[ti] = pack<P>(delta[ti]);
+            wave_lds_sync();
+#pragma unroll
+            for (int ti = 0; ti < N::OT; ++ti) {
+                write_staged(sD + wr + 16 * ti, dp[ti]);
+                write_staged(sH + wr + 16 * ti, pack<P>(hs[k - 1][ti]));
+            }
+            wave_lds_sync();
+            accumulate_dw_lp<N::OT, N::OT, P>(sD + rd, sH + rd, dWh[k - 1]);
 #pragma unroll
             for (int to = 0; to < N::OT; ++to) {
                 floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -402,21 +420,17 @@ __device__ __forceinline__ void mlp_bwd_tiles_lp(unsigned char* __restrict__ sme
                 delta[to] = mask_pos(acc, hs[k - 1][to]);
             }
         }
-        // layer 1: stage delta and the inputs (features 16 m + 4 q + r of sample j)
-        wave_lds_sync();
-#pragma unroll
-        for (int to = 0; to < N::OT; ++to)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) sD[j * B::DW + 16 * to + 4 * q + r] = delta[to][r];
-#pragma unroll
-        for (int m = 0; m < N::KB1; ++m)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) sH[j * B::HW + 16 * m + 4 * q + r] = yf[m][r];  // zero beyond IN
-        wave_lds_sync();
-        accumulate_dw_lp<N::OT, N::IT, B::DW, B::HW, P>(sD, sH, dW1, q, j);
+        // layer 1: stage delta and the inputs (features 16 m + 4 q + r of sample j, zero beyond IN)
         typename P::vec dp[N::OT];
 #pragma unroll
         for (int ti = 0; ti < N::OT; ++ti) dp[ti] = pack<P>(delta[ti]);
+        wave_lds_sync();
+#pragma unroll
+        for (int ti = 0; ti < N::OT; ++ti) write_staged(sD + wr + 16 * ti, dp[ti]);
+#pragma unroll
+        for (int m = 0; m < N::KB1; ++m) write_staged(sH + wr + 16 * m, pack<P>(yf[m]));
+        wave_lds_sync();
+        accumulate_dw_lp<N::OT, N::IT, P>(sD + rd, sH + rd, dW1);
 #pragma unroll
         for (int to = 0; to < N::IT; ++to) {
             floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -484,7 +498,7 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd_lp_batch(const MlpWo
 // one 16-sample tile per wave, recomputes the forward, runs the transposed chain
 // and accumulates the weight gradient, whose operands (four consecutive samples
 // of a neuron) go through LDS: deltas and activations of the 128 samples in the
-// MFMA type, neuron-major.  The waves split the output rows, 16 each, so the
+// MFMA type.  The waves split the output rows, 16 each, so the
 // block's partial is written without a merge.  Forward and transposed fragments
 // (86 KB with two layers) and the two staged arrays (68 KB) fill a CU's LDS.
 // Nothing but the features, the head outputs and their adjoint is read: storing
@@ -493,19 +507,20 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd_lp_batch(const MlpWo
 // objects, 28.5 M samples 128 wide: forward 4.0 and backward 10.3 ms).
 constexpr int kWideWavesLp = 8;
 constexpr int kWideChunk = 16 * kWideWavesLp;  // samples staged at a time
-constexpr int kWidePitch = kWideChunk + 8;     // halfwords per staged row: 272 bytes, so that a
-                                               // half wave's 8-byte reads of 16 rows miss each other's banks
+constexpr int kHeadPitch = kWideChunk + 8;     // halfwords per row of the staged head adjoint
 
 template <int IN, int W, int D>
 struct WideLdsLp {
     using N = NetLp<IN, W, D>;
     static constexpr int N_FRAG = N::FO + (N::N_ALL - N::N_FWD);  // hidden forward fragments, then the transposed ones
-    // staged rows, in halfwords from the end of the fragments
+    // staged arrays, a row per sample, in halfwords from the end of the fragments
+    static constexpr int PITCH = lds_pitch(W);
     static constexpr int A = 0;
-    static constexpr int B = A + W * kWidePitch;
-    static constexpr int DO = B + W * kWidePitch;           // head adjoint, 4 rows
-    static constexpr int Y = D == 1 ? DO + 4 * kWidePitch : B;  // inputs: beside the others, or in place of B
-    static constexpr int HALVES = D == 1 ? Y + 16 * N::IT * kWidePitch : DO + 4 * kWidePitch;
+    static constexpr int B = A + kWideChunk * PITCH;
+    static constexpr int Y_PITCH = D == 1 ? lds_pitch(16 * N::IT) : PITCH;
+    static constexpr int Y = D == 1 ? B + kWideChunk * PITCH : B;  // inputs: beside the others, or in place of B
+    static constexpr int DO = D == 1 ? Y + kWideChunk * Y_PITCH : B + kWideChunk * PITCH;  // head adjoint: 4 rows of samples
+    static constexpr int HALVES = DO + 4 * kHeadPitch;
     static constexpr size_t BYTES = (size_t)N_FRAG * 512 + sizeof(uint16_t) * (size_t)HALVES;
     static_assert(BYTES <= 160 * 1024 && (IN <= 32 && D <= 2), "LDS of one CU");
 };
@@ -531,17 +546,12 @@ __device__ __forceinline__ void mlp_wide_bwd_lp(unsigned char* __restrict__ smem
     load_fragments_lp<IN, W, D, P>(w, ffrag, N::FO);
     load_fragments_lp<IN, W, D, P>(w, bfrag, N::N_ALL - N::N_FWD, N::N_FWD);
     const int col = 16 * wave + j;  // the lane's sample within the chunk
-    // rows 16 t + 4 q + r of a staged array: the lane's values of sample `col`
-    auto put = [&](int base, int t, vec v) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const auto x = v[r];
-            st[base + (16 * t + 4 * q + r) * kWidePitch + col] = __builtin_bit_cast(uint16_t, x);
-        }
-    };
-    // samples k0 .. k0 + 3 of row `row`: an MFMA operand
-    auto op = [&](int base, int row, int k0) {
-        return __builtin_bit_cast(vec, *reinterpret_cast<const uint2*>(st + base + row * kWidePitch + k0));
+    // neurons 16 t + 4 q .. + 3 of sample `col`, into a staged array
+    auto put = [&](int base, int pitch, int t, vec v) { write_staged(st + base + col * pitch + 16 * t + 4 * q, v); };
+    // samples 16 ks + 4 q .. + 3 of neuron 16 t + j: an MFMA operand
+    const int row = 4 * q + j / 4, piece = 4 * (j & 3);
+    auto op = [&](int base, int pitch, int t, int ks) {
+        return read_transposed<vec>(st + base + (16 * ks + row) * pitch + 16 * t + piece);
     };
     floatx4 aH[N::OT], a1[N::IT], aO = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -549,25 +559,21 @@ __device__ __forceinline__ void mlp_wide_bwd_lp(unsigned char* __restrict__ smem
 #pragma unroll
     for (int t = 0; t < N::IT; ++t) a1[t] = {0.0f, 0.0f, 0.0f, 0.0f};
     // W_out: A[i][k] = dO_i (rows i >= 4 zero), B = the last layer's activations
-    // Two layers hold twice the sums, so their loops are not unrolled: with the
-    // registers of a second step 65536 rays x 48, 12 levels took 1264 us, without
-    // 1184; the one-layer kernel has them to spare (381 against 397).
     auto add_out = [&](int hbase) {
-#pragma unroll(D == 1 ? 2 : 1)
+#pragma unroll 2
         for (int ks = 0; ks < kWideChunk / 16; ++ks) {
-            const int k0 = 16 * ks + 4 * q;
-            vec d = op(L::DO, j & 3, k0);
+            vec d = __builtin_bit_cast(
+                vec, *reinterpret_cast<const uint2*>(st + L::DO + (j & 3) * kHeadPitch + 16 * ks + 4 * q));
             if (j >= 4) d = pack<P>(0.0f, 0.0f, 0.0f, 0.0f);
-            aO = P::mma(d, op(hbase, 16 * wave + j, k0), aO);
+            aO = P::mma(d, op(hbase, L::PITCH, wave, ks), aO);
         }
     };
     auto add_in = [&](int dbase) {  // W_1
-#pragma unroll(D == 1 ? 2 : 1)
+#pragma unroll 2
         for (int ks = 0; ks < kWideChunk / 16; ++ks) {
-            const int k0 = 16 * ks + 4 * q;
-            const vec av = op(dbase, 16 * wave + j, k0);
+            const vec av = op(dbase, L::PITCH, wave, ks);
 #pragma unroll
-            for (int t = 0; t < N::IT; ++t) a1[t] = P::mma(av, op(L::Y, 16 * t + j, k0), a1[t]);
+            for (int t = 0; t < N::IT; ++t) a1[t] = P::mma(av, op(L::Y, L::Y_PITCH, t, ks), a1[t]);
         }
     };
     // the next tile's inputs, upstream gradient and head outputs, loaded while
@@ -617,7 +623,13 @@ __device__ __forceinline__ void mlp_wide_bwd_lp(unsigned char* __restrict__ smem
             dp[to] = pack<P>(mask_by_bits(d, mask[D - 1], to));
         }
         auto put_out = [&] {
-            if (q == 0) put(L::DO, 0, dO);
+            if (q == 0) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const auto x = dO[r];
+                    st[L::DO + r * kHeadPitch + col] = __builtin_bit_cast(uint16_t, x);
+                }
+            }
         };
         auto store_dy = [&] {
             floatx4 gy[N::IT];
@@ -635,11 +647,11 @@ __device__ __forceinline__ void mlp_wide_bwd_lp(unsigned char* __restrict__ smem
         if constexpr (D == 1) {
 #pragma unroll
             for (int to = 0; to < N::OT; ++to) {
-                put(L::A, to, dp[to]);
-                put(L::B, to, hp[0][to]);
+                put(L::A, L::PITCH, to, dp[to]);
+                put(L::B, L::PITCH, to, hp[0][to]);
             }
 #pragma unroll
-            for (int m = 0; m < N::KB1; ++m) put(L::Y, m, yp[m]);
+            for (int m = 0; m < N::KB1; ++m) put(L::Y, L::Y_PITCH, m, yp[m]);
             put_out();
             __syncthreads();
             add_out(L::B);
@@ -649,8 +661,8 @@ __device__ __forceinline__ void mlp_wide_bwd_lp(unsigned char* __restrict__ smem
             // the last activations in A until W_out's gradient has them, then the deltas
 #pragma unroll
             for (int to = 0; to < N::OT; ++to) {
-                put(L::A, to, hp[D - 1][to]);
-                put(L::B, to, hp[0][to]);
+                put(L::A, L::PITCH, to, hp[D - 1][to]);
+                put(L::B, L::PITCH, to, hp[0][to]);
             }
             put_out();
             __syncthreads();
@@ -659,23 +671,22 @@ __device__ __forceinline__ void mlp_wide_bwd_lp(unsigned char* __restrict__ smem
             __syncthreads();
 #pragma unroll
             for (int to = 0; to < N::OT; ++to) {
-                put(L::A, to, dp[to]);
+                put(L::A, L::PITCH, to, dp[to]);
                 dp[to] = pack<P>(mask_by_bits(acc[to], mask[0], to));
             }
             __syncthreads();
-#pragma unroll 1
+#pragma unroll 2
             for (int ks = 0; ks < kWideChunk / 16; ++ks) {
-                const int k0 = 16 * ks + 4 * q;
-                const vec av = op(L::A, 16 * wave + j, k0);
+                const vec av = op(L::A, L::PITCH, wave, ks);
 #pragma unroll
-                for (int t = 0; t < N::OT; ++t) aH[t] = P::mma(av, op(L::B, 16 * t + j, k0), aH[t]);
+                for (int t = 0; t < N::OT; ++t) aH[t] = P::mma(av, op(L::B, L::PITCH, t, ks), aH[t]);
             }
             store_dy();
             __syncthreads();
 #pragma unroll
-            for (int to = 0; to < N::OT; ++to) put(L::A, to, dp[to]);
+            for (int to = 0; to < N::OT; ++to) put(L::A, L::PITCH, to, dp[to]);
 #pragma unroll
-            for (int m = 0; m < N::KB1; ++m) put(L::Y, m, yp[m]);
+            for (int m = 0; m < N::KB1; ++m) put(L::Y, L::Y_PITCH, m, yp[m]);
             __syncthreads();
             add_in(L::A);
         }
