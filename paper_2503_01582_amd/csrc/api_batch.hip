@@ -284,7 +284,12 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
         for (int i = 0; i < n; ++i)
             if (in_group(mlp_shape(&b->objects[i].arch))) tiles.push_back((b->objects[i].n_rays * S + 15) / 16);
         const int64_t run_f = run_length(tiles, g.fwd_tiles, kFwdQuantum, kCus);
-        const int64_t run_b = run_length(tiles, g.bwd_tiles, kBwdQuantum, kCus * bwd_blocks_per_cu(g.shape));
+        // FP32 weight gradients keep the tuned runs: a run's sums are rounded in one
+        // order, and another split moves their last bits, which a ReLU at zero can
+        // turn into a thousandth of a gradient one step later.
+        const int64_t run_b = g.shape.dtype == PRENOM_F32
+                                  ? g.bwd_tiles
+                                  : run_length(tiles, g.bwd_tiles, kBwdQuantum, kCus * bwd_blocks_per_cu(g.shape));
         for (int i = 0; i < n; ++i) {
             const prenom_arch* a = &b->objects[i].arch;
             const MlpShape m = mlp_shape(a);
@@ -622,13 +627,14 @@ prenom_status prenom_batch_render_bwd(const prenom_batch* batch, const prenom_re
     int32_t* nonfinite = batch->loss_scale ? batch->scaler_state : nullptr;
     for (const Group& g : p.groups) {
         const MlpWork* work = at<const MlpWork>(workspace, p.o_bwd) + g.bwd_first;
+        const MlpWork* fwd_work = at<const MlpWork>(workspace, p.o_fwd) + g.fwd_first;
         const int64_t n_mlp = mlp_params_of(g.shape);
         float* y = at<float>(workspace, p.y);
         float* dy = at<float>(workspace, p.dy);
         PRENOM_LAUNCH("k_mlp_bwd", s,
                       g.shape.dtype == PRENOM_F32
-                          ? launch_mlp_bwd_batch(g.shape, work, (int)g.n_bwd, batch->params, y, c.dout, c.sc, dy,
-                                                 partial + g.partial_off, n_mlp, at<float>(workspace, p.act), s)
+                          ? launch_mlp_bwd_batch(g.shape, work, (int)g.n_bwd, fwd_work, (int)g.n_fwd, batch->params, y, c.dout,
+                                                 c.sc, dy, partial + g.partial_off, n_mlp, at<float>(workspace, p.act), s)
                           : launch_mlp_bwd_lp_batch(g.shape, work, (int)g.n_bwd, batch->params, y, c.dout, c.sc, dy,
                                                     partial + g.partial_off, n_mlp, s));
     }

@@ -415,8 +415,9 @@ hipError_t launch_mlp_bwd_lp(const MlpShape& m, const float* w, const float* y, 
                              int64_t n_s, float* dy, float* partial, hipStream_t s);
 hipError_t launch_mlp_fwd_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
                                 const float* y, float* sc, float* act, hipStream_t s);
-hipError_t launch_mlp_bwd_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
-                                const float* y, const float* dout, const float* sc, float* dy, float* partial,
+// chain: the runs in which the 128-wide backward computes deltas and dy (any split).
+hipError_t launch_mlp_bwd_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const MlpWork* chain,
+                                int n_chain, const float* params, const float* y, const float* dout, const float* sc, float* dy, float* partial,
                                 int64_t slot_stride, float* act, hipStream_t s);
 hipError_t launch_mlp_fwd_lp_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
                                    const float* y, float* sc, hipStream_t s);

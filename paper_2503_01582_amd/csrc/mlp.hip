@@ -592,19 +592,22 @@ __device__ __forceinline__ void mlp_chain_bwd_tiles(const float* __restrict__ bf
 constexpr int kDwPitchF32 = kWideWidth + 16;  // 144 = 16 mod 64: lanes q one sample apart, no bank conflict
 constexpr int kDwPitchY = 48;
 
-template <int IN, int W, int D>
+// RS x CS: the blocks that share a range, each with its rows and columns of the
+// gradients (part: which); the first columns' blocks also take W_1 and W_out.
+template <int IN, int W, int D, int RS, int CS>
 __device__ __forceinline__ void mlp_dw_range(float* __restrict__ lds, const float* __restrict__ y, const float4* __restrict__ sc,
                              const float4* __restrict__ dout, const float* __restrict__ act,
                              const float* __restrict__ dlt, int64_t n_s, int64_t s_begin, int64_t s_end,
-                             float* __restrict__ dst)
+                             int part, float* __restrict__ dst)
 {
     using N = Net<IN, W, D>;
     constexpr int PW = kDwPitchF32, PY = kDwPitchY;
     using St = DwStage<W, D, PW, PY>;
-    constexpr int RT = N::OT / kWideWaves;
-    static_assert(N::OT % kWideWaves == 0 && W + 16 == PW, "rows per wave, pitch");
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, j = lane & 15;
-    floatx4 aH[D > 1 ? D - 1 : 1][RT][N::OT], a1[RT][N::IT], aO[RT];
+    constexpr int RT = N::OT / (kWideWaves * RS), CT = N::OT / CS;
+    static_assert(N::OT % (kWideWaves * RS) == 0 && N::OT % CS == 0 && W + 16 == PW, "rows per wave, pitch");
+    const int wave = (threadIdx.x >> 6) + kWideWaves * (part % RS), lane = threadIdx.x & 63, q = lane >> 4, j = lane & 15;
+    const int col0 = 16 * CT * (part / RS);
+    floatx4 aH[D > 1 ? D - 1 : 1][RT][CT], a1[RT][N::IT], aO[RT];
 #pragma unroll
     for (int a = 0; a < RT; ++a) {
         aO[a] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -613,7 +616,7 @@ __device__ __forceinline__ void mlp_dw_range(float* __restrict__ lds, const floa
 #pragma unroll
         for (int k = 0; k < (D > 1 ? D - 1 : 1); ++k)
 #pragma unroll
-            for (int t = 0; t < N::OT; ++t) aH[k][a][t] = {0.0f, 0.0f, 0.0f, 0.0f};
+            for (int t = 0; t < CT; ++t) aH[k][a][t] = {0.0f, 0.0f, 0.0f, 0.0f};
     }
     // the next chunk's global loads overlap the current chunk's MFMAs
     DwRegs<W, D, PY> R;
@@ -626,25 +629,27 @@ __device__ __forceinline__ void mlp_dw_range(float* __restrict__ lds, const floa
         for (int ks = 0; ks < kDwChunk / 4; ++ks) {
             const int r = 4 * ks + q;  // the lane's sample within the chunk
             // W_out: A[i][k] = dO_i (rows i >= 4 zero), B = h_{D-1}
-            const float dOi = j < 4 ? lds[St::DO + r * 4 + j] : 0.0f;
-            const float* hl = lds + St::AC + ((D - 1) * kDwChunk + r) * PW;
+            if (CS == 1 || col0 == 0) {
+                const float dOi = j < 4 ? lds[St::DO + r * 4 + j] : 0.0f;
+                const float* hl = lds + St::AC + ((D - 1) * kDwChunk + r) * PW;
 #pragma unroll
-            for (int a = 0; a < RT; ++a) aO[a] = mfma4(dOi, hl[16 * (RT * wave + a) + j], aO[a]);
+                for (int a = 0; a < RT; ++a) aO[a] = mfma4(dOi, hl[16 * (RT * wave + a) + j], aO[a]);
+            }
 #pragma unroll
             for (int k = 1; k < D; ++k) {
                 const float* dk = lds + St::DL + (k * kDwChunk + r) * PW;
                 const float* hk = lds + St::AC + ((k - 1) * kDwChunk + r) * PW;
-                float av[RT], bv[N::OT];
+                float av[RT], bv[CT];
 #pragma unroll
                 for (int a = 0; a < RT; ++a) av[a] = dk[16 * (RT * wave + a) + j];
 #pragma unroll
-                for (int t = 0; t < N::OT; ++t) bv[t] = hk[16 * t + j];
+                for (int t = 0; t < CT; ++t) bv[t] = hk[col0 + 16 * t + j];
 #pragma unroll
                 for (int a = 0; a < RT; ++a)
 #pragma unroll
-                    for (int t = 0; t < N::OT; ++t) aH[k - 1][a][t] = mfma4(av[a], bv[t], aH[k - 1][a][t]);
+                    for (int t = 0; t < CT; ++t) aH[k - 1][a][t] = mfma4(av[a], bv[t], aH[k - 1][a][t]);
             }
-            {
+            if (CS == 1 || col0 == 0) {
                 const float* d0 = lds + St::DL + r * PW;
                 const float* yr = lds + St::Y + r * PY;
                 float av[RT], bv[N::IT];
@@ -669,13 +674,13 @@ __device__ __forceinline__ void mlp_dw_range(float* __restrict__ lds, const floa
 #pragma unroll
             for (int t = 0; t < N::IT; ++t) {
                 const int col = 16 * t + j;
-                if (col < IN) dst[N::OFF_W1 + row * IN + col] = a1[a][t][r];
+                if (col < IN && (CS == 1 || col0 == 0)) dst[N::OFF_W1 + row * IN + col] = a1[a][t][r];
             }
 #pragma unroll
             for (int k = 1; k < D; ++k)
 #pragma unroll
-                for (int t = 0; t < N::OT; ++t) dst[N::OFF_H + (k - 1) * W * W + row * W + 16 * t + j] = aH[k - 1][a][t][r];
-            if (q == 0) dst[N::OFF_OUT + r * W + 16 * (RT * wave + a) + j] = aO[a][r];
+                for (int t = 0; t < CT; ++t) dst[N::OFF_H + (k - 1) * W * W + row * W + col0 + 16 * t + j] = aH[k - 1][a][t][r];
+            if (q == 0 && (CS == 1 || col0 == 0)) dst[N::OFF_OUT + r * W + 16 * (RT * wave + a) + j] = aO[a][r];
         }
 }
 
@@ -727,11 +732,11 @@ __global__ __launch_bounds__(64 * kWideWaves) void k_mlp_dw(const float* __restr
     extern __shared__ float dw_lds[];
     const int64_t b = (int64_t)blockIdx.x * tiles_per_block * 16;
     const int64_t e = min(b + tiles_per_block * 16, n_s);
-    mlp_dw_range<IN, W, D>(dw_lds, y, sc, dout, act, act + (int64_t)D * n_s * W, n_s, b, e,
+    mlp_dw_range<IN, W, D, 1, 1>(dw_lds, y, sc, dout, act, act + (int64_t)D * n_s * W, n_s, b, e, 0,
                            partial + (int64_t)blockIdx.x * N::N_PARAMS);
 }
 
-template <int IN, int W, int D>
+template <int IN, int W, int D, int RS, int CS>
 __global__ __launch_bounds__(64 * kWideWaves) void k_mlp_dw_batch(const MlpWork* __restrict__ work,
                                                                   const float* __restrict__ y,
                                                                   const float4* __restrict__ sc,
@@ -743,8 +748,8 @@ __global__ __launch_bounds__(64 * kWideWaves) void k_mlp_dw_batch(const MlpWork*
     const MlpWork wk = work[blockIdx.x];
     const int64_t b = wk.tile_begin * 16, e = min(wk.tile_end * 16, wk.n_s);
     const float* a = act + wk.a_off;
-    mlp_dw_range<IN, W, D>(dw_lds, y + wk.y_off, sc + wk.s_off, dout + wk.s_off, a, a + (int64_t)D * wk.n_s * W, wk.n_s,
-                           b, e, partial + (int64_t)blockIdx.x * slot_stride);
+    mlp_dw_range<IN, W, D, RS, CS>(dw_lds, y + wk.y_off, sc + wk.s_off, dout + wk.s_off, a, a + (int64_t)D * wk.n_s * W,
+                           wk.n_s, b, e, (int)blockIdx.y, partial + (int64_t)blockIdx.x * slot_stride);
 }
 
 // Batch: thread per (object, MLP parameter); the object's partials summed in FP64.
@@ -855,22 +860,37 @@ hipError_t fwd_batch_impl(const MlpWork* work, int n_blocks, const float* params
     return hipGetLastError();
 }
 
+template <int IN, int W, int D, int RS, int CS>
+hipError_t dw_batch(const MlpWork* work, int n_blocks, const float* y, const float* dout, const float* sc,
+                    const float* act, float* partial, int64_t slot_stride, hipStream_t s)
+{
+    const size_t lds = dw_lds_bytes<IN, W, D>();
+    const hipError_t e = set_lds(k_mlp_dw_batch<IN, W, D, RS, CS>, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_mlp_dw_batch<IN, W, D, RS, CS>), dim3((uint32_t)n_blocks, RS * CS), dim3(64 * kWideWaves), lds,
+                       s, work, y, (const float4*)sc, (const float4*)dout, act, partial, slot_stride);
+    return hipGetLastError();
+}
+
 template <int IN, int W, int D>
-hipError_t bwd_batch_impl(const MlpWork* work, int n_blocks, const float* params, const float* y, const float* dout,
-                          const float* sc, float* dy, float* partial, int64_t slot_stride, float* act, hipStream_t s)
+hipError_t bwd_batch_impl(const MlpWork* work, int n_blocks, const MlpWork* chain, int n_chain, const float* params,
+                          const float* y, const float* dout, const float* sc, float* dy, float* partial,
+                          int64_t slot_stride, float* act, hipStream_t s)
 {
     if constexpr (W >= kWideWidth) {
         const size_t lds = chain_bwd_lds_bytes<IN, W, D>();
         hipError_t e = set_lds(k_mlp_chain_bwd_batch<IN, W, D>, lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_mlp_chain_bwd_batch<IN, W, D>), dim3((uint32_t)n_blocks), dim3(fwd_threads(W)), lds, s, work,
+        hipLaunchKernelGGL((k_mlp_chain_bwd_batch<IN, W, D>), dim3((uint32_t)n_chain), dim3(fwd_threads(W)), lds, s, chain,
                            params, (const float4*)sc, (const float4*)dout, act, (float2*)dy);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        const size_t dwl = dw_lds_bytes<IN, W, D>();
-        if ((e = set_lds(k_mlp_dw_batch<IN, W, D>, dwl)) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_mlp_dw_batch<IN, W, D>), dim3((uint32_t)n_blocks), dim3(64 * kWideWaves), dwl, s, work, y,
-                           (const float4*)sc, (const float4*)dout, act, partial, slot_stride);
-        return hipGetLastError();
+        // Few ranges leave CUs idle, and a range's sums are one chain of additions: up
+        // to a quarter of the CUs, its rows and columns go to four blocks, each staging
+        // the whole range (59 ranges 274 -> 198 us, 11 ranges 288 -> 196; 134 ranges
+        // 323 -> 443).
+        if (4 * (int64_t)n_blocks <= kCus)
+            return dw_batch<IN, W, D, 2, 2>(work, n_blocks, y, dout, sc, act, partial, slot_stride, s);
+        return dw_batch<IN, W, D, 1, 1>(work, n_blocks, y, dout, sc, act, partial, slot_stride, s);
     } else {
         const size_t lds = bwd_lds_bytes<IN, W, D>();
         auto kern = k_mlp_bwd_batch<IN, W, D>;
@@ -948,14 +968,14 @@ hipError_t launch_mlp_fwd_batch(const MlpShape& m, const MlpWork* work, int n_bl
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_mlp_bwd_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const float* params,
-                                const float* y, const float* dout, const float* sc, float* dy, float* partial,
+hipError_t launch_mlp_bwd_batch(const MlpShape& m, const MlpWork* work, int n_blocks, const MlpWork* chain,
+                                int n_chain, const float* params, const float* y, const float* dout, const float* sc, float* dy, float* partial,
                                 int64_t slot_stride, float* act, hipStream_t s)
 {
     if (n_blocks == 0) return hipSuccess;
 #define X(I, Wd, Dp)                                                                                   \
     if (m.in_dim == I && m.width == Wd && m.hidden == Dp)                                            \
-        return bwd_batch_impl<I, Wd, Dp>(work, n_blocks, params, y, dout, sc, dy, partial, slot_stride, act, s);
+        return bwd_batch_impl<I, Wd, Dp>(work, n_blocks, chain, n_chain, params, y, dout, sc, dy, partial, slot_stride, act, s);
     PRENOM_FOR_EACH_MLP(X)
 #undef X
     return hipErrorInvalidValue;
