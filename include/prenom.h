@@ -360,8 +360,9 @@ typedef struct prenom_object {
  * autotuner; shapes without an entry use defaults).  fwd_tiles: at most so many
  * 16-sample tiles per forward block, a multiple of 4 in [4, 4096]; bwd_tiles:
  * per backward block (each writes one partial weight gradient), a multiple of
- * 32 in [32, 1024].  A launch whose objects would leave CUs idle with these
- * takes shorter runs. */
+ * 32 in [32, 1024].  A forward or 16-bit backward launch whose objects would
+ * leave CUs idle with these takes shorter runs; the FP32 weight gradients keep
+ * bwd_tiles, as their last bits depend on it. */
 typedef struct prenom_mlp_tiles {
     int32_t in_dim, width, hidden, dtype;
     int32_t fwd_tiles, bwd_tiles;

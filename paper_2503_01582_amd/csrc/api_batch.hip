@@ -96,15 +96,14 @@ void tiles_for(const prenom_batch* b, const MlpShape& m, int& fwd, int& bwd)
 // round and a bit of them.  So the tuned (or default) length is the longest
 // one used, and the length is the shortest multiple of the quantum (the tiles
 // a block's waves take at once) that needs no more rounds of `target` blocks
-// than the tuned length does.  Measured on gfx950, forward and backward of a
-// step: 16 objects of 18000 rays together 4.59 -> 1.8 ms, 24 objects of
-// 338571 rays 15.0 -> 12.5 ms, 48 objects in BF16 19.2 -> 18.9 ms; two rounds
-// in place of one (512 forward blocks) 0.56 against 0.51 ms on the 16 objects,
-// and 0.81 against 0.77 ms backward on a meta-iteration's 64-wide network.
+// than the tuned length does.  Measured on gfx950, forward of a step: 16 objects
+// of 18000 rays together 0.96 -> 0.45 ms, 24 objects of 338571 rays 3.46 -> 3.07;
+// two rounds in place of one (512 blocks) 0.56 against 0.51 ms on the 16 objects.
+// The 128-wide FP32 chain runs in the forward's runs (16 objects: backward 2.40
+// -> 1.96 ms); 16-bit backward, 48 objects 10.83 -> 10.64 ms.
 constexpr int64_t kFwdQuantum = 4, kBwdQuantum = 8;
 
-// Backward blocks that one CU's LDS holds at a time: the 32-wide kernels' 50 KB
-// leave room for two.
+// 16-bit backward blocks that a CU holds at a time.
 int64_t bwd_blocks_per_cu(const MlpShape& m) { return m.width <= 32 ? 2 : 1; }
 
 // Tiles per work item of a launch over objects of `tiles` 16-sample tiles.
