@@ -238,14 +238,6 @@ int64_t buffered_rays(int64_t n_rays, int32_t S, bool recompute)
     return n_rays < c ? n_rays : c;
 }
 
-// Scatter geometry of one object in a pass of its own.
-ScatterObj scatter_plan(const GridInfo& g, int64_t n_s)
-{
-    ScatterObj o = scatter_obj(g, n_s);
-    scatter_split(o, scatter_target(scatter_records(o)));
-    return o;
-}
-
 WsLayout ws_layout(const prenom_arch* a, int64_t n_rays_all, int32_t S, bool recompute)
 {
     WsLayout w{};
@@ -481,6 +473,10 @@ prenom_status prenom_render_bwd(const prenom_model* model, const prenom_render_c
         const int64_t nr = n_rays - r0 < chunk ? n_rays - r0 : chunk;
         const int64_t n_s = nr * S;
         const ScatterObj plan = scatter_plan(g, n_s);
+        // (w.plan is of the longest pass)
+        if (scatter_items(plan) > scatter_items(w.plan) || scatter_segs(plan) > scatter_segs(w.plan) ||
+            plan.n_parts > w.plan.n_parts)
+            return fail(PRENOM_ERR_WORKSPACE, "scatter of %lld samples does not fit the workspace", (long long)n_s);
         const float* ro = ray_obj + 6 * r0;
         const float* tc = t + S * r0;
         CompositeArgs c{};

@@ -232,10 +232,9 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
             ++i;
         } while (i < n && g.records + scatter_records(p.sc[i]) <= budget);
         g.count = i - g.first;
-        const int64_t target = scatter_target(g.records);
         for (int k = g.first; k < i; ++k) {
             ScatterObj& lo = p.sc_pass[k];
-            scatter_split(lo, target);
+            scatter_split(lo, g.records);
             lo.item_off = g.n_items;
             lo.lev_off = g.n_levels;
             lo.seg_off = g.n_segs;

@@ -337,10 +337,11 @@ int64_t scatter_items(const ScatterObj& o);      // L * n_blocks
 int64_t scatter_records(const ScatterObj& o);    // record capacity: 4096 per item
 int64_t scatter_segs(const ScatterObj& o);       // segment starts
 int scatter_tiles_max(const ScatterObj& o);      // max tiles of one level
-// Records a reduce item of a pass over `records` of capacity should take, and
-// the object's split of its tiles into such items.
-int64_t scatter_target(int64_t records);
-void scatter_split(ScatterObj& o, int64_t target);
+// The object's split of its tiles into reduce items, in a pass over `records`
+// of capacity.
+void scatter_split(ScatterObj& o, int64_t records);
+// Geometry of an object in a pass of its own; no array of it grows when n_s falls.
+ScatterObj scatter_plan(const GridInfo& g, int64_t n_s);
 size_t scatter_part_bytes();                     // one partial sum
 
 struct ScatterArgs {

@@ -610,21 +610,21 @@ int64_t scatter_items(const ScatterObj& o) { return (int64_t)o.grid.n_levels * o
 int64_t scatter_records(const ScatterObj& o) { return scatter_items(o) * kRecordsPerBlock; }
 int64_t scatter_segs(const ScatterObj& o) { return (int64_t)o.n_blocks * (o.n_tiles + o.grid.n_levels); }
 
-int64_t scatter_target(int64_t records)
-{
-    const int64_t t = records / kReduceItems;
-    return t > kReduceMinRecords ? t : kReduceMinRecords;
-}
-
 // Every tile of a level is estimated at an even share of the level's records.
-void scatter_split(ScatterObj& o, int64_t target)
+// A tile's ranges are ceil(kReduceItems times its share of the pass, or of
+// kReduceItems * kReduceMinRecords records in a smaller pass) in whole numbers:
+// with an object alone in its pass the share does not fall when its samples
+// grow, so a plan of fewer samples fits the arrays of one of more (rounded
+// quotients would ask for one range more whenever they pass an integer).
+void scatter_split(ScatterObj& o, int64_t records)
 {
+    const int64_t pass = records > kReduceItems * kReduceMinRecords ? records : kReduceItems * kReduceMinRecords;
     o.n_ritems = o.n_ctiles = 0;
     o.n_parts = 0;
     for (int l = 0; l < o.grid.n_levels; ++l) {
-        const int64_t per_tile = (int64_t)o.n_blocks * kRecordsPerBlock / o.tiles[l];
-        int64_t k = (per_tile + target - 1) / target;
-        k = k < 1 ? 1 : k > o.n_blocks ? o.n_blocks : k;
+        const int64_t level = (int64_t)o.n_blocks * kRecordsPerBlock * kReduceItems;  // < 2^43
+        int64_t k = (level + o.tiles[l] * pass - 1) / (o.tiles[l] * pass);
+        k = k > o.n_blocks ? o.n_blocks : k;
         if (k < 1) k = 1;
         o.split[l] = (int32_t)k;
         o.ritem_base[l] = o.n_ritems;
@@ -636,6 +636,13 @@ void scatter_split(ScatterObj& o, int64_t target)
             o.n_ctiles += o.tiles[l];
         }
     }
+}
+
+ScatterObj scatter_plan(const GridInfo& g, int64_t n_s)
+{
+    ScatterObj o = scatter_obj(g, n_s);
+    scatter_split(o, scatter_records(o));
+    return o;
 }
 
 size_t scatter_part_bytes() { return sizeof(unsigned long long) * 2 * kTileRows; }
