@@ -59,7 +59,8 @@ struct Plan {
     std::vector<Group> groups;
     int64_t n_rays = 0, n_params = 0, n_mlp_total = 0, n_items = 0, n_lds = 0;
     int64_t y_floats = 0, partial_floats = 0, act_floats = 0;
-    int64_t records = 0, pass_items = 0, pass_segs = 0, pass_parts = 0;  // largest of any scatter pass
+    int64_t fwd_capacity = 0, bwd_capacity = 0;               // work items the lists hold
+    int64_t records = 0, pass_items = 0, pass_segs = 0;  // largest of any scatter pass
     int32_t pass_levels = 0, tiles_max = 1;
     bool any_f16_table = false, all_f16_table = true;
     // workspace offsets (bytes)
@@ -106,14 +107,18 @@ constexpr int64_t kFwdQuantum = 4, kBwdQuantum = 8;
 // 16-bit backward blocks that a CU holds at a time.
 int64_t bwd_blocks_per_cu(const MlpShape& m) { return m.width <= 32 ? 2 : 1; }
 
-// Tiles per work item of a launch over objects of `tiles` 16-sample tiles.
+// Work items of runs of `run` tiles over objects of `tiles` 16-sample tiles.
+int64_t run_items(const std::vector<int64_t>& tiles, int64_t run)
+{
+    int64_t k = 0;
+    for (int64_t t : tiles) k += (t + run - 1) / run;
+    return k;
+}
+
+// Tiles per work item of a launch over them.
 int64_t run_length(const std::vector<int64_t>& tiles, int64_t most, int64_t quantum, int64_t target)
 {
-    auto items = [&](int64_t run) {
-        int64_t k = 0;
-        for (int64_t t : tiles) k += (t + run - 1) / run;
-        return k;
-    };
+    auto items = [&](int64_t run) { return run_items(tiles, run); };
     const int64_t bound = round_up(items(most), target);
     int64_t lo = 1, hi = round_up(most, quantum) / quantum;  // in quanta; items(hi) <= bound
     while (lo < hi) {
@@ -124,6 +129,15 @@ int64_t run_length(const std::vector<int64_t>& tiles, int64_t most, int64_t quan
             lo = mid + 1;
     }
     return hi * quantum < most ? hi * quantum : most;
+}
+
+// Work items that the arrays of such a launch hold: no fewer than run_length
+// gives, and no more for fewer tiles (its own number falls where a tile more
+// takes a longer run).
+int64_t run_capacity(const std::vector<int64_t>& tiles, int64_t most, int64_t quantum, int64_t target)
+{
+    const int64_t a = run_items(tiles, quantum), b = round_up(run_items(tiles, most), target);
+    return a < b ? a : b;
 }
 
 prenom_status check_objects(const prenom_object* objs, int32_t n)
@@ -251,7 +265,6 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
         p.records = g.records > p.records ? g.records : p.records;
         p.pass_items = g.n_items > p.pass_items ? g.n_items : p.pass_items;
         p.pass_segs = g.n_segs > p.pass_segs ? g.n_segs : p.pass_segs;
-        p.pass_parts = g.n_parts > p.pass_parts ? g.n_parts : p.pass_parts;
         p.pass_levels = g.n_levels > p.pass_levels ? g.n_levels : p.pass_levels;
         p.sgroups.push_back(g);
     }
@@ -282,12 +295,15 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
         for (int i = 0; i < n; ++i)
             if (in_group(mlp_shape(&b->objects[i].arch))) tiles.push_back((b->objects[i].n_rays * S + 15) / 16);
         const int64_t run_f = run_length(tiles, g.fwd_tiles, kFwdQuantum, kCus);
+        p.fwd_capacity += run_capacity(tiles, g.fwd_tiles, kFwdQuantum, kCus);
         // FP32 weight gradients keep the tuned runs: a run's sums are rounded in one
         // order, and another split moves their last bits, which a ReLU at zero can
         // turn into a thousandth of a gradient one step later.
-        const int64_t run_b = g.shape.dtype == PRENOM_F32
-                                  ? g.bwd_tiles
-                                  : run_length(tiles, g.bwd_tiles, kBwdQuantum, kCus * bwd_blocks_per_cu(g.shape));
+        const bool fixed = g.shape.dtype == PRENOM_F32;
+        const int64_t fill = kCus * bwd_blocks_per_cu(g.shape);
+        const int64_t run_b = fixed ? g.bwd_tiles : run_length(tiles, g.bwd_tiles, kBwdQuantum, fill);
+        const int64_t slots = fixed ? run_items(tiles, run_b) : run_capacity(tiles, g.bwd_tiles, kBwdQuantum, fill);
+        p.bwd_capacity += slots;
         for (int i = 0; i < n; ++i) {
             const prenom_arch* a = &b->objects[i].arch;
             const MlpShape m = mlp_shape(a);
@@ -318,7 +334,7 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
         g.n_fwd = (int64_t)p.fwd.size() - g.fwd_first;
         g.n_bwd = (int64_t)p.bwd.size() - g.bwd_first;
         const int64_t n_mlp = mlp_params_of(g.shape);
-        partial += g.n_bwd * n_mlp;
+        partial += slots * n_mlp;
         if (g.n_fwd >= ((int64_t)1 << 31) || g.n_bwd >= ((int64_t)1 << 31))
             return fail(PRENOM_ERR_SHAPE, "MLP grid too large");
     }
@@ -339,8 +355,8 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
     p.o_sc = take(sizeof(ScatterObj) * n);
     p.o_sc_pass = take(sizeof(ScatterObj) * n);
     p.o_red = take(sizeof(MlpRed) * n);
-    p.o_fwd = take(sizeof(MlpWork) * p.fwd.size());
-    p.o_bwd = take(sizeof(MlpWork) * p.bwd.size());
+    p.o_fwd = take(sizeof(MlpWork) * (size_t)p.fwd_capacity);
+    p.o_bwd = take(sizeof(MlpWork) * (size_t)p.bwd_capacity);
     p.y = take(sizeof(float) * (size_t)p.y_floats);
     p.sc_out = take(sizeof(float) * 4 * n_s);
     p.dout = take(sizeof(float) * 4 * n_s);
@@ -352,7 +368,7 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
     p.seg = take(sizeof(uint16_t) * (size_t)p.pass_segs);
     p.block_max = take(sizeof(float) * (size_t)p.pass_items);
     p.level_exp = take(sizeof(int32_t) * (size_t)p.pass_levels);
-    p.parts = take(scatter_part_bytes() * (size_t)p.pass_parts);
+    p.parts = take(scatter_part_bytes() * (size_t)scatter_parts_most(p.records));
     p.recs = take(sizeof(uint64_t) * (size_t)p.records);
     p.total = off;
     return PRENOM_OK;

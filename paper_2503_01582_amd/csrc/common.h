@@ -342,6 +342,9 @@ int scatter_tiles_max(const ScatterObj& o);      // max tiles of one level
 void scatter_split(ScatterObj& o, int64_t records);
 // Geometry of an object in a pass of its own; no array of it grows when n_s falls.
 ScatterObj scatter_plan(const GridInfo& g, int64_t n_s);
+// Partial sums that a pass over `records` needs at most, however they are spread
+// over objects and levels.
+int64_t scatter_parts_most(int64_t records);
 size_t scatter_part_bytes();                     // one partial sum
 
 struct ScatterArgs {

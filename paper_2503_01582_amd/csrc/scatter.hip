@@ -645,6 +645,14 @@ ScatterObj scatter_plan(const GridInfo& g, int64_t n_s)
     return o;
 }
 
+// A level in k = ceil(x) > 1 ranges a tile has tiles * k < 2 tiles * x parts, and
+// the tiles * x of a pass's levels add up to kReduceItems at most.
+int64_t scatter_parts_most(int64_t records)
+{
+    const int64_t full = kReduceItems * kReduceMinRecords;
+    return records < full ? 2 * records / kReduceMinRecords : 2 * kReduceItems;
+}
+
 size_t scatter_part_bytes() { return sizeof(unsigned long long) * 2 * kTileRows; }
 
 int scatter_tiles_max(const ScatterObj& o)

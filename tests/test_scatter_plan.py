@@ -56,3 +56,70 @@ def test_workspace_size_grows_with_the_rays(levels, log2t, S, recompute):
         size = api.prenom_workspace_size(arch, n, S, recompute=recompute)
         assert size >= last, f"{n} rays need {size} bytes, fewer rays {last}"
         last = size
+
+
+MIXED = r"""
+    srand(5);
+    for (int trial = 0; trial < 4000; ++trial) {
+        std::vector<ScatterObj> objs(1 + rand() % 48);
+        int64_t records = 0;
+        for (ScatterObj& o : objs) {
+            GridInfo g{};
+            g.n_levels = 1 + rand() % PRENOM_MAX_LEVELS;
+            g.log2_table = 10 + rand() % 15;
+            for (int l = 0; l < g.n_levels; ++l) {
+                g.res[l] = 2 + rand() % 400;
+                const int64_t side = g.res[l] + 1;
+                if (side * side * side <= (int64_t)1 << g.log2_table) g.dense_mask |= 1u << l;
+            }
+            o = scatter_obj(g, (int64_t)(rand() % 1000) << rand() % 15);
+            records += scatter_records(o);
+        }
+        int64_t parts = 0;
+        for (ScatterObj& o : objs) {
+            scatter_split(o, records);
+            parts += o.n_parts;
+        }
+        CHECK(parts <= scatter_parts_most(records), "trial %d: %lld records need %lld parts, reserved %lld\n", trial,
+              (long long)records, (long long)parts, (long long)scatter_parts_most(records));
+    }
+    for (int64_t r = 0; r < 40000000; r += 4096)
+        CHECK(scatter_parts_most(r) <= scatter_parts_most(r + 4096), "%lld records\n", (long long)r);
+"""
+
+
+def test_parts_of_a_batch_pass_fit(tmp_path):
+    out = run_plan_program(tmp_path, MIXED)
+    assert out == "ok\n", out
+
+
+def batch_size(shapes, rays, S, tiles=()):
+    """Workspace of a batch of objects, from its sizes alone."""
+    import ctypes as C
+
+    from paper_2503_01582_amd import _lib as L
+    from paper_2503_01582_amd import batch as B
+    from synth.workloads import nocs_affine
+    objs = B._c_objects([B.BatchObject(a, n, None, nocs_affine()) for a, n in zip(shapes, rays)])
+    b = L.PrenomBatch()
+    b.n_objects, b.objects = len(shapes), C.cast(objs, C.POINTER(L.PrenomObject))
+    arr, b.n_tiles = B._c_tiles(tiles)
+    b.tiles = C.cast(arr, C.POINTER(L.PrenomMlpTiles))
+    size = L.lib().prenom_batch_workspace_size(C.byref(b), S)
+    assert size > 0
+    return size
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("width", [32, 128])
+def test_batch_workspace_size_grows_with_an_object(width, dtype):
+    """One of three objects grows from nothing through the lengths at which the
+    MLP runs and the scatter's ranges change; the batch stays one scatter pass."""
+    shapes = [Arch(n_levels=8, log2_table=14, width=width, hidden=2, mlp_dtype=dtype),
+              Arch(n_levels=16, log2_table=17, width=32, hidden=1, mlp_dtype=dtype),
+              Arch(n_levels=8, log2_table=11, width=width, hidden=2, mlp_dtype=dtype)]
+    S, last = 16, 0
+    for n in list(range(0, 9000, 37)) + list(range(9000, 60000, 997)):
+        size = batch_size(shapes, [n, 3000, 800], S)
+        assert size >= last, f"{n} rays need {size} bytes, fewer rays {last}"
+        last = size
