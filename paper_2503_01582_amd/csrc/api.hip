@@ -644,11 +644,7 @@ prenom_status prenom_reptile_update(float* theta, float* tasks, int64_t n_params
 size_t prenom_canonical_yaw_workspace_size(int64_t n_points, int32_t n_yaw)
 {
     if (n_points < 1 || n_points > PRENOM_MAX_YAW_POINTS || n_yaw < 1 || n_yaw > PRENOM_MAX_YAWS) return 0;
-    YawArgs a{};
-    a.n = n_points;
-    a.K = n_yaw;
-    yaw_split(a);
-    return align_up(yaw_doubles(a) * sizeof(double));
+    return align_up(yaw_doubles_most(n_points, n_yaw) * sizeof(double));
 }
 
 prenom_status prenom_canonical_yaw(const float* points, int64_t n_points, const float* prior, int32_t prior_res,

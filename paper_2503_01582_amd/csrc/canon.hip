@@ -378,6 +378,23 @@ size_t yaw_doubles(const YawArgs& a)
     return (size_t)(a.K * a.n_chunks + (4 * (int64_t)a.K + 2) * (a.n_ext + 1) + 2 * (int64_t)a.K);
 }
 
+// The split's numbers of chunks rise and fall with the points and the yaws; this
+// is at least yaw_doubles of any split of n points or fewer and K yaws or fewer.
+// Score chunks hold 32 points at least, and there are at most 4 kCus / groups or
+// one per 4096 points, of groups that hold at most 64 yaws each; extents chunks
+// hold 64 points, and there are at most kYawJoin, or one per 1024 points and
+// either 2 kCus / groups + 1 or one per 16384 points.
+size_t yaw_doubles_most(int64_t n, int64_t K)
+{
+    const int64_t by_points = K * div_up(n, 32), by_blocks = 64 * 4 * kCus + K * div_up(n, 4096);
+    const int64_t ext_points = K * div_up(n, 1024), ext_blocks = 64 * 2 * kCus + K + K * div_up(n, 16384);
+    const int64_t sums = by_points < by_blocks ? by_points : by_blocks;
+    const int64_t short_ext = div_up(n, 64) < kYawJoin ? div_up(n, 64) : kYawJoin;
+    const int64_t ext = K * short_ext + (ext_points < ext_blocks ? ext_points : ext_blocks);
+    const int64_t z = short_ext + div_up(n, 1024);
+    return (size_t)(sums + 4 * (ext + K) + 2 * (z + 1) + 2 * K);
+}
+
 void yaw_place(YawArgs& a, double* ws)
 {
     a.turn = (double2*)ws;

@@ -575,6 +575,7 @@ struct YawArgs {
 };
 void yaw_split(YawArgs& a);
 size_t yaw_doubles(const YawArgs& a);
+size_t yaw_doubles_most(int64_t n, int64_t K);  // of any call of up to n points and K yaws
 void yaw_place(YawArgs& a, double* ws);
 hipError_t launch_canonical_yaw(YawArgs a, hipStream_t s);
 
