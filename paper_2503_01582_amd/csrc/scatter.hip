@@ -71,7 +71,7 @@ constexpr int64_t kReduceMinRecords = 1 << 15;
 // (EB bits) and the two's-complement mantissas qx, qy (MB bits each); its
 // value is (qx, qy) * 2^(E - r - (MB - 1)), E being the record exponent of
 // its item (level, sample block).  A record whose larger feature lies below
-// 2^(E - 2^EB) has the largest r and fewer significant bits.  Two formats:
+// 2^(E - r), r at its largest, has fewer significant bits.  Two formats:
 //   full:    EB = 7, MB = 22, one 64-bit word (21 significant bits);
 //   compact: EB = 5, MB = 15, 48 bits kept as a 32-bit word (bits 0-31) in
 //            one array and a 16-bit word (bits 32-47) in another (14
@@ -85,14 +85,19 @@ static_assert(kTileBits + kRecExpBits + 2 * kRecMantBits == 64, "record fields f
 
 // Record exponent E of a block whose largest |dy| is bm: a record sums at most
 // 8 contributions w dy with 0 <= w <= 1, so |record| <= 8 bm < 2^(E - 1).
-// Held at 2^kExpFloor, so that every scale stays a normal number.
-constexpr int kExpFloor = -100;
 __device__ __forceinline__ int block_rec_exp(float bm)
 {
     int e = 0;
     frexpf(bm, &e);  // bm < 2^e
-    return max(e + 4, kExpFloor);
+    return e + 4;
 }
+
+// A record is encoded by a product with 2^(MB - 1 - E + r), which has to be a
+// normal number: r goes up to E + 100, and a block with E below kTinyExp has its
+// values multiplied by 2^kTinyUp first (exact; E then is within -48 and 51).  So
+// r reaches 52 at least, unless its field ends before or no FP32 value needs as
+// much, and what it does not reach is below the fixed point's rounding.
+constexpr int kTinyExp = -44, kTinyUp = 96;
 
 // max(|x|, |y|) in one instruction (fmaxf would first quiet both operands).
 __device__ __forceinline__ float max_abs(float x, float y)
@@ -114,8 +119,8 @@ __device__ __forceinline__ int clamp0(int v, int hi)
 // rounded to nearest by adding 1.5 * 2^23 (the sum's unit in the last place is
 // 1, its low bits the two's complement of the integer); the larger one can
 // round up to 2^(MB-1), one past the field: it is held at 2^(MB-1) - 1 (an
-// error of one unit in its last place).  r_max: the largest exponent offset,
-// by the field and by kExpFloor; a smaller record keeps it and fewer bits.
+// error of one unit in its last place).  r_max: the largest exponent offset; a
+// smaller record keeps it and fewer bits.
 template <int EB, int MB>
 __device__ __forceinline__ void encode_record(float2 v, int E, int r_max, uint32_t row, uint32_t& lo, uint32_t& hi)
 {
@@ -144,11 +149,12 @@ __device__ __forceinline__ void decode_record(uint32_t lo, uint32_t hi, uint32_t
     qy = (int)((uint32_t)(w >> (kTileBits + EB + MB)) << (32 - MB)) >> (32 - MB);
 }
 
-// q * 2^sh rounded to an integer (halves upward), for |q| <= 2^21, sh <= 37
-// (larger shifts only come from non-finite gradients, and are held there).
+// q * 2^sh rounded to an integer (halves upward), for |q| <= 2^21 and sh <= 37
+// (a block's E is at most 4 above its level's, whose scale holds 8 max|dy| below
+// 2^50: sh <= 51 - (MB - 1)).
 __device__ __forceinline__ long long scale_mantissa(int q, int sh)
 {
-    const int d = min(max(40 - sh, 2), 63);
+    const int d = min(40 - sh, 63);
     return (((long long)q << 40) + (1ll << (d - 1))) >> d;
 }
 
@@ -285,7 +291,13 @@ __global__ __launch_bounds__(kPlaceThreads) void k_scatter_place(ScatterArgs a)
     }
     __syncthreads();
     const float bm = __uint_as_float(s_max);
-    const int E = block_rec_exp(bm), r_max = min((1 << EB) - 1, E - kExpFloor);
+    int E = __builtin_amdgcn_readfirstlane(block_rec_exp(bm));
+    if (E < kTinyExp) {
+        E += kTinyUp;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) val[e] = make_float2(val[e].x * 0x1p96f, val[e].y * 0x1p96f);
+    }
+    const int r_max = min((1 << EB) - 1, E + 100);
     // segment starts: exclusive scan of the histogram in place (by one wave)
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;

@@ -1,0 +1,58 @@
+"""The hash-table gradient far from one: an upstream gradient scaled by a power
+of two scales the table gradient by it, down to feature gradients near the
+smallest normal number, in both record formats and in whole and split tiles."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from parity_util import rel_errors
+from synth.arch import Arch
+from synth.params import init_params
+from synth.workloads import SampleSpec, small_batch
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def case(levels, log2t, rays, S, table="fp32"):
+    """Model, samples and workspace of a uniform-sampling render, and random upstream gradients."""
+    from paper_2503_01582_amd import api
+    arch = Arch(n_levels=levels, log2_table=log2t, width=32, hidden=1, table_dtype=table)
+    rng = np.random.default_rng([levels, log2t, rays, S])
+    b = small_batch(0, res=96)
+    pick = rng.integers(0, b.rays_o.shape[0], rays)
+    dev = lambda a: torch.as_tensor(np.ascontiguousarray(a)).cuda()
+    spec = SampleSpec(n_coarse=0, n_fine=S, include_coarse=False, uniform_only=True)
+    samp = api.prenom_sample(spec, dev(b.rays_o[pick]), dev(b.rays_d[pick]), dev(rng.random((rays, S), dtype=np.float32)),
+                             b.world_to_obj)
+    params = init_params(arch, 3)
+    params[:arch.n_table_params] *= 1e3
+    model = api.Model(arch, params)
+    ws = api.Workspace().get(arch, rays, S)
+    api.prenom_render_fwd(model, samp, None, ws, want_loss=False)
+
+    def table_gradient(d_rgb):
+        model.grads.zero_()
+        api.prenom_render_bwd(model, samp, None, ws, d_rgb=dev(d_rgb))
+        return model.grads.cpu().numpy()[:arch.n_table_params]
+
+    return arch, rng.normal(size=(rays, 3)).astype(np.float32), table_gradient
+
+
+# The MLP's products and the contributions are FP32 down to 2^-149.  With the
+# largest row about 2^-110, the absolute roundings of subnormal numbers (2^-150
+# each, some 2^13 of them in a row) are 2^-27 of it.
+@pytest.mark.parametrize("levels,log2t,rays,S,table", [(8, 14, 511, 9, "fp32"), (8, 11, 4099, 33, "fp32"),
+                                                       (12, 17, 301, 17, "fp16")])
+@pytest.mark.parametrize("target", [-30, -60, -100, -110])
+def test_scaled_gradient(levels, log2t, rays, S, table, target):
+    print(f"test_scaled_gradient: {levels} levels of 2^{log2t}, {rays} rays x {S}, {table}, 2^{target}", flush=True)
+    arch, d_rgb, table_gradient = case(levels, log2t, rays, S, table)
+    ref = table_gradient(d_rgb)
+    shift = target - int(np.floor(np.log2(np.abs(ref).max())))
+    got = table_gradient(np.ldexp(d_rgb, shift))
+    e_max, e_2 = rel_errors(np.ldexp(got.astype(np.float64), -shift), ref)
+    print(f"  shift {shift}: max-rel {e_max:.2e}, 2-rel {e_2:.2e}", flush=True)
+    assert e_max <= 2.0 ** -20 and e_2 <= 2.0 ** -20
