@@ -220,6 +220,10 @@ prenom_status prenom_render_fwd(const prenom_model* model, const prenom_render_c
  * The table gradient is accumulated per 2^13-row tile in 64-bit fixed point,
  * which does not depend on the order of the additions: its bits are the same
  * from run to run.
+ * A feature gradient that is infinite or NaN (from the upstream gradient, or
+ * overflowed on the way) adds nothing to the table gradient, so the rows that
+ * the other samples reach keep their values; with a loss scale it marks the
+ * step, which the optimizer then skips.  The MLP's gradients carry it on.
  * ---------------------------------------------------------------------- */
 prenom_status prenom_render_bwd(const prenom_model* model, const prenom_render_cfg* cfg,
                                 const float* ray_obj, const float* t, const float* dt,

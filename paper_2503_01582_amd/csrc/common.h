@@ -192,7 +192,8 @@ __device__ __forceinline__ bool run_head(const Corners& c, bool has)
 // Per lane that starts a run (boundary set): the sums of v over its run (the
 // lane and the following lanes of its group of 8 up to the next boundary); a
 // segmented suffix scan in three steps, in a fixed order.  Lanes without a
-// contribution pass v = 0 and boundary = true.  Every lane of the wave must call it.
+// contribution pass v = 0 and boundary = true; values and their sums have to be
+// finite (other runs' are multiplied by 0).  Every lane of the wave must call it.
 __device__ __forceinline__ void run_sum(float2 (&v)[8], bool boundary)
 {
     const int g = threadIdx.x & 7;

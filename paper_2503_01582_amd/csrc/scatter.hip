@@ -251,11 +251,15 @@ __global__ __launch_bounds__(kPlaceThreads) void k_scatter_place(ScatterArgs a)
     level_corners<true>(o.grid, l, sample_coord(ts, ro[3], ro[0]), sample_coord(ts, ro[4], ro[1]),
                   sample_coord(ts, ro[5], ro[2]), c);
     if (!in) d = make_float2(0.0f, 0.0f);
+    // A non-finite feature gradient marks the step for the loss scaler, which
+    // then skips the update, and contributes nothing: it would take the other
+    // samples' scale, and their run sums (products with 0) if it lies beside them.
+    const bool fx = isfinite(d.x), fy = isfinite(d.y);
+    if (a.nonfinite && !(fx && fy)) a.nonfinite[0] = 1;
+    d = make_float2(fx ? d.x : 0.0f, fy ? d.y : 0.0f);
     const bool has = d.x != 0.0f || d.y != 0.0f;
-    // a non-finite feature gradient (fmaxf would drop a NaN) marks the step
-    // for the loss scaler, which then skips the update
-    if (a.nonfinite && !(isfinite(d.x) && isfinite(d.y))) a.nonfinite[0] = 1;
-    const bool head = run_head(c, has);
+    // (runs whose sum could overflow stay apart)
+    const bool start = run_head(c, has), head = __ballot(max_abs(d.x, d.y) >= 0x1p124f) ? has : start;
     float2 val[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e)

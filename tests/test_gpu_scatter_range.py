@@ -1,6 +1,8 @@
 """The hash-table gradient far from one: an upstream gradient scaled by a power
-of two scales the table gradient by it, down to feature gradients near the
-smallest normal number, in both record formats and in whole and split tiles."""
+of two scales the table gradient by it, from feature gradients near the smallest
+normal number to ones near the largest, in both record formats and in whole and
+split tiles; and samples whose gradient is not finite leave the others'
+contributions as they are."""
 from __future__ import annotations
 
 import numpy as np
@@ -16,8 +18,10 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-def case(levels, log2t, rays, S, table="fp32"):
-    """Model, samples and workspace of a uniform-sampling render, and random upstream gradients."""
+def case(levels, log2t, rays, S, table="fp32", up=0):
+    """Architecture, random upstream gradients and the table gradient of a
+    uniform-sampling render; the feature gradients are 2^up times larger (the
+    first layer's weights are, and the features as much smaller)."""
     from paper_2503_01582_amd import api
     arch = Arch(n_levels=levels, log2_table=log2t, width=32, hidden=1, table_dtype=table)
     rng = np.random.default_rng([levels, log2t, rays, S])
@@ -28,7 +32,8 @@ def case(levels, log2t, rays, S, table="fp32"):
     samp = api.prenom_sample(spec, dev(b.rays_o[pick]), dev(b.rays_d[pick]), dev(rng.random((rays, S), dtype=np.float32)),
                              b.world_to_obj)
     params = init_params(arch, 3)
-    params[:arch.n_table_params] *= 1e3
+    params[:arch.n_table_params] *= 1e3 * 2.0 ** -up
+    params[arch.n_table_params:arch.n_table_params + arch.width * arch.in_dim] *= 2.0 ** up
     model = api.Model(arch, params)
     ws = api.Workspace().get(arch, rays, S)
     api.prenom_render_fwd(model, samp, None, ws, want_loss=False)
@@ -56,3 +61,32 @@ def test_scaled_gradient(levels, log2t, rays, S, table, target):
     e_max, e_2 = rel_errors(np.ldexp(got.astype(np.float64), -shift), ref)
     print(f"  shift {shift}: max-rel {e_max:.2e}, 2-rel {e_2:.2e}", flush=True)
     assert e_max <= 2.0 ** -20 and e_2 <= 2.0 ** -20
+
+
+# Above 2^124 a wave's runs are not merged, so the records are others: each keeps
+# its larger feature to 2^-22 in nearest rounding, as the merged ones do.
+def test_large_gradient():
+    print("test_large_gradient", flush=True)
+    arch, d_rgb, table_gradient = case(8, 14, 511, 9, up=12)
+    ref = table_gradient(d_rgb)
+    shift = 126 - int(np.floor(np.log2(np.abs(ref).max())))
+    got = table_gradient(np.ldexp(d_rgb, shift))
+    e_max, e_2 = rel_errors(np.ldexp(got.astype(np.float64), -shift), ref)
+    print(f"  shift {shift}: max-rel {e_max:.2e}, 2-rel {e_2:.2e}", flush=True)
+    assert e_max <= 2.0 ** -20 and e_2 <= 2.0 ** -20
+
+
+@pytest.mark.parametrize("levels,log2t,rays,S,table", [(8, 14, 511, 9, "fp32"), (8, 11, 4099, 33, "fp32"),
+                                                       (12, 17, 301, 17, "fp16")])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_non_finite_samples_leave_the_others(levels, log2t, rays, S, table, value):
+    """The bits of the gradient with those rays' upstream gradient zero."""
+    print(f"test_non_finite_samples_leave_the_others: {levels} levels of 2^{log2t}, {rays} rays x {S}, {table}, {value}",
+          flush=True)
+    arch, d_rgb, table_gradient = case(levels, log2t, rays, S, table)
+    bad = np.arange(5, rays, 37)
+    d_rgb[bad] = 0.0
+    ref = table_gradient(d_rgb)
+    d_rgb[bad, bad % 3] = value
+    got = table_gradient(d_rgb)
+    assert np.abs(ref).max() > 0 and np.array_equal(got.view(np.uint32), ref.view(np.uint32))
