@@ -60,9 +60,9 @@ FP32_MFMA_PEAK_TFLOPS = 157.3  # MI355X dense FP32 matrix
 LOWP_MFMA_PEAK_TFLOPS = 2500.0  # MI355X dense BF16 / FP16 matrix
 FP64_VECTOR_PEAK_TFLOPS = 78.6  # MI355X FP64 vector
 METRIC = "training rays/s (fwd+bwd) vs plain FP32 at equal PSNR; % HBM/MFMA roofline"
-# The hash-table gradient is one operation run as four dependent kernels
-# (k_scatter_place, _level, _reduce, _combine); its algorithmic bytes belong to
-# the group, timed as their sum.
+# The hash-table gradient is one operation run as three dependent kernels
+# (k_scatter_place, _reduce, _combine); its algorithmic bytes belong to the
+# group, timed as their sum.
 SCATTER_GROUP = "k_scatter_* (hash-table gradient)"
 
 

@@ -387,7 +387,7 @@ typedef struct prenom_mlp_tiles {
  *   worst-case records (64 bytes per sample and level) fit the budget; an
  *   object above it is a group of its own.  The workspace holds the largest
  *   group's records, so a smaller budget trades a smaller workspace for more
- *   launches (four per group); the gradients do not depend on the grouping. */
+ *   launches (three per group); the gradients do not depend on the grouping. */
 #define PRENOM_RECORD_BUDGET ((int64_t)4 << 30)
 typedef struct prenom_batch {
     int32_t n_objects;

@@ -212,7 +212,7 @@ using namespace prenom::host;
 
 struct WsLayout {
     size_t y, sc, dout, dy, ray_state, loss_partial, mlp_partial, act;
-    size_t seg, block_max, level_exp, parts, recs, total;
+    size_t seg, block_max, part_exp, parts, recs, total;
     int n_loss_blocks, n_mlp_slots;
     ScatterObj plan;
 };
@@ -267,8 +267,8 @@ WsLayout ws_layout(const prenom_arch* a, int64_t n_rays_all, int32_t S, bool rec
     off = align_up(off + (size_t)scatter_segs(w.plan) * sizeof(uint16_t));
     w.block_max = off;
     off = align_up(off + (size_t)scatter_items(w.plan) * sizeof(float));
-    w.level_exp = off;
-    off = align_up(off + (size_t)a->n_levels * sizeof(int32_t));
+    w.part_exp = off;
+    off = align_up(off + (size_t)w.plan.n_parts * sizeof(int32_t));
     w.parts = off;
     off = align_up(off + (size_t)w.plan.n_parts * scatter_part_bytes());
     w.recs = off;
@@ -531,13 +531,12 @@ prenom_status prenom_render_bwd(const prenom_model* model, const prenom_render_c
         sa.n_items = scatter_items(plan);
         sa.n_ritems = plan.n_ritems;
         sa.n_ctiles = plan.n_ctiles;
-        sa.n_levels_total = a->n_levels;
         sa.ray_obj = ro;
         sa.t = tc;
         sa.dy = reinterpret_cast<const float2*>(dy);
         sa.g_table = model->grads;
         sa.block_max = at<float>(workspace, w.block_max);
-        sa.level_exp = at<int32_t>(workspace, w.level_exp);
+        sa.part_exp = at<int32_t>(workspace, w.part_exp);
         sa.seg = at<uint16_t>(workspace, w.seg);
         sa.parts = at<unsigned long long>(workspace, w.parts);
         sa.recs = at<uint64_t>(workspace, w.recs);

@@ -40,12 +40,11 @@ struct Group {
 
 // One pass of the table-gradient scatter: consecutive whole objects
 // [first, first + count), with their scatter geometry re-based so the pass's
-// items, levels, segments, reduce items and partial sums count from 0 (dy and
+// items, segments, reduce items and partial sums count from 0 (dy and
 // the gradient keep the batch's offsets).
 struct ScatterGroup {
     int first = 0, count = 0;
     int64_t n_items = 0, records = 0, n_segs = 0, n_ritems = 0, n_ctiles = 0, n_parts = 0;
-    int32_t n_levels = 0;
 };
 
 struct Plan {
@@ -61,11 +60,11 @@ struct Plan {
     int64_t y_floats = 0, partial_floats = 0, act_floats = 0;
     int64_t fwd_capacity = 0, bwd_capacity = 0;               // work items the lists hold
     int64_t records = 0, pass_items = 0, pass_segs = 0;  // largest of any scatter pass
-    int32_t pass_levels = 0, tiles_max = 1;
+    int32_t tiles_max = 1;
     bool any_f16_table = false, all_f16_table = true;
     // workspace offsets (bytes)
     size_t o_dev, o_sc, o_sc_pass, o_red, o_fwd, o_bwd;
-    size_t y, sc_out, dout, dy, ray_state, ray_loss, partial, act, seg, block_max, level_exp, parts, recs, total;
+    size_t y, sc_out, dout, dy, ray_state, ray_loss, partial, act, seg, block_max, part_exp, parts, recs, total;
     uint64_t fingerprint = 0;
 };
 
@@ -250,13 +249,11 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
             ScatterObj& lo = p.sc_pass[k];
             scatter_split(lo, g.records);
             lo.item_off = g.n_items;
-            lo.lev_off = g.n_levels;
             lo.seg_off = g.n_segs;
             lo.ritem_off = g.n_ritems;
             lo.part_off = g.n_parts;
             lo.ctile_off = g.n_ctiles;
             g.n_items += scatter_items(lo);
-            g.n_levels += lo.grid.n_levels;
             g.n_segs += scatter_segs(lo);
             g.n_ritems += lo.n_ritems;
             g.n_parts += lo.n_parts;
@@ -265,7 +262,6 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
         p.records = g.records > p.records ? g.records : p.records;
         p.pass_items = g.n_items > p.pass_items ? g.n_items : p.pass_items;
         p.pass_segs = g.n_segs > p.pass_segs ? g.n_segs : p.pass_segs;
-        p.pass_levels = g.n_levels > p.pass_levels ? g.n_levels : p.pass_levels;
         p.sgroups.push_back(g);
     }
 
@@ -367,7 +363,7 @@ prenom_status build_plan(const prenom_batch* b, int32_t S, Plan& p)
     p.act = take(sizeof(float) * (size_t)p.act_floats);
     p.seg = take(sizeof(uint16_t) * (size_t)p.pass_segs);
     p.block_max = take(sizeof(float) * (size_t)p.pass_items);
-    p.level_exp = take(sizeof(int32_t) * (size_t)p.pass_levels);
+    p.part_exp = take(sizeof(int32_t) * (size_t)scatter_parts_most(p.records));
     p.parts = take(scatter_part_bytes() * (size_t)scatter_parts_most(p.records));
     p.recs = take(sizeof(uint64_t) * (size_t)p.records);
     p.total = off;
@@ -414,13 +410,12 @@ ScatterArgs scatter_args(const Plan& p, const ScatterGroup& g, void* ws, const f
     sa.n_items = g.n_items;
     sa.n_ritems = g.n_ritems;
     sa.n_ctiles = g.n_ctiles;
-    sa.n_levels_total = g.n_levels;
     sa.ray_obj = ray_obj;
     sa.t = t;
     sa.dy = at<const float2>(ws, p.dy);
     sa.g_table = grads;
     sa.block_max = at<float>(ws, p.block_max);
-    sa.level_exp = at<int32_t>(ws, p.level_exp);
+    sa.part_exp = at<int32_t>(ws, p.part_exp);
     sa.seg = at<uint16_t>(ws, p.seg);
     sa.parts = at<unsigned long long>(ws, p.parts);
     sa.recs = at<uint64_t>(ws, p.recs);

@@ -308,7 +308,6 @@ struct ScatterObj {
     GridInfo grid;
     int32_t n_blocks;  // sample blocks per level
     int32_t n_tiles;   // table tiles over the object's levels
-    int32_t lev_off;   // first (object, level) entry of level_exp
     int32_t n_ritems;  // reduce items
     int32_t n_ctiles;  // tiles reduced in several ranges of blocks
     int32_t n_parts;   // 64-bit partial sums of those (one per range)
@@ -353,8 +352,6 @@ struct ScatterArgs {
     float inv_S;                // 1 / S
     int32_t n_obj;              // 1: `one` holds the object; else `objs` (device) holds n_obj of them
     int32_t tiles_max;          // max tiles of one level over all objects
-    int32_t n_levels_total;     // (object, level) pairs
-    int32_t pad_;
     int64_t n_items;            // (object, level, sample block) items
     int64_t n_ritems;           // reduce items
     int64_t n_ctiles;           // tiles reduced in several ranges
@@ -365,9 +362,9 @@ struct ScatterArgs {
     const float2* dy;
     float* g_table;
     float* block_max;           // [n_items] max |dy| of the item
-    int32_t* level_exp;         // [n_levels_total] fixed-point exponent
     uint16_t* seg;              // per item [tiles + 1]: start of each tile's segment, and the end
-    unsigned long long* parts;  // partial sums: 64-bit fixed point, [2][tile rows] each
+    unsigned long long* parts;  // partial sums: 64-bit fixed point, [2][tile rows] each, and
+    int32_t* part_exp;          // their exponents
     uint64_t* recs;             // packed records (scatter.hip), 4096 per item
     int64_t n_records;          // length of recs
     int32_t* nonfinite;         // set to 1 when a dy entry is not finite (loss scaling), or null
@@ -376,8 +373,8 @@ struct ScatterArgs {
     int32_t compact;
 };
 // The scatter runs as kScatterPhases dependent kernels, launched in order:
-// place, level scales, reduce, combine (none where no tile is split).
-constexpr int kScatterPhases = 4;
+// place, reduce, combine (none where no tile is split).
+constexpr int kScatterPhases = 3;
 extern const char* const kScatterPhaseNames[kScatterPhases];
 hipError_t launch_scatter_phase(const ScatterArgs& a, int phase, hipStream_t s);
 

@@ -14,21 +14,23 @@
 //            largest |dy|.  Nothing has to be known about the other blocks, so
 //            no counting pass and no scan over blocks precede it, and the
 //            write is one linear copy out of LDS
-//   level  : per (object, level) the largest |dy| and the sum of the block
-//            maxima, which fix the level's fixed-point scale 2^e
 //   reduce : one workgroup per (tile, range of blocks) gathers the tile's
 //            segments of those blocks, 16 lanes per segment, and accumulates
 //            them in LDS; a tile with one range is added to the gradient rows
 //            (the workgroup owns them), the others write their 64-bit sums
-//   combine: the 64-bit sums of a tile's ranges added and applied
+//            and the scale of these
+//   combine: the sums of a tile's ranges added, in their order, and applied
 //
 // The LDS accumulation is 64-bit fixed point (integer LDS atomics run several
-// times faster than FP32 ones).  The trilinear weights of a sample sum to 1,
-// so |sum| of a row <= sum over the blocks of 512 max|dy|; with e chosen so
-// that this bound times 2^e < 2^62 no sum can overflow, and with one record's
-// value times 2^e < 2^50 as well, each contribution is rounded by at most
-// 2^-(e+1), far below FP32 resolution of the result.  Integer sums do not
-// depend on order, so the gradient is bit-reproducible.
+// times faster than FP32 ones), at a scale 2^e of the workgroup's own.  A row
+// gets at most 512 max|dy| from a block, as the trilinear weights of a sample
+// sum to 1, and at most 8 max|dy| from a record; with e chosen so that the
+// smaller of the two, summed over the blocks, times 2^e < 2^62 no sum can
+// overflow, and with one record's value times 2^e < 2^50 as well, each
+// contribution is rounded by at most 2^-(e+1), far below FP32 resolution of the
+// tile's larger rows however few of the level's records it holds.  Integer sums
+// do not depend on order and the ranges' are added in one order, so the gradient
+// is bit-reproducible.
 //
 // A record keeps 21 significant bits of the larger of its two features (an
 // FP32 value has 24): each feature is within 2^-21 of the larger one's
@@ -57,7 +59,6 @@ constexpr int kSegGroups = kReduceThreads / kSegLanes;  // segments in flight pe
 // segments of a 2^19-row level (4096 / 64 = 64 records on average) take one.
 constexpr int kSegStep = 5;
 constexpr int kHeads = 2048;  // blocks whose segment bounds a workgroup holds in LDS
-constexpr int kLevelThreads = 1024;
 constexpr int kCombineThreads = 256;
 // Reduce items of a pass (scatter_split): about kReduceItems of even size, so
 // that the CUs stay busy to the end whatever the tables' sizes, but none
@@ -150,8 +151,8 @@ __device__ __forceinline__ void decode_record(uint32_t lo, uint32_t hi, uint32_t
 }
 
 // q * 2^sh rounded to an integer (halves upward), for |q| <= 2^21 and sh <= 37
-// (a block's E is at most 4 above its level's, whose scale holds 8 max|dy| below
-// 2^50: sh <= 51 - (MB - 1)).
+// (8 max|dy| times the scale is below 2^50, and a block's E at most 4 above the
+// exponent of the largest: sh <= 51 - (MB - 1)).
 __device__ __forceinline__ long long scale_mantissa(int q, int sh)
 {
     const int d = min(40 - sh, 63);
@@ -358,65 +359,30 @@ __global__ __launch_bounds__(kPlaceThreads) void k_scatter_place(ScatterArgs a)
     }
 }
 
-// Fixed-point exponent of each (object, level): the largest e with
-//   sum over the blocks of 512 max|dy| * 2^e < 2^62  (bound on any row's sum)
-//   8 max|dy| * 2^e < 2^50                            (bound on one record)
-// One workgroup per pair; a pass has few of them, so each takes 16 waves.  The
-// sum of the maxima is taken in FP64 in a fixed order.
-template <bool kMany>
-__global__ __launch_bounds__(kLevelThreads) void k_scatter_level(ScatterArgs a)
+// Largest e with bound * 2^e < 2^62 (on any row's sum) and 8 m * 2^e < 2^50 (on
+// any record).
+__device__ __forceinline__ int fixed_point_exp(double bound, float m)
 {
-    __shared__ float red[kLevelThreads / 64];
-    __shared__ double sum[kLevelThreads / 64];
-    const int pair = blockIdx.x;
-    const ScatterObj& o = sobj<kMany>(a, last_le<kMany>(a, pair, [](const ScatterObj& v) { return (int64_t)v.lev_off; }));
-    const int l = pair - o.lev_off;
-    const float* bm = a.block_max + o.item_off + (int64_t)l * o.n_blocks;
-    float m = 0.0f;
-    double t = 0.0;
-    for (int b = threadIdx.x; b < o.n_blocks; b += kLevelThreads) {
-        m = fmaxf(m, bm[b]);
-        t += (double)bm[b];
-    }
-#pragma unroll
-    for (int dd = 32; dd >= 1; dd >>= 1) {
-        m = fmaxf(m, __shfl_xor(m, dd));
-        t += __shfl_xor(t, dd);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        red[threadIdx.x >> 6] = m;
-        sum[threadIdx.x >> 6] = t;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float r = 0.0f;
-        double b = 0.0;
-        for (int w = 0; w < kLevelThreads / 64; ++w) {
-            r = fmaxf(r, red[w]);
-            b += sum[w];
-        }
-        int e = 0;
-        b *= (double)kSamplesPerBlock;
-        if (b > 0.0 && isfinite(b)) {
-            int ex, evx;
-            frexp(b, &ex);    // bound < 2^ex
-            frexpf(r, &evx);  // max|dy| < 2^evx
-            e = min(62 - ex, 47 - evx);
-        }
-        a.level_exp[pair] = e;
-    }
+    if (!(bound > 0.0)) return 0;
+    int ex = 0, evx = 0;
+    frexp(bound, &ex);   // bound < 2^ex
+    frexpf(m, &evx);     // m < 2^evx
+    return min(62 - ex, 47 - evx);
 }
 
 // One workgroup per reduce item: blocks [b0, b1) of one tile.  Its segments
 // are read 16 lanes each (128 contiguous bytes a load), the next step's records
 // requested before the current one's are added.  Bound by the LDS atomics
-// (two 64-bit adds per record).
+// (two 64-bit adds per record).  The bounds of the first kHeads segments stay in
+// LDS from the pass that finds the scale; longer ranges read theirs twice.
 template <bool kMany, bool kCompact>
 __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a)
 {
     constexpr int EB = kCompact ? kRecExpBitsC : kRecExpBits, MB = kCompact ? kRecMantBitsC : kRecMantBits;
     __shared__ unsigned long long acc[2 * kTileRows];  // fixed point: feature 0 rows, then feature 1 rows
     __shared__ uint2 head[kHeads];  // segments of kHeads blocks: start and end, max |dy| of the block
+    __shared__ double w_bound[kReduceThreads / 64];
+    __shared__ float w_max[kReduceThreads / 64];
     const int64_t ritem = blockIdx.x;
     const ScatterObj& o = sobj<kMany>(a, last_le<kMany>(a, ritem, [](const ScatterObj& v) { return v.ritem_off; }));
     const int rl = (int)(ritem - o.ritem_off);
@@ -429,7 +395,6 @@ __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a
     const int b0 = min(part * per, nb), b1 = min(b0 + per, nb);
     const int64_t row0 = (int64_t)tt << kTileBits;
     const int n_rows = (int)min((int64_t)kTileRows, o.level_rows[l] - row0);
-    const int ex = a.level_exp[o.lev_off + l];
     for (int i = threadIdx.x; i < n_rows; i += kReduceThreads) {
         acc[i] = 0ull;
         acc[kTileRows + i] = 0ull;
@@ -438,13 +403,42 @@ __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a
     const int nt1 = o.tiles[l] + 1;
     const uint16_t* seg = a.seg + seg_index(o, l, 0) + tt;
     const int64_t item0 = o.item_off + (int64_t)l * nb;
+    auto segment = [&](int b) {
+        const uint16_t* p = seg + (int64_t)b * nt1;
+        return make_uint2((uint32_t)p[0] | (uint32_t)p[1] << 16, __float_as_uint(a.block_max[item0 + b]));
+    };
+    double bound = 0.0;  // of the rows' sums, and
+    float m = 0.0f;      // the largest |dy| of the blocks that reach the tile
+    for (int i = threadIdx.x; i < b1 - b0; i += kReduceThreads) {
+        const uint2 h = segment(b0 + i);
+        if (i < kHeads) head[i] = h;
+        const uint32_t n = (h.x >> 16) - (h.x & 0xffffu);
+        const float bm = n ? __uint_as_float(h.y) : 0.0f;
+        bound += (double)min(8u * n, (uint32_t)kSamplesPerBlock) * (double)bm;
+        m = fmaxf(m, bm);
+    }
+#pragma unroll
+    for (int dd = 32; dd >= 1; dd >>= 1) {
+        bound += __shfl_xor(bound, dd);
+        m = fmaxf(m, __shfl_xor(m, dd));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        w_bound[threadIdx.x >> 6] = bound;
+        w_max[threadIdx.x >> 6] = m;
+    }
+    __syncthreads();  // (also orders the cleared accumulators before the additions)
+    bound = 0.0;
+    for (int w = 0; w < kReduceThreads / 64; ++w) {
+        bound += w_bound[w];
+        m = fmaxf(m, w_max[w]);
+    }
+    const int ex = __builtin_amdgcn_readfirstlane(fixed_point_exp(bound, m));
     for (int c0 = b0; c0 < b1; c0 += kHeads) {
         const int n = min(kHeads, b1 - c0);
-        for (int i = threadIdx.x; i < n; i += kReduceThreads) {
-            const uint16_t* p = seg + (int64_t)(c0 + i) * nt1;
-            head[i] = make_uint2((uint32_t)p[0] | (uint32_t)p[1] << 16, __float_as_uint(a.block_max[item0 + c0 + i]));
+        if (c0 != b0) {
+            for (int i = threadIdx.x; i < n; i += kReduceThreads) head[i] = segment(c0 + i);
+            __syncthreads();
         }
-        __syncthreads();  // (also orders the cleared accumulators before the additions)
         // Steps of up to kSegStep * kSegLanes records of one segment: the lane's
         // records are u * kSegLanes < left.  Loads are unconditional, of clamped
         // addresses, and looked at two steps later, so that none waits for
@@ -518,8 +512,9 @@ __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a
     }
     __syncthreads();
     if (n_split > 1) {
-        unsigned long long* out =
-            a.parts + (o.part_off + o.part_base[l] + (int64_t)tt * n_split + part) * (2 * kTileRows);
+        const int64_t slot = o.part_off + o.part_base[l] + (int64_t)tt * n_split + part;
+        unsigned long long* out = a.parts + slot * (2 * kTileRows);
+        if (threadIdx.x == 0) a.part_exp[slot] = ex;
         for (int i = threadIdx.x; i < n_rows; i += kReduceThreads) {
             out[i] = acc[i];
             out[kTileRows + i] = acc[kTileRows + i];
@@ -537,8 +532,8 @@ __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a
     }
 }
 
-// Tiles reduced in several ranges: the ranges' 64-bit sums added, one thread
-// per row; blockIdx.y counts the pass's split tiles.
+// Tiles reduced in several ranges: the ranges' sums added in FP64, one thread per
+// row; blockIdx.y counts the pass's split tiles.
 template <bool kMany>
 __global__ __launch_bounds__(kCombineThreads) void k_scatter_combine(ScatterArgs a)
 {
@@ -551,19 +546,20 @@ __global__ __launch_bounds__(kCombineThreads) void k_scatter_combine(ScatterArgs
     const int64_t row0 = (int64_t)tt << kTileBits;
     const int i = (int)(blockIdx.x * kCombineThreads + threadIdx.x);
     if (i >= (int)min((int64_t)kTileRows, o.level_rows[l] - row0)) return;
-    const unsigned long long* in = a.parts + (o.part_off + o.part_base[l] + (int64_t)tt * n_split) * (2 * kTileRows) + i;
-    unsigned long long sx = 0, sy = 0;
+    const int64_t slot = o.part_off + o.part_base[l] + (int64_t)tt * n_split;
+    const unsigned long long* in = a.parts + slot * (2 * kTileRows) + i;
+    double sx = 0.0, sy = 0.0;
 #pragma unroll 4
     for (int k = 0; k < n_split; ++k) {
-        sx += in[(int64_t)k * 2 * kTileRows];
-        sy += in[(int64_t)k * 2 * kTileRows + kTileRows];
+        const double scale = ldexp(1.0, -a.part_exp[slot + k]);
+        sx = fma((double)(long long)in[(int64_t)k * 2 * kTileRows], scale, sx);
+        sy = fma((double)(long long)in[(int64_t)k * 2 * kTileRows + kTileRows], scale, sy);
     }
-    if (sx == 0 && sy == 0) return;
-    const int ex = a.level_exp[o.lev_off + l];
+    if (sx == 0.0 && sy == 0.0) return;
     float2* g = reinterpret_cast<float2*>(a.g_table + o.g_off) + ((int64_t)l << o.grid.log2_table) + row0;
     float2 w = g[i];
-    w.x += (float)ldexp((double)(long long)sx, -ex);
-    w.y += (float)ldexp((double)(long long)sy, -ex);
+    w.x += (float)sx;
+    w.y += (float)sy;
     g[i] = w;
 }
 
@@ -582,9 +578,6 @@ hipError_t scatter_phase_impl(const ScatterArgs& a, int phase, hipStream_t s)
     switch (phase) {
         case 0: return a.compact ? place_impl<kMany, true>(a, s) : place_impl<kMany, false>(a, s);
         case 1:
-            hipLaunchKernelGGL(k_scatter_level<kMany>, dim3((uint32_t)a.n_levels_total), dim3(kLevelThreads), 0, s, a);
-            break;
-        case 2:
             if (a.compact)
                 hipLaunchKernelGGL((k_scatter_reduce<kMany, true>), dim3((uint32_t)a.n_ritems), dim3(kReduceThreads), 0,
                                    s, a);
@@ -592,7 +585,7 @@ hipError_t scatter_phase_impl(const ScatterArgs& a, int phase, hipStream_t s)
                 hipLaunchKernelGGL((k_scatter_reduce<kMany, false>), dim3((uint32_t)a.n_ritems), dim3(kReduceThreads), 0,
                                    s, a);
             break;
-        case 3:
+        case 2:
             hipLaunchKernelGGL(k_scatter_combine<kMany>, dim3(kTileRows / kCombineThreads, (uint32_t)a.n_ctiles),
                                dim3(kCombineThreads), 0, s, a);
             break;
@@ -678,12 +671,11 @@ int scatter_tiles_max(const ScatterObj& o)
     return m;
 }
 
-const char* const kScatterPhaseNames[kScatterPhases] = {"k_scatter_place", "k_scatter_level", "k_scatter_reduce",
-                                                        "k_scatter_combine"};
+const char* const kScatterPhaseNames[kScatterPhases] = {"k_scatter_place", "k_scatter_reduce", "k_scatter_combine"};
 
 hipError_t launch_scatter_phase(const ScatterArgs& a, int phase, hipStream_t s)
 {
-    if (a.n_items == 0 || (phase == 3 && a.n_ctiles == 0)) return hipSuccess;
+    if (a.n_items == 0 || (phase == 2 && a.n_ctiles == 0)) return hipSuccess;
     return a.n_obj == 1 && a.objs == nullptr ? scatter_phase_impl<false>(a, phase, s)
                                              : scatter_phase_impl<true>(a, phase, s);
 }

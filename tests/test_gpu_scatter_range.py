@@ -90,3 +90,49 @@ def test_non_finite_samples_leave_the_others(levels, log2t, rays, S, table, valu
     d_rgb[bad, bad % 3] = value
     got = table_gradient(d_rgb)
     assert np.abs(ref).max() > 0 and np.array_equal(got.view(np.uint32), ref.view(np.uint32))
+
+
+# 2^22 samples over levels of 2^24 rows, a tenth of the rays 2^-20 of the others.
+# With M the largest feature gradient, a tile of a hashed level gets at most two
+# records of a block on average, so its sums stay below 2 * 8 M * 8192 = 2^17 M and
+# its scale is at least 2^44 / M (coarser ones, of the level's 2^22 M, 2^39 / M): a
+# record is rounded with an RMS error of 2^-45 M / sqrt(3), and a row that only the
+# small rays reach holds a few.  M is taken as the large rays' largest row of the
+# finest level, whose rows hold a few samples as well.
+def test_small_rows_of_large_tables():
+    from paper_2503_01582_amd import api
+    print("test_small_rows_of_large_tables", flush=True)
+    rays, S = 65536, 64
+    arch = Arch(n_levels=8, log2_table=24, width=32, hidden=1, resolutions=(16, 32, 64, 128, 256, 512, 1024, 2048))
+    gen = torch.Generator("cuda").manual_seed(3)
+    rand = lambda *shape: torch.rand(shape, device="cuda", generator=gen)
+    o = torch.randn((rays, 3), device="cuda", generator=gen)
+    o = 1.5 * o / o.norm(dim=1, keepdim=True)
+    d = rand(rays, 3) * 0.9 - 0.45 - o
+    d = d / d.norm(dim=1, keepdim=True)
+    spec = SampleSpec(n_coarse=0, n_fine=S, include_coarse=False, uniform_only=True)
+    samp = api.prenom_sample(spec, o, d, rand(rays, S), small_batch(0).world_to_obj)
+    params = init_params(Arch(n_levels=8, log2_table=10, width=32, hidden=1), 3)[-arch.n_mlp_params:]
+    model = api.Model(arch, np.zeros(arch.n_params, np.float32))
+    model.params[arch.n_table_params:] = torch.as_tensor(params).cuda()
+    model.params[:arch.n_table_params] = rand(arch.n_table_params) * 0.2 - 0.1
+    ws = api.Workspace().get(arch, rays, S)
+    api.prenom_render_fwd(model, samp, None, ws, want_loss=False)
+    d_rgb = torch.randn((rays, 3), device="cuda", generator=gen)
+    small = (rand(rays) < 0.1)[:, None]
+
+    def table_gradient(up):
+        model.grads.zero_()
+        api.prenom_render_bwd(model, samp, None, ws, d_rgb=up.contiguous())
+        return model.grads[:arch.n_table_params].clone()
+
+    zero = torch.zeros_like(d_rgb)
+    large = table_gradient(torch.where(small, zero, d_rgb))
+    ref = table_gradient(torch.where(small, d_rgb * 2.0 ** -20, zero))
+    got = table_gradient(torch.where(small, d_rgb * 2.0 ** -20, d_rgb))
+    rows = (large == 0) & (ref != 0)
+    M = float(large[-2 << arch.log2_table:].abs().max())
+    rms = float((got[rows].double() - ref[rows].double()).square().mean().sqrt())
+    print(f"  {int(rows.sum())} rows, rms 2^{np.log2(rms / M):.1f} M, rows' own rms "
+          f"2^{np.log2(float(ref[rows].double().square().mean().sqrt()) / M):.1f} M", flush=True)
+    assert int(rows.sum()) > 100000 and rms <= 2.0 ** -43 * M
