@@ -252,6 +252,19 @@ __device__ __forceinline__ int find_object(const ObjDev* objs, int n_obj, int64_
     return lo;
 }
 
+// ------------------------------------------------------------------ XCD order
+// Item of a block of a launch whose items should stay on one XCD in runs: blocks go to
+// the 8 XCDs in turn, and each XCD's L2 fetches what its blocks read.
+constexpr uint32_t kXcds = 8;
+
+__host__ __device__ __forceinline__ uint32_t xcd_item(uint32_t block, int run_log2)
+{
+    const uint32_t slot = block / kXcds, xcd = block % kXcds;
+    return ((slot >> run_log2) * kXcds + xcd) << run_log2 | (slot & ((1u << run_log2) - 1u));
+}
+
+int xcd_run_log2(int64_t n_items);
+
 // ------------------------------------------------------------------ launches
 // Every launcher returns hipSuccess or the launch error.
 

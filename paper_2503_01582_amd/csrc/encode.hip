@@ -369,19 +369,6 @@ __global__ __launch_bounds__(kLdsThreads) void k_encode_batch_lds(const ObjDev* 
         encode(reinterpret_cast<const float2*>(params + o.param_off) + row0);
 }
 
-// Item of a block of the launch below.  Blocks go to the 8 XCDs in turn, and each
-// XCD's L2 fetches the levels that its blocks read; with runs of 2^kXcdRunLog2
-// items an XCD a level of a small object is read by one or two of them instead
-// of all.  16 small objects 259 -> 238 us, 8 tasks of 4096 rays 224 -> 211; no
-// change where a level has many runs (48 objects 7.88 -> 7.80 ms).
-constexpr int kXcdRunLog2 = 8;
-
-__device__ __forceinline__ uint32_t xcd_item(uint32_t block)
-{
-    const uint32_t slot = block >> 3, xcd = block & 7u;
-    return ((slot >> kXcdRunLog2) * 8u + xcd) << kXcdRunLog2 | (slot & ((1u << kXcdRunLog2) - 1u));
-}
-
 // Batched, the other objects: one block per item (object, level, block of
 // kScatterBlockSamples samples); sobjs[i] and objs[i] describe object i.
 __global__ __launch_bounds__(kScatterBlockSamples) void k_encode_batch(const ObjDev* __restrict__ objs,
@@ -390,10 +377,10 @@ __global__ __launch_bounds__(kScatterBlockSamples) void k_encode_batch(const Obj
                                                                    const half2_t* __restrict__ params_f16,
                                                                    const float* __restrict__ ray_obj,
                                                                    const float* __restrict__ t, int32_t S,
-                                                                   uint32_t n_items,
+                                                                   uint32_t n_items, int run_log2,
                                                                    float2* __restrict__ y)
 {
-    const int64_t item = xcd_item(blockIdx.x);
+    const int64_t item = xcd_item(blockIdx.x, run_log2);
     if (item >= n_items) return;
     const int lo = item_object(sobjs, n_obj, &ScatterObj::item_off, item);
     const ScatterObj& so = sobjs[lo];
@@ -552,6 +539,20 @@ hipError_t launch_density_grid(const float* sc, int64_t n, float* out, hipStream
     return hipGetLastError();
 }
 
+// With runs of a fixed length a launch of fewer items than 8 of them leaves XCDs
+// without work; runs of at most a 32nd of the items give none of them more than a
+// quarter above its share, and 256 items are as long as helps.  Measured on gfx950
+// (us; runs of one, of an 8th, a 32nd and a 64th of the items, of 256): 512 items,
+// 2^17 rows 14.4 / 10.1 / 11.3 / 13.1 / 24.0, 2^14 rows 9.0 / 9.2 / 9.2 / 9.0 / 19.7;
+// 2304 items 47.0 / 42.4 / 35.0 / 32.6 / 42.5; 3760 76.6 / 48.7 / 49.4 / 52.2 / 48.7;
+// 8192 126.5 / 108.1 / 107.8 / 101.9 / 107.8; 16384 and more within 2%.
+int xcd_run_log2(int64_t n_items)
+{
+    int r = 0;
+    while (r < 8 && ((int64_t)64 << r) <= n_items) ++r;
+    return r;
+}
+
 void encode_split(const ObjDev* objs, ScatterObj* sobjs, int n_obj, int64_t& n_items, int64_t& n_lds)
 {
     auto planes = [&](int i) {
@@ -598,9 +599,10 @@ hipError_t launch_encode_batch(const ObjDev* objs, const ScatterObj* sobjs, int 
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (n_items == 0) return hipSuccess;
-    const dim3 grid((uint32_t)round_up(n_items, (int64_t)8 << kXcdRunLog2));
+    const int run_log2 = xcd_run_log2(n_items);
+    const dim3 grid((uint32_t)round_up(n_items, (int64_t)kXcds << run_log2));
     hipLaunchKernelGGL(k_encode_batch, grid, dim3(kScatterBlockSamples), 0, s, objs, sobjs, n_obj, params,
-                       (const half2_t*)params_f16, ray_obj, t, S, (uint32_t)n_items, (float2*)y);
+                       (const half2_t*)params_f16, ray_obj, t, S, (uint32_t)n_items, run_log2, (float2*)y);
     return hipGetLastError();
 }
 
