@@ -7,8 +7,12 @@ more blocks for small objects.  For each MLP shape (input features, width,
 hidden layers, element type) this module times the batched forward and
 backward MLP kernels over candidate run lengths on a synthetic one-object
 batch, with the library's per-kernel event timing, and keeps the fastest of
-each.  Results are cached in a JSON file keyed by GPU architecture, HIP
-runtime version, library version and shape.
+each.  A forward or 16-bit backward launch takes a shorter run than asked for
+where the asked one leaves CUs idle, so only lengths are tried that cut the
+object into whole rounds of blocks, which run as they are; an FP32 backward
+always takes the asked one, so its lengths are tried on a smaller object, which
+the longest of them leave too few blocks of.  Results are cached in a JSON file keyed by GPU
+architecture, HIP runtime version, library version and shape.
 
     python -m paper_2503_01582_amd.autotune [--out FILE] [--rays N]
 """
@@ -23,6 +27,12 @@ import numpy as np
 
 FWD_CANDIDATES = (16, 32, 64, 128, 256, 512)
 BWD_CANDIDATES = (32, 64, 128, 256, 512, 1024)
+# 16-sample tiles of a run of length c come in whole rounds of blocks if the object
+# has a multiple of ROUND * c tiles: no launch holds more blocks at a time.
+ROUND = 512
+N_RAYS = 131072  # x SAMPLES = 512 * 1024 tiles: every candidate
+N_RAYS_FIXED = 16384
+SAMPLES = 64
 PACKAGED = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tiles_gfx950.json")
 
 
@@ -62,16 +72,16 @@ def _rays(n: int, seed: int):
     return o.astype(np.float32), d.astype(np.float32)
 
 
-def time_shape(arch, fwd_tiles: int, bwd_tiles: int, n_rays: int = 16384, reps: int = 4) -> Dict[str, float]:
+def time_shape(arch, fwd_tiles: int, bwd_tiles: int, n_rays: int = N_RAYS, reps: int = 4) -> Dict[str, float]:
     """Average ms of the batched MLP forward and backward launches of one
-    object of `arch` with n_rays x 64 samples at the given tile shape."""
+    object of `arch` with n_rays x SAMPLES samples at the given tile shape."""
     import torch
     from synth.params import init_params
     from synth.workloads import LossSpec, SampleSpec, nocs_affine
     from . import api
     from . import batch as B
 
-    spec = SampleSpec(n_coarse=16, n_fine=48, include_coarse=True, uniform_only=True)
+    spec = SampleSpec(n_coarse=16, n_fine=SAMPLES - 16, include_coarse=True, uniform_only=True)
     obj = B.BatchObject(arch, n_rays, None, nocs_affine())
     tiles = [dict(in_dim=arch.in_dim, width=arch.width, hidden=arch.hidden, dtype=arch.mlp_dtype,
                   fwd_tiles=fwd_tiles, bwd_tiles=bwd_tiles)]
@@ -95,8 +105,19 @@ def time_shape(arch, fwd_tiles: int, bwd_tiles: int, n_rays: int = 16384, reps: 
     return {k: kt[k][1] / kt[k][0] for k in ("k_mlp_fwd", "k_mlp_bwd") if k in kt}
 
 
-def tune(arches: Iterable, n_rays: int = 16384, out: Optional[str] = None, log=print) -> List[dict]:
+def candidates(n_rays: int, lengths: Iterable[int]) -> List[int]:
+    """The lengths that launches over n_rays x SAMPLES samples run as asked for."""
+    tiles = n_rays * SAMPLES // 16
+    fit = [c for c in lengths if n_rays * SAMPLES % 16 == 0 and tiles % (ROUND * c) == 0]
+    if not fit:
+        raise ValueError(f"no run length can be timed on {n_rays} rays (a multiple of "
+                         f"{ROUND * 16 * min(lengths) // SAMPLES} is needed)")
+    return fit
+
+
+def tune(arches: Iterable, n_rays: int = N_RAYS, out: Optional[str] = None, log=print) -> List[dict]:
     """Tunes every distinct MLP shape of `arches`; merges into the cache."""
+    fwd, bwd = candidates(n_rays, FWD_CANDIDATES), candidates(n_rays, BWD_CANDIDATES)
     path = out or cache_path()
     cache = _load(path)
     dk = device_key()
@@ -107,17 +128,25 @@ def tune(arches: Iterable, n_rays: int = 16384, out: Optional[str] = None, log=p
         if key in seen:
             continue
         seen.add(key)
-        best_f = best_b = None
-        for f, b in zip(FWD_CANDIDATES, BWD_CANDIDATES):
+        fixed = a.mlp_dtype == "fp32"
+        best = {}
+
+        def timed(kernel, length, t, rays):
+            us = t[kernel] * 1e3
+            log(f"  {key}: {kernel} {length:5d} tiles {us:8.1f} us")
+            if kernel not in best or us < best[kernel][1]:
+                best[kernel] = (length, us, rays)
+
+        for i in range(max(len(fwd), len(bwd))):
+            f, b = fwd[min(i, len(fwd) - 1)], bwd[min(i, len(bwd) - 1)]
             t = time_shape(a, f, b, n_rays)
-            log(f"  {key}: fwd {f:4d} tiles {t['k_mlp_fwd'] * 1e3:8.1f} us, bwd {b:5d} tiles "
-                f"{t['k_mlp_bwd'] * 1e3:8.1f} us")
-            if best_f is None or t["k_mlp_fwd"] < best_f[1]:
-                best_f = (f, t["k_mlp_fwd"])
-            if best_b is None or t["k_mlp_bwd"] < best_b[1]:
-                best_b = (b, t["k_mlp_bwd"])
-        table[key] = dict(fwd_tiles=best_f[0], bwd_tiles=best_b[0], fwd_us=best_f[1] * 1e3,
-                          bwd_us=best_b[1] * 1e3, n_rays=n_rays)
+            timed("k_mlp_fwd", f, t, n_rays)
+            if not fixed:
+                timed("k_mlp_bwd", b, t, n_rays)
+        for b in BWD_CANDIDATES if fixed else ():
+            timed("k_mlp_bwd", b, time_shape(a, fwd[0], b, N_RAYS_FIXED), N_RAYS_FIXED)
+        table[key] = dict(fwd_tiles=best["k_mlp_fwd"][0], bwd_tiles=best["k_mlp_bwd"][0], fwd_us=best["k_mlp_fwd"][1],
+                          bwd_us=best["k_mlp_bwd"][1], n_rays=n_rays, n_rays_bwd=best["k_mlp_bwd"][2])
     os.makedirs(os.path.dirname(os.path.abspath(path)), exist_ok=True)
     with open(path, "w") as f:
         json.dump(cache, f, indent=1, sort_keys=True)
@@ -153,7 +182,7 @@ def all_shapes(dtypes=("fp32",)):
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--out", default=None)
-    ap.add_argument("--rays", type=int, default=16384)
+    ap.add_argument("--rays", type=int, default=N_RAYS)
     ap.add_argument("--dtypes", default="fp32,bf16,fp16")
     args = ap.parse_args()
     tune(all_shapes(tuple(args.dtypes.split(","))), args.rays, args.out)

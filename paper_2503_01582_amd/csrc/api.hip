@@ -753,6 +753,6 @@ const char* prenom_status_string(prenom_status s)
 
 const char* prenom_last_error(void) { return g_last_error; }
 
-const char* prenom_version(void) { return "prenom-mi355x 0.1 (gfx950)"; }
+const char* prenom_version(void) { return "prenom-mi355x 0.2 (gfx950)"; }
 
 }  // extern "C"

@@ -10,14 +10,16 @@ import subprocess
 import pytest
 
 
-def run_plan_program(tmp_path, body: str) -> str:
-    """Output of a C++ main() whose body is `body`, compiled for the host only."""
+def run_plan_program(tmp_path, body: str, headers=()) -> str:
+    """Output of a C++ main() whose body is `body`, compiled for the host only,
+    after the internal headers named."""
     from paper_2503_01582_amd import _lib
     from paper_2503_01582_amd.build import CSRC, HIPCC, ROOT
     if shutil.which(HIPCC) is None:
         pytest.skip("hipcc not available")
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
     src.write_text('#include <cstdio>\n#include <cstdlib>\n#include <vector>\n#include "common.h"\n'
+                   + "".join(f'#include "{h}"\n' for h in headers) +
                    "using namespace prenom;\n"
                    "#define CHECK(c, ...) do { if (!(c)) { printf(__VA_ARGS__); return 1; } } while (0)\n"
                    "int main()\n{\n" + body + "\n    printf(\"ok\\n\");\n    return 0;\n}\n")
