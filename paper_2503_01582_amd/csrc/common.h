@@ -11,7 +11,9 @@ namespace prenom {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWave = 64;
-constexpr int64_t kCus = 256;  // compute units of a gfx950 in one partition
+// Compute units of a gfx950 in one partition.  Plans are cut for them, so that they
+// are a function of the sizes alone; a device with fewer runs them in more rounds.
+constexpr int64_t kCus = 256;
 
 // Level table of a hash grid, passed by value to kernels.
 struct GridInfo {
@@ -392,7 +394,7 @@ extern const char* const kScatterPhaseNames[kScatterPhases];
 hipError_t launch_scatter_phase(const ScatterArgs& a, int phase, hipStream_t s);
 
 // MLP: forward writes (sigma, r, g, b) per sample; backward recomputes the
-// activations, writes dy and per-wave partial weight gradients.
+// activations, writes dy and per-block partial weight gradients.
 struct MlpShape {
     int32_t in_dim, width, hidden, dtype;
 };

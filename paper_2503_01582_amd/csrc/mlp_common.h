@@ -40,7 +40,6 @@ __device__ __forceinline__ float sigmoidf_(float z) { return 1.0f / (1.0f + __ex
 // Per-block LDS and launch parameters of the backward kernels.
 constexpr int kBwdWaves = 8;      // waves per block
 constexpr int kBwdMaxBlocks = 256;
-constexpr int kStagePad = 4;      // floats of padding per staged row
 
 // Blocks of the backward grid for n_s samples (each block writes one partial dW).
 inline int bwd_blocks(int64_t n_s)
@@ -105,13 +104,12 @@ __device__ __forceinline__ void merge_dw(float* __restrict__ dst, const floatx4 
 }
 
 // ---------------------------------------------------------------- 128-wide weight gradient
-// The weight-gradient kernels of the 128-wide MLP stage a chunk of
+// The weight-gradient kernel of the 128-wide FP32 MLP stages a chunk of
 // kDwChunk samples in LDS: every layer's delta and activation rows (pitch PW
 // floats), the input features (pitch PY, zero beyond IN) and the head adjoint
 // dO, all loaded with coalesced vector reads; the MFMA operands are then read
-// from LDS.  PW is chosen per operand pattern so those reads are free of bank
-// conflicts (FP32: lanes q step one sample, PW = 16 mod 64; 16-bit operands:
-// lanes q step four samples, PW = 4 mod 16).
+// from LDS.  Lanes q step one sample, so PW = 16 mod 64 keeps those reads free of
+// bank conflicts.
 constexpr int kDwChunk = 32;
 
 template <int W, int D, int PW, int PY>

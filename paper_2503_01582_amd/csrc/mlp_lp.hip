@@ -12,8 +12,9 @@
 // weight fragments hold W[16 to + j][16 ti + 4q .. 4q+3].
 //
 // The weight gradient contracts over the 16 samples of a tile with one MFMA
-// per (out tile, in tile), after the same per-wave LDS transpose as the FP32
-// form; the 8 waves of a block merge their dW in LDS and write one partial.
+// per (out tile, in tile), whose operands are staged in LDS in the MFMA type and
+// read transposed; the 8 waves of a block merge their dW in LDS and write one
+// partial.
 #include "mlp_common.h"
 
 namespace prenom {
@@ -498,7 +499,7 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_bwd_lp_batch(const MlpWo
 // of a neuron) go through LDS: deltas and activations of the 128 samples in the
 // MFMA type.  The waves split the output rows, 16 each, so the
 // block's partial is written without a merge.  Forward and transposed fragments
-// (86 KB with two layers) and the two staged arrays (68 KB) fill a CU's LDS.
+// (86 KB with two layers) and the two staged arrays (72 KB) fill a CU's LDS.
 // Nothing but the features, the head outputs and their adjoint is read: storing
 // the activations in the forward and the deltas between a chain and a
 // weight-gradient kernel moved 2.5 KB a sample and ran at the HBM's rate (48
