@@ -196,6 +196,39 @@ __device__ __forceinline__ int level_of(const int32_t* base, int n_levels, int v
     return l;
 }
 
+// Sum and maximum over a wave by DPP (row shifts, whose lanes before the row's
+// start read 0; then each row's last lane into the next rows): the last lane ends
+// with them.  For values that are not negative; every lane must call them.
+__device__ __forceinline__ float row_sum(float v)
+{
+    v += dpp_f32<0x111>(v);
+    v += dpp_f32<0x112>(v);
+    v += dpp_f32<0x114>(v);
+    return v + dpp_f32<0x118>(v);
+}
+
+__device__ __forceinline__ float row_max(float v)
+{
+    v = fmaxf(v, dpp_f32<0x111>(v));
+    v = fmaxf(v, dpp_f32<0x112>(v));
+    v = fmaxf(v, dpp_f32<0x114>(v));
+    return fmaxf(v, dpp_f32<0x118>(v));
+}
+
+__device__ __forceinline__ float wave_sum(float v)
+{
+    v = row_sum(v);
+    v += dpp_f32<0x142>(v);
+    return v + dpp_f32<0x143>(v);
+}
+
+__device__ __forceinline__ float wave_max(float v)
+{
+    v = row_max(v);
+    v = fmaxf(v, dpp_f32<0x142>(v));
+    return fmaxf(v, dpp_f32<0x143>(v));
+}
+
 // First entry of item (level l, block bx) of object o in the segment starts:
 // tiles[l] + 1 of them per item.
 __device__ __forceinline__ int64_t seg_index(const ScatterObj& o, int l, int bx)
@@ -266,16 +299,7 @@ __global__ __launch_bounds__(kPlaceThreads) void k_scatter_place(ScatterArgs a)
     for (int e = 0; e < 8; ++e)
         val[e] = make_float2(c.w[e] * d.x, c.w[e] * d.y);
     if (__ballot(has && !head)) run_sum(val, head || !has);
-    // Wave maximum of |dy| by DPP (row shifts, whose lanes past the row's end
-    // read 0, the identity of a maximum of absolute values; then each row's
-    // last lane into the next rows): the last lane ends with it.
-    float m = max_abs(d.x, d.y);
-    m = fmaxf(m, dpp_f32<0x111>(m));
-    m = fmaxf(m, dpp_f32<0x112>(m));
-    m = fmaxf(m, dpp_f32<0x114>(m));
-    m = fmaxf(m, dpp_f32<0x118>(m));
-    m = fmaxf(m, dpp_f32<0x142>(m));
-    m = fmaxf(m, dpp_f32<0x143>(m));
+    const float m = wave_max(max_abs(d.x, d.y));
     __syncthreads();
     if ((threadIdx.x & 63) == 63) atomicMax(&s_max, __float_as_uint(m));  // (m >= 0: ordered as its bits)
     // Rank of each record within its tile (LDS atomics), in units of kUnit; the
@@ -359,14 +383,15 @@ __global__ __launch_bounds__(kPlaceThreads) void k_scatter_place(ScatterArgs a)
     }
 }
 
-// Largest e with bound * 2^e < 2^62 (on any row's sum) and 8 m * 2^e < 2^50 (on
-// any record).
-__device__ __forceinline__ int fixed_point_exp(double bound, float m)
+// Largest e with bound * 2^e < 2^62 (on any row's sum; rounding the bound itself
+// takes a part of the factor 2 that is left to 2^63) and 8 m * 2^e < 2^50 (on any
+// record).  A bound beyond FP32 is below 2^157: 2^20 blocks of 2^9 * 2^128.
+__device__ __forceinline__ int fixed_point_exp(float bound, float m)
 {
-    if (!(bound > 0.0)) return 0;
-    int ex = 0, evx = 0;
-    frexp(bound, &ex);   // bound < 2^ex
-    frexpf(m, &evx);     // m < 2^evx
+    if (!(bound > 0.0f)) return 0;
+    int ex = 157, evx = 0;
+    if (isfinite(bound)) frexpf(bound, &ex);  // bound < 2^ex
+    frexpf(m, &evx);                          // m < 2^evx
     return min(62 - ex, 47 - evx);
 }
 
@@ -381,8 +406,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a
     constexpr int EB = kCompact ? kRecExpBitsC : kRecExpBits, MB = kCompact ? kRecMantBitsC : kRecMantBits;
     __shared__ unsigned long long acc[2 * kTileRows];  // fixed point: feature 0 rows, then feature 1 rows
     __shared__ uint2 head[kHeads];  // segments of kHeads blocks: start and end, max |dy| of the block
-    __shared__ double w_bound[kReduceThreads / 64];
-    __shared__ float w_max[kReduceThreads / 64];
+    __shared__ float2 w_part[kReduceThreads / 64];  // bound and maximum of a wave
     const int64_t ritem = blockIdx.x;
     const ScatterObj& o = sobj<kMany>(a, last_le<kMany>(a, ritem, [](const ScatterObj& v) { return v.ritem_off; }));
     const int rl = (int)(ritem - o.ritem_off);
@@ -407,32 +431,23 @@ __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a
         const uint16_t* p = seg + (int64_t)b * nt1;
         return make_uint2((uint32_t)p[0] | (uint32_t)p[1] << 16, __float_as_uint(a.block_max[item0 + b]));
     };
-    double bound = 0.0;  // of the rows' sums, and
+    float bound = 0.0f;  // of the rows' sums, and
     float m = 0.0f;      // the largest |dy| of the blocks that reach the tile
     for (int i = threadIdx.x; i < b1 - b0; i += kReduceThreads) {
         const uint2 h = segment(b0 + i);
         if (i < kHeads) head[i] = h;
         const uint32_t n = (h.x >> 16) - (h.x & 0xffffu);
         const float bm = n ? __uint_as_float(h.y) : 0.0f;
-        bound += (double)min(8u * n, (uint32_t)kSamplesPerBlock) * (double)bm;
+        bound = fmaf((float)min(8u * n, (uint32_t)kSamplesPerBlock), bm, bound);
         m = fmaxf(m, bm);
     }
-#pragma unroll
-    for (int dd = 32; dd >= 1; dd >>= 1) {
-        bound += __shfl_xor(bound, dd);
-        m = fmaxf(m, __shfl_xor(m, dd));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        w_bound[threadIdx.x >> 6] = bound;
-        w_max[threadIdx.x >> 6] = m;
-    }
+    bound = wave_sum(bound);
+    m = wave_max(m);
+    if ((threadIdx.x & 63) == 63) w_part[threadIdx.x >> 6] = make_float2(bound, m);
     __syncthreads();  // (also orders the cleared accumulators before the additions)
-    bound = 0.0;
-    for (int w = 0; w < kReduceThreads / 64; ++w) {
-        bound += w_bound[w];
-        m = fmaxf(m, w_max[w]);
-    }
-    const int ex = __builtin_amdgcn_readfirstlane(fixed_point_exp(bound, m));
+    static_assert(kReduceThreads / 64 == 16, "a wave's partials fill a row");
+    const float2 part_of = w_part[threadIdx.x & 15];
+    const int ex = __builtin_amdgcn_readlane(fixed_point_exp(row_sum(part_of.x), row_max(part_of.y)), 15);
     for (int c0 = b0; c0 < b1; c0 += kHeads) {
         const int n = min(kHeads, b1 - c0);
         if (c0 != b0) {
