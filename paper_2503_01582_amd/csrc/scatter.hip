@@ -58,7 +58,9 @@ constexpr int kSegGroups = kReduceThreads / kSegLanes;  // segments in flight pe
 // Records in flight per lane: a step covers 80 records of a segment, so the
 // segments of a 2^19-row level (4096 / 64 = 64 records on average) take one.
 constexpr int kSegStep = 5;
-constexpr int kHeads = 2048;  // blocks whose segment bounds a workgroup holds in LDS
+// Blocks whose segment bounds a workgroup holds: in LDS at a time, and in registers
+// from the pass that finds the scale (each thread's, kReduceThreads apart).
+constexpr int kHeads = 2048, kHeldHeads = 8;
 constexpr int kCombineThreads = 256;
 // Reduce items of a pass (scatter_split): about kReduceItems of even size, so
 // that the CUs stay busy to the end whatever the tables' sizes, but none
@@ -398,8 +400,10 @@ __device__ __forceinline__ int fixed_point_exp(float bound, float m)
 // One workgroup per reduce item: blocks [b0, b1) of one tile.  Its segments
 // are read 16 lanes each (128 contiguous bytes a load), the next step's records
 // requested before the current one's are added.  Bound by the LDS atomics
-// (two 64-bit adds per record).  The bounds of the first kHeads segments stay in
-// LDS from the pass that finds the scale; longer ranges read theirs twice.
+// (two 64-bit adds per record).  The scale needs all the segments' bounds before
+// the first record: they are read at once and kept (ranges of more than 8192
+// blocks read the others twice; reading them in turn, and all beyond the first
+// 2048 twice, took 26 us of the 865 of 65536 rays x 64, 16 levels of 2^19 rows).
 template <bool kMany, bool kCompact>
 __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a)
 {
@@ -431,27 +435,47 @@ __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a
         const uint16_t* p = seg + (int64_t)b * nt1;
         return make_uint2((uint32_t)p[0] | (uint32_t)p[1] << 16, __float_as_uint(a.block_max[item0 + b]));
     };
+    const int n_range = b1 - b0;
+    uint2 held[kHeldHeads];
+#pragma unroll
+    for (int u = 0; u < kHeldHeads; ++u) {
+        const int i = (int)threadIdx.x + u * kReduceThreads;
+        held[u] = make_uint2(0u, 0u);
+        if (u * kReduceThreads < n_range && i < n_range) held[u] = segment(b0 + i);
+    }
     float bound = 0.0f;  // of the rows' sums, and
     float m = 0.0f;      // the largest |dy| of the blocks that reach the tile
-    for (int i = threadIdx.x; i < b1 - b0; i += kReduceThreads) {
-        const uint2 h = segment(b0 + i);
-        if (i < kHeads) head[i] = h;
+    auto note = [&](uint2 h) {
         const uint32_t n = (h.x >> 16) - (h.x & 0xffffu);
         const float bm = n ? __uint_as_float(h.y) : 0.0f;
         bound = fmaf((float)min(8u * n, (uint32_t)kSamplesPerBlock), bm, bound);
         m = fmaxf(m, bm);
-    }
+    };
+#pragma unroll
+    for (int u = 0; u < kHeldHeads; ++u) note(held[u]);
+    for (int i = (int)threadIdx.x + kHeldHeads * kReduceThreads; i < n_range; i += kReduceThreads) note(segment(b0 + i));
+    static_assert(kHeads == 2 * kReduceThreads && kHeldHeads % 2 == 0, "two bounds a thread and chunk");
+    auto to_lds = [&] {
+        head[threadIdx.x] = held[0];
+        head[kReduceThreads + threadIdx.x] = held[1];
+#pragma unroll
+        for (int u = 2; u < kHeldHeads; ++u) held[u - 2] = held[u];
+    };
+    to_lds();
     bound = wave_sum(bound);
     m = wave_max(m);
     if ((threadIdx.x & 63) == 63) w_part[threadIdx.x >> 6] = make_float2(bound, m);
     __syncthreads();  // (also orders the cleared accumulators before the additions)
     static_assert(kReduceThreads / 64 == 16, "a wave's partials fill a row");
-    const float2 part_of = w_part[threadIdx.x & 15];
-    const int ex = __builtin_amdgcn_readlane(fixed_point_exp(row_sum(part_of.x), row_max(part_of.y)), 15);
+    const float2 of_wave = w_part[threadIdx.x & 15];
+    int ex = 0;
     for (int c0 = b0; c0 < b1; c0 += kHeads) {
         const int n = min(kHeads, b1 - c0);
         if (c0 != b0) {
-            for (int i = threadIdx.x; i < n; i += kReduceThreads) head[i] = segment(c0 + i);
+            if (c0 - b0 < kHeldHeads * kReduceThreads)
+                to_lds();
+            else
+                for (int i = threadIdx.x; i < n; i += kReduceThreads) head[i] = segment(c0 + i);
             __syncthreads();
         }
         // Steps of up to kSegStep * kSegLanes records of one segment: the lane's
@@ -471,9 +495,9 @@ __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a
             const int64_t base = (item0 + c0 + min(b, n - 1)) * kRecordsPerBlock;
             st.any = b < n;
             st.left = b < n ? end - p - ln : 0;
-            // a record (qx, qy, r) is worth (qx, qy) 2^(E - r - (MB - 1)); in
-            // fixed point at 2^ex that is (qx, qy) 2^(sh0 - r)
-            st.sh0 = block_rec_exp(__uint_as_float(h.y)) - (MB - 1) + ex;
+            // a record (qx, qy, r) is worth (qx, qy) 2^(sh0 - r); in fixed point
+            // that is (qx, qy) 2^(sh0 + ex - r)
+            st.sh0 = block_rec_exp(__uint_as_float(h.y)) - (MB - 1);
 #pragma unroll
             for (int u = 0; u < kSegStep; ++u) {
                 const int i = p + ln + u * kSegLanes;
@@ -499,20 +523,23 @@ __global__ __launch_bounds__(kReduceThreads) void k_scatter_reduce(ScatterArgs a
             }
         };
         auto add = [&](const Step& st) {
+            const int sh0 = st.sh0 + ex;
 #pragma unroll
             for (int u = 0; u < kSegStep; ++u) {
                 uint32_t key;
                 int r, qx, qy;
                 decode_record<EB, MB>(st.lo[u], st.hi[u], key, r, qx, qy);
                 if (u * kSegLanes < st.left) {
-                    atomicAdd(&acc[key], (unsigned long long)scale_mantissa(qx, st.sh0 - r));
-                    atomicAdd(&acc[kTileRows + key], (unsigned long long)scale_mantissa(qy, st.sh0 - r));
+                    atomicAdd(&acc[key], (unsigned long long)scale_mantissa(qx, sh0 - r));
+                    atomicAdd(&acc[kTileRows + key], (unsigned long long)scale_mantissa(qy, sh0 - r));
                 }
             }
         };
         Step s0, s1, s2;
         fetch(s0);
         fetch(s1);
+        if (c0 == b0)  // (under the first records' loads)
+            ex = __builtin_amdgcn_readlane(fixed_point_exp(row_sum(of_wave.x), row_max(of_wave.y)), 15);
         while (s0.any) {
             fetch(s2);
             add(s0);
