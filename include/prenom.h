@@ -173,7 +173,8 @@ typedef struct prenom_render_cfg {
 } prenom_render_cfg;
 
 /* Bytes of device workspace render_fwd/render_bwd need for this batch, in the
- * stored (recompute = 0) or the recompute (1) form; 0 on invalid input. */
+ * stored (recompute = 0) or the recompute (1) form; 0 on invalid input.  It does
+ * not fall as n_rays grows: a workspace of the largest call does for the others. */
 size_t prenom_workspace_size(const prenom_arch* arch, int64_t n_rays, int32_t n_samples, int32_t recompute);
 
 /* ------------------------------------------------------------------------
@@ -322,8 +323,8 @@ prenom_status prenom_encode(const prenom_arch* arch, const float* table, const f
  * FP64 arithmetic; sums in a fixed order (results do not depend on
  * scheduling).  1 <= n_points <= PRENOM_MAX_YAW_POINTS, 1 <= n_yaw <=
  * PRENOM_MAX_YAWS, 2 <= prior_res <= PRENOM_MAX_PRIOR_RES; workspace: >=
- * prenom_canonical_yaw_workspace_size bytes (0 for invalid sizes), 256-byte
- * aligned.  Errors: PRENOM_ERR_SHAPE, PRENOM_ERR_INVALID_ARG,
+ * prenom_canonical_yaw_workspace_size bytes (0 for invalid sizes; no fewer for
+ * more points or yaws), 256-byte aligned.  Errors: PRENOM_ERR_SHAPE, PRENOM_ERR_INVALID_ARG,
  * PRENOM_ERR_WORKSPACE, checked before any launch.
  * ---------------------------------------------------------------------- */
 #define PRENOM_MAX_YAWS 4096
